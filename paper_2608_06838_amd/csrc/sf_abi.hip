@@ -377,10 +377,11 @@ sf_status conv_resolve(const sf_conv_shape *sh, ConvShape &r) {
     return SF_OK;
 }
 
-// tokens per workgroup row: 256 in the forward; the backward grows it with L
-// so that at most 256 dw partials per batch go through the workspace
+// tokens per block: the forward's is one thread's run (256 when that fills the
+// chip); the backward's is what one dw partial covers and grows with L so that
+// at most 256 partials per batch go through the workspace
 int64_t conv_block(const ConvShape &r, bool bwd) {
-    if (!bwd) return 256;
+    if (!bwd) return sf::conv_fwd_run(r.B, r.C, r.L);
     const int64_t per = (r.L + 255) / 256;
     return std::max<int64_t>(256, (per + 63) / 64 * 64);
 }

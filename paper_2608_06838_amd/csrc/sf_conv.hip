@@ -6,11 +6,17 @@
 //
 // Pure streaming work (W <= 4 multiply-adds per element): the roofline is HBM.
 // Each thread owns 8 consecutive channels (one 16-byte row piece in bf16,
-// two in fp32) of one batch and walks a block of tokens in order, keeping the
-// previous W-1 inputs in registers, so every input row is read once per block
-// (plus a W-1 token halo) and a wave's 64 lanes read 64 consecutive 16-byte
+// two in fp32) of one batch and walks a run of tokens in order, keeping the
+// previous W-1 inputs in registers, so every input row is read once per run
+// (plus a W-1 token halo) and the lanes of a wave read consecutive 16-byte
 // pieces of a row.  Loads go out in groups of 8 tokens; outputs are written
 // with non-temporal stores.
+//
+// A run's length is a balance: 256 tokens make the halo 1% of the reads, but a
+// small call then has too few waves to hide the latency of its serial run
+// (B 2, L 1037, C 1536: 10 workgroups).  The launcher therefore shortens the
+// runs until the launch has CONV_FILL threads (six waves per CU), down to one
+// load group; the halos of short runs come from the cache.
 //
 // Backward: du_t = dy_t * act'(u_t); dxh_s = sum_j w[j] du_{s+W-1-j} plus
 // dtail_out[s-L+W-1] for the last W-1 positions; dw[c][j] = sum_{b,t} du_t
@@ -21,13 +27,14 @@
 #include "sf_device.hpp"
 #include "sf_launch.hpp"
 
+#include <type_traits>
+
 namespace sf {
 
 namespace {
 
 constexpr int CONV_NT = 256;  // threads per workgroup
-constexpr int CONV_E = 8;     // channels per thread
-constexpr int CONV_G = 8;     // tokens per load group (4 and 16 measured slower)
+// CONV_E channels per thread; CONV_G tokens per load group (4 and 16 measured slower)
 
 template <typename T>
 struct Row8 {
@@ -99,10 +106,24 @@ __device__ __forceinline__ float dact_f(float u) {
     }
 }
 
-// channel group of this thread, or -1 past the last one
-__device__ __forceinline__ int conv_group(const ConvArgs &a) {
-    const int cg = (int)blockIdx.x * CONV_NT + (int)threadIdx.x;
-    return cg < a.C / CONV_E ? cg : -1;
+// (channel group, token block) of this thread; false past the last one.  Launches
+// that fill the chip run over a grid (groups, blocks), so that a workgroup's rows
+// stay aligned (flattened, with 1920 groups, L 106496: 4.46 against 3.41 ms);
+// smaller ones run over the flattened pairs, channel groups fastest, so that no
+// lane idles where C / 8 is far from a multiple of the workgroup.
+template <bool FLAT>
+__device__ __forceinline__ bool conv_pair(const ConvArgs &a, int &cg, int64_t &tb) {
+    const int ncg = a.C / CONV_E;
+    if constexpr (FLAT) {
+        const int64_t i = (int64_t)blockIdx.x * CONV_NT + threadIdx.x;
+        tb = i / ncg;
+        cg = (int)(i - tb * ncg);
+        return tb < a.nTB;
+    } else {
+        tb = blockIdx.y;
+        cg = (int)blockIdx.x * CONV_NT + (int)threadIdx.x;
+        return cg < ncg;
+    }
 }
 
 // xh_s for s in [-(W-1), L): x row or tail row (zero without a tail)
@@ -122,13 +143,14 @@ __device__ __forceinline__ void load_xh(const ConvArgs &a, int64_t b, int c0, in
     }
 }
 
-template <typename T, int W, bool SILU>
+template <typename T, int W, bool SILU, bool FLAT>
 __global__ void __launch_bounds__(CONV_NT) k_conv_fwd(ConvArgs a) {
-    const int cg = conv_group(a);
-    if (cg < 0) return;
+    int cg;
+    int64_t tb;
+    if (!conv_pair<FLAT>(a, cg, tb)) return;
     const int c0 = cg * CONV_E;
     const int64_t b = blockIdx.z;
-    const int64_t t0 = (int64_t)blockIdx.y * a.T;
+    const int64_t t0 = tb * a.T;
     const int64_t t1 = t0 + a.T < a.L ? t0 + a.T : a.L;
     float wt[W][CONV_E];
 #pragma unroll
@@ -176,114 +198,155 @@ __global__ void __launch_bounds__(CONV_NT) k_conv_fwd(ConvArgs a) {
     }
 }
 
-template <typename T, int W, bool SILU>
-__global__ void __launch_bounds__(CONV_NT) k_conv_bwd(ConvArgs a) {
-    const int cg = conv_group(a);
-    if (cg < 0) return;
+// TSUB runs per token block.  TSUB = 1: a thread's run is its whole block.
+// TSUB > 1: a workgroup holds CONV_NT / TSUB channel groups of one block, each cut into
+// TSUB runs, whose dw sums are added in LDS in run order, so the workspace
+// keeps one partial per block whatever the split.  (B 2, L 1037, C 1536 fp32,
+// forward and backward: 309 us with whole blocks, 41 us with runs of 8.)
+// Registers: the bf16 form is held to two waves per SIMD (left alone, the split
+// forms take one: 552 against 384 us at L 16384, C 15360); the fp32 form has 64
+// more registers of loads in flight and runs faster at one (L 8192, C 15360:
+// 352 against 465 us with half the load group).
+template <typename T, int W, bool SILU, int TSUB>
+__global__ void __launch_bounds__(CONV_NT, sizeof(T) == 2 ? 2 : 1) k_conv_bwd(ConvArgs a) {
+    constexpr int CGW = CONV_NT / TSUB, NW8 = CONV_E * W;
+    const int sub = TSUB > 1 ? (int)threadIdx.x / CGW : 0;
+    int cg;
+    int64_t tb;
+    if constexpr (TSUB > 1) {
+        cg = (int)blockIdx.x * CGW + (int)threadIdx.x % CGW;
+        tb = blockIdx.y;
+    } else {
+        if (!conv_pair<false>(a, cg, tb)) return;
+    }
+    const bool live = TSUB == 1 || cg < a.C / CONV_E;
     const int c0 = cg * CONV_E;
     const int64_t b = blockIdx.z;
-    const int64_t t0 = (int64_t)blockIdx.y * a.T;
-    const int64_t t1 = t0 + a.T < a.L ? t0 + a.T : a.L;  // tokens whose dx and dw this block owns
-    const int64_t tend = t1 + (W - 1);                    // du needed up to tend - 1 (zero from L on)
-    float wt[W][CONV_E];
-#pragma unroll
-    for (int e = 0; e < CONV_E; ++e)
-#pragma unroll
-        for (int j = 0; j < W; ++j) wt[j][e] = a.w[(int64_t)(c0 + e) * W + j];
-    float h[W][CONV_E];   // xh window of the token whose du is produced next
-    float du[W][CONV_E];  // du[W-1] = du_t, du[j] = du_{t-W+1+j}
+    const int64_t run = a.T / TSUB;
+    const int64_t t0 = tb * a.T + sub * run;
+    const int64_t t1 = t0 + run < a.L ? t0 + run : a.L;  // tokens whose dx and dw this run owns
+    const int64_t tend = t1 + (W - 1);                   // du needed up to tend - 1 (zero from L on)
     float dw[W][CONV_E];
 #pragma unroll
     for (int j = 0; j < W; ++j)
 #pragma unroll
-        for (int e = 0; e < CONV_E; ++e) {
-            du[j][e] = 0.f;
-            dw[j][e] = 0.f;
-        }
+        for (int e = 0; e < CONV_E; ++e) dw[j][e] = 0.f;
+    if (live && t0 < a.L) {
+        float wt[W][CONV_E];
 #pragma unroll
-    for (int j = 0; j < W - 1; ++j) load_xh<T>(a, b, c0, t0 - (W - 1) + j, h[j]);
-    const T *xb = (const T *)a.x + b * a.sx_b + c0;
-    const T *dyb = (const T *)a.dy + b * a.sx_b + c0;
-    T *dxb = (T *)a.dx + b * a.sx_b + c0;
-    const int64_t tail0 = a.L - (W - 1);  // first position that feeds tail_out
-    // the first block also emits dxh_s for s < 0 (dtail_in), so it starts emitting at -(W-1)
-    const int64_t s_first = t0 == 0 ? -(int64_t)(W - 1) : t0;
-    for (int64_t tg = t0; tg < tend; tg += CONV_G) {
-        Row8<T> rx[CONV_G], rd[CONV_G];
+        for (int e = 0; e < CONV_E; ++e)
 #pragma unroll
-        for (int g = 0; g < CONV_G; ++g) {
-            const int64_t t = tg + g;
-            if (t < tend && t < a.L) {
-                rx[g].load(xb + t * a.sx_l);
-                rd[g].load(dyb + t * a.sx_l);
+            for (int j = 0; j < W; ++j) wt[j][e] = a.w[(int64_t)(c0 + e) * W + j];
+        float h[W][CONV_E];   // xh window of the token whose du is produced next
+        float du[W][CONV_E];  // du[W-1] = du_t, du[j] = du_{t-W+1+j}
+#pragma unroll
+        for (int j = 0; j < W; ++j)
+#pragma unroll
+            for (int e = 0; e < CONV_E; ++e) du[j][e] = 0.f;
+#pragma unroll
+        for (int j = 0; j < W - 1; ++j) load_xh<T>(a, b, c0, t0 - (W - 1) + j, h[j]);
+        const T *xb = (const T *)a.x + b * a.sx_b + c0;
+        const T *dyb = (const T *)a.dy + b * a.sx_b + c0;
+        T *dxb = (T *)a.dx + b * a.sx_b + c0;
+        const int64_t tail0 = a.L - (W - 1);  // first position that feeds tail_out
+        // the first run also emits dxh_s for s < 0 (dtail_in), so it starts emitting at -(W-1)
+        const int64_t s_first = t0 == 0 ? -(int64_t)(W - 1) : t0;
+        for (int64_t tg = t0; tg < tend; tg += CONV_G) {
+            Row8<T> rx[CONV_G], rd[CONV_G];
+#pragma unroll
+            for (int g = 0; g < CONV_G; ++g) {
+                const int64_t t = tg + g;
+                if (t < tend && t < a.L) {
+                    rx[g].load(xb + t * a.sx_l);
+                    rd[g].load(dyb + t * a.sx_l);
+                }
             }
-        }
 #pragma unroll
-        for (int g = 0; g < CONV_G; ++g) {
-            const int64_t t = tg + g;
-            if (t < tend) {
-#pragma unroll
-                for (int j = 0; j < W - 1; ++j)
-#pragma unroll
-                    for (int e = 0; e < CONV_E; ++e) du[j][e] = du[j + 1][e];
-                if (t < a.L) {
-                    rx[g].to_f32(h[W - 1]);
-                    float dy[CONV_E];
-                    rd[g].to_f32(dy);
-#pragma unroll
-                    for (int e = 0; e < CONV_E; ++e) {
-                        float u = 0.f;
-#pragma unroll
-                        for (int j = 0; j < W; ++j) u = fmaf(wt[j][e], h[j][e], u);
-                        du[W - 1][e] = dy[e] * dact_f<SILU>(u);
-                    }
-                    if (t < t1) {
-#pragma unroll
-                        for (int j = 0; j < W; ++j)
-#pragma unroll
-                            for (int e = 0; e < CONV_E; ++e) dw[j][e] = fmaf(du[W - 1][e], h[j][e], dw[j][e]);
-                    }
+            for (int g = 0; g < CONV_G; ++g) {
+                const int64_t t = tg + g;
+                if (t < tend) {
 #pragma unroll
                     for (int j = 0; j < W - 1; ++j)
 #pragma unroll
-                        for (int e = 0; e < CONV_E; ++e) h[j][e] = h[j + 1][e];
-                } else {
+                        for (int e = 0; e < CONV_E; ++e) du[j][e] = du[j + 1][e];
+                    if (t < a.L) {
+                        rx[g].to_f32(h[W - 1]);
+                        float dy[CONV_E];
+                        rd[g].to_f32(dy);
 #pragma unroll
-                    for (int e = 0; e < CONV_E; ++e) du[W - 1][e] = 0.f;
-                }
-                // dxh_s, s = t - W + 1, is complete: sum_j w[j] du_{s+W-1-j}
-                const int64_t s = t - (W - 1);
-                if (s >= s_first && s < t1) {
-                    float dx[CONV_E];
+                        for (int e = 0; e < CONV_E; ++e) {
+                            float u = 0.f;
 #pragma unroll
-                    for (int e = 0; e < CONV_E; ++e) {
-                        float acc = 0.f;
+                            for (int j = 0; j < W; ++j) u = fmaf(wt[j][e], h[j][e], u);
+                            du[W - 1][e] = dy[e] * dact_f<SILU>(u);
+                        }
+                        if (t < t1) {
 #pragma unroll
-                        for (int j = 0; j < W; ++j) acc = fmaf(wt[j][e], du[W - 1 - j][e], acc);
-                        dx[e] = acc;
+                            for (int j = 0; j < W; ++j)
+#pragma unroll
+                                for (int e = 0; e < CONV_E; ++e) dw[j][e] = fmaf(du[W - 1][e], h[j][e], dw[j][e]);
+                        }
+#pragma unroll
+                        for (int j = 0; j < W - 1; ++j)
+#pragma unroll
+                            for (int e = 0; e < CONV_E; ++e) h[j][e] = h[j + 1][e];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < CONV_E; ++e) du[W - 1][e] = 0.f;
                     }
-                    if (s >= tail0 && a.dtail_out) {
-                        const float *p = a.dtail_out + (b * (W - 1) + (s - tail0)) * (int64_t)a.C + c0;
+                    // dxh_s, s = t - W + 1, is complete: sum_j w[j] du_{s+W-1-j}
+                    const int64_t s = t - (W - 1);
+                    if (s >= s_first && s < t1) {
+                        float dx[CONV_E];
 #pragma unroll
-                        for (int e = 0; e < CONV_E; ++e) dx[e] += p[e];
-                    }
-                    if (s >= 0) {
-                        store_row8<T>(dxb + s * a.sx_l, dx);
-                    } else if (a.dtail_in) {
-                        float *p = a.dtail_in + (b * (W - 1) + (W - 1 + s)) * (int64_t)a.C + c0;
+                        for (int e = 0; e < CONV_E; ++e) {
+                            float acc = 0.f;
 #pragma unroll
-                        for (int e = 0; e < CONV_E; ++e) p[e] = dx[e];
+                            for (int j = 0; j < W; ++j) acc = fmaf(wt[j][e], du[W - 1 - j][e], acc);
+                            dx[e] = acc;
+                        }
+                        if (s >= tail0 && a.dtail_out) {
+                            const float *p = a.dtail_out + (b * (W - 1) + (s - tail0)) * (int64_t)a.C + c0;
+#pragma unroll
+                            for (int e = 0; e < CONV_E; ++e) dx[e] += p[e];
+                        }
+                        if (s >= 0) {
+                            store_row8<T>(dxb + s * a.sx_l, dx);
+                        } else if (a.dtail_in) {
+                            float *p = a.dtail_in + (b * (W - 1) + (W - 1 + s)) * (int64_t)a.C + c0;
+#pragma unroll
+                            for (int e = 0; e < CONV_E; ++e) p[e] = dx[e];
+                        }
                     }
                 }
             }
         }
     }
-    // this block's dw partial: ws[(b * nTB + block)][c][j]
-    float *pw = a.ws + ((b * a.nTB + blockIdx.y) * (int64_t)a.C + c0) * W;
+    // the block's dw partial: ws[(b * nTB + block)][c][j]
+    float *pw = a.ws + ((b * a.nTB + tb) * (int64_t)a.C) * W;
+    if constexpr (TSUB == 1) {
 #pragma unroll
-    for (int e = 0; e < CONV_E; ++e)
+        for (int e = 0; e < CONV_E; ++e)
 #pragma unroll
-        for (int j = 0; j < W; ++j) pw[e * W + j] = dw[j][e];
+            for (int j = 0; j < W; ++j) pw[(int64_t)c0 * W + e * W + j] = dw[j][e];
+    } else {
+        // [run][entry][channel group], groups fastest (consecutive lanes, consecutive banks)
+        __shared__ float sdw[TSUB * NW8 * CGW];
+#pragma unroll
+        for (int e = 0; e < CONV_E; ++e)
+#pragma unroll
+            for (int j = 0; j < W; ++j) sdw[(sub * NW8 + e * W + j) * CGW + (int)threadIdx.x % CGW] = dw[j][e];
+        __syncthreads();
+        for (int i = (int)threadIdx.x; i < NW8 * CGW; i += CONV_NT) {
+            const int g = i / NW8, k = i % NW8;  // entry k of group g: consecutive lanes write consecutive floats
+            const int64_t cgi = (int64_t)blockIdx.x * CGW + g;
+            if (cgi >= a.C / CONV_E) break;
+            float sum = 0.f;
+#pragma unroll 4
+            for (int r = 0; r < TSUB; ++r) sum += sdw[(r * NW8 + k) * CGW + g];
+            pw[cgi * NW8 + k] = sum;
+        }
+    }
 }
 
 // dw[c][j] = sum over (batch, token block) of the partials, in that order.
@@ -314,11 +377,28 @@ __global__ void __launch_bounds__(CONV_NT) k_conv_copy(const float *src, float *
 
 template <typename T, int W, bool SILU>
 hipError_t conv_td(bool bwd, const ConvArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    const dim3 grid((unsigned)((a.C / CONV_E + CONV_NT - 1) / CONV_NT), (unsigned)a.nTB, (unsigned)a.B);
-    if (!bwd) {
-        hipExtLaunchKernelGGL((k_conv_fwd<T, W, SILU>), grid, dim3(CONV_NT), 0, s, e0, e1, 0, a);
+    const int64_t ncg = a.C / CONV_E;
+    const dim3 rows((unsigned)((ncg + CONV_NT - 1) / CONV_NT), (unsigned)a.nTB, (unsigned)a.B);
+    if (!bwd && a.T == 256) {
+        hipExtLaunchKernelGGL((k_conv_fwd<T, W, SILU, false>), rows, dim3(CONV_NT), 0, s, e0, e1, 0, a);
+    } else if (!bwd) {
+        const dim3 flat((unsigned)((ncg * a.nTB + CONV_NT - 1) / CONV_NT), 1, (unsigned)a.B);
+        hipExtLaunchKernelGGL((k_conv_fwd<T, W, SILU, true>), flat, dim3(CONV_NT), 0, s, e0, e1, 0, a);
     } else {
-        hipExtLaunchKernelGGL((k_conv_bwd<T, W, SILU>), grid, dim3(CONV_NT), 0, s, e0, nullptr, 0, a);
+        // runs per block: doubled until the launch fills the chip, at most one per load group
+        const int64_t threads = ncg * a.nTB * a.B;
+        int sub = 1;
+        while (sub < 32 && threads * sub < (sizeof(T) == 2 ? CONV_FILL_BWD16 : CONV_FILL_BWD32)) sub *= 2;
+        auto split = [&](auto tsub) {
+            constexpr int TS = decltype(tsub)::value, CGW = CONV_NT / TS;
+            const dim3 grid((unsigned)((ncg + CGW - 1) / CGW), (unsigned)a.nTB, (unsigned)a.B);
+            hipExtLaunchKernelGGL((k_conv_bwd<T, W, SILU, TS>), grid, dim3(CONV_NT), 0, s, e0, nullptr, 0, a);
+        };
+        if (sub == 1) split(std::integral_constant<int, 1>());
+        else if (sub <= 4) split(std::integral_constant<int, 4>());
+        else if (sub <= 8) split(std::integral_constant<int, 8>());
+        else if (sub <= 16) split(std::integral_constant<int, 16>());
+        else split(std::integral_constant<int, 32>());
         const int64_t n = (int64_t)a.C * W;
         hipExtLaunchKernelGGL(k_conv_dw_sum, dim3((unsigned)((n + DWS_NT - 1) / DWS_NT)), dim3(DWS_NT), 0, s,
                               nullptr, e1, 0, (const float *)a.ws, a.dw, n, (int64_t)a.B * a.nTB);

@@ -47,8 +47,8 @@ hipError_t launch_kernel(int kind, int io, int D, const SegArgs &a, hipStream_t 
 hipError_t launch_kernel_vg(int kind, int io, int D, const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_state_copy(const float *src, float *dst, int64_t n, hipStream_t s);
 
-// Short convolution (sf_conv.hip).  Token block T per workgroup row; nTB
-// blocks per batch; ws holds B * nTB dw partials of C * W floats.
+// Short convolution (sf_conv.hip).  Token blocks of T; nTB blocks per batch;
+// ws holds B * nTB dw partials of C * W floats.
 struct ConvArgs {
     const void *x;
     const float *w;
@@ -66,6 +66,19 @@ struct ConvArgs {
     int64_t L, T, sx_b, sx_l;
 };
 int conv_channels_per_thread();
+constexpr int CONV_E = 8, CONV_G = 8;          // channels per thread, tokens per load group
+// Threads that fill the chip, below which runs are shortened.  Forward: six waves
+// per CU (bf16, 101248 threads: whole runs 214 us, halves 226).  Backward: the
+// split runs cost halos, so the line lies where they stop paying (whole blocks /
+// runs, us): bf16 122880 threads 350/384, 101248 340/343, 50624 253/199; fp32
+// 61440 threads 318/352, 50624 309/346, 25312 253/200.
+constexpr int64_t CONV_FILL = 256 * 384, CONV_FILL_BWD16 = 256 * 384, CONV_FILL_BWD32 = 256 * 160;
+// tokens per thread of the forward: 256, halved until the launch fills the chip
+inline int64_t conv_fwd_run(int64_t B, int64_t C, int64_t L) {
+    int64_t T = 256;
+    while (T > CONV_G && B * (C / CONV_E) * ((L + T - 1) / T) < CONV_FILL) T /= 2;
+    return T;
+}
 
 // Gated delta rule (sf_gdn.hip).  n_super superchunks of ts tokens per
 // (batch, head); with n_super > 1 the workspace holds the boundary states

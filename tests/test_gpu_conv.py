@@ -160,3 +160,29 @@ def test_conv_full_size_sampled():
     ref = run_oracle(sub, w["act"])
     got_sub = {k: pick(v) for k, v in got.items()}
     compare(got_sub, ref, "bf16", W)
+
+
+@pytest.mark.parametrize("io,C,L", [
+    ("bf16", 264, 8 * 61 + 1),    # 32 runs per block, a lone token in the last run
+    ("bf16", 2056, 7 * 256 + 17),  # 16
+    ("bf16", 4104, 9 * 256 - 1),   # 8
+    ("bf16", 15368, 11 * 256 + 5),  # 4
+    ("bf16", 15368, 53 * 256 + 3),  # whole blocks; 128-token and whole runs forward
+    ("f32", 5128, 5 * 256 + 2),
+    ("f32", 15368, 22 * 256 + 9),
+])
+def test_conv_run_splits(io, C, L):
+    """Every split of a token block into runs, with a ragged last block, a last
+    workgroup of channel groups that is not full and tails on both sides,
+    against the oracle on sampled channels."""
+    W = 4
+    say(f"[conv] run splits io={io} C={C} L={L}")
+    inp = synth.make_conv_inputs(1, L, C, W, io=io, seed=3600 + L, device=DEV)
+    got = run_gpu(inp, "silu")
+    cols = torch.from_numpy(np.unique(np.concatenate([np.arange(0, 16), np.arange(120, 136), np.arange(C - 16, C)]))).to(DEV)
+
+    def pick(v):
+        return v[..., cols] if v.dim() == 3 else v[cols]
+
+    ref = run_oracle({k: pick(v).cpu() for k, v in inp.items()}, "silu")
+    compare({k: pick(v) for k, v in got.items()}, ref, io, W)
