@@ -1161,11 +1161,24 @@ sf_status sf_conv_bwd(const sf_conv_shape *shape, const void *x, const float *w,
 
 namespace {
 
-// Gated delta rule: superchunk length.  One walk workgroup fills a CU (its
-// LDS), so `slots` = CUs; the prep walk ([M | N], twice the columns) costs
-// about kPrep chunk steps of the output walk per chunk and one scan step about
-// kScan.  Choose chunks per superchunk m minimising
-//   rounds(walk) * m + kPrep * rounds(prep) * m + kScan * (superchunks - 1).
+// Gated delta rule: superchunk length.  Chunks per superchunk m minimising, in
+// units of one chunk step of all the walks of a forward and a backward (28.6 us
+// alone on a CU at D = 128), with W = B H n workgroups for n superchunks:
+//   m f(W) + kScan (n - 1) + kLaunch
+// f: up to one workgroup per CU 1.1 + 0.45 W / CUs (the walks share the memory),
+// up to two 1.9 + W / (2 CUs), then 2.87 for every full round of two per CU and
+// the remainder like the first round.  A superchunk costs the three scans 5.6 us
+// (more once their B H D / 16 workgroups exceed half the CUs), the prep, dS prep
+// and scan launches 45 us; one superchunk needs none of them and 0.6 of the step.
+// Fitted to sweeps over 1 to 40 heads and 1088 to 65536 tokens; forward and
+// backward without the per-chunk gradients, us, chosen against the sweep's best:
+// H 40 L 65536 7121 (best), H 10 L 65536 2022 (1969), H 20 L 8192 633 (best), H 4
+// L 16384 511 (best), H 1 L 65536 882 (best).
+double gdn_step_factor(double W, double cu) {
+    auto part = [&](double w) { return w <= 0 ? 0.0 : w <= cu ? 1.1 + 0.45 * w / cu : 1.9 + w / (2 * cu); };
+    const double k = std::floor(W / (2 * cu));
+    return 2.87 * k + part(W - 2 * cu * k);
+}
 sf_status gdn_pick_ts(const Shape &r, const sf_tuning *t, int &ts) {
     if (t && t->ts != 0) {
         if (t->ts < 64 || t->ts % 64) return fail(SF_E_SHAPE, "tuning.ts must be a positive multiple of 64");
@@ -1177,15 +1190,15 @@ sf_status gdn_pick_ts(const Shape &r, const sf_tuning *t, int &ts) {
         ts = 64;
         return SF_OK;
     }
-    const double slots = device_cus(), kPrep = 1.3, kScan = 0.15;
+    const double cu = device_cus(), kLaunch = 1.6;
+    const double kScan = 0.2 * std::max(1.0, (double)bh * (r.D / 16) / (0.55 * cu));
     double best = 1e300;
     int64_t best_m = nc;
     for (int64_t m = 1; m <= nc; ++m) {
         const int64_t ns = (nc + m - 1) / m;
         if (m > 1 && (nc + m - 2) / (m - 1) == ns) continue;
-        const double walk = std::ceil((double)(bh * ns) / slots) * (double)m;
-        const double prep = ns > 1 ? kPrep * std::ceil((double)(bh * (ns - 1)) / slots) * (double)m : 0.0;
-        const double cost = walk + prep + kScan * (double)(ns - 1);
+        const double step = (double)m * gdn_step_factor((double)(bh * ns), cu);
+        const double cost = ns > 1 ? step + kScan * (double)(ns - 1) + kLaunch : 0.6 * step;
         if (cost < best - 1e-9) {
             best = cost;
             best_m = m;
@@ -1267,6 +1280,7 @@ sf::GdnArgs gdn_seg_args(const Shape &r, int64_t tok, int64_t L, int ts, const v
     a.sg_l = r.sg_l;
     a.sg_h = r.sg_h;
     a.ts = ts;
+    a.n_cu = device_cus();
     a.n_super = std::max(1, n_super_of(L, ts));
     return a;
 }
@@ -1321,10 +1335,12 @@ sf_status gdn_shape_ok(const Shape &r) {
 }
 
 // one kernel of the delta-rule pipeline; its timing kind is SF_K_GDN_PREP + phase
+// (T counts as preparation)
 sf_status gdn_launch(int phase, const sf::GdnArgs &a, int D, hipStream_t s, sf_timing *tm) {
     if (phase == sf::GDN_DCHUNK && a.L < 64) return SF_OK;  // no chunk: nothing to launch
+    if (phase == sf::GDN_TPREP && (a.L < 64 || D != 128)) return SF_OK;
     hipEvent_t e0, e1;
-    take_pair(tm, SF_K_GDN_PREP + phase, e0, e1);
+    take_pair(tm, phase == sf::GDN_TPREP ? SF_K_GDN_PREP : SF_K_GDN_PREP + phase, e0, e1);
     const hipError_t e = sf::launch_gdn_phase(phase, a, D, s, e0, e1);
     return e == hipSuccess ? SF_OK : hip_fail(e, "kernel launch");
 }
@@ -1332,6 +1348,7 @@ sf_status gdn_launch(int phase, const sf::GdnArgs &a, int D, hipStream_t s, sf_t
 
 // the phases of one delta-rule segment call, in order, on one stream
 sf_status gdn_run_fwd(const sf::GdnArgs &a, int D, hipStream_t s, sf_timing *tm) {
+    TRY(gdn_launch(sf::GDN_TPREP, a, D, s, tm));
     if (a.n_super > 1) {
         TRY(gdn_launch(sf::GDN_PREP, a, D, s, tm));
         TRY(gdn_launch(sf::GDN_SCAN, a, D, s, tm));
@@ -1339,6 +1356,7 @@ sf_status gdn_run_fwd(const sf::GdnArgs &a, int D, hipStream_t s, sf_timing *tm)
     return gdn_launch(sf::GDN_OUT, a, D, s, tm);
 }
 sf_status gdn_run_bwd(const sf::GdnArgs &a, int D, hipStream_t s, sf_timing *tm) {
+    TRY(gdn_launch(sf::GDN_TPREP, a, D, s, tm));
     if (a.n_super > 1) {
         TRY(gdn_launch(sf::GDN_PREP, a, D, s, tm));
         TRY(gdn_launch(sf::GDN_SCAN, a, D, s, tm));
@@ -1392,6 +1410,8 @@ sf_status sf_gdn_fwd(const sf_shape *shape, const void *q, const void *k, const 
     a.beta = beta;
     a.S_in = S_in;
     a.o = o;
+    a.tw = o;
+    a.n_cu = device_cus();
     a.v_new = v_new;
     a.S_out = S_out;
     a.B = r.B;
@@ -1459,6 +1479,8 @@ sf_status sf_gdn_bwd(const sf_shape *shape, const void *q, const void *k, const 
     a.dO = dO;
     a.dS_out = dS_out;
     a.dq = dq;
+    a.tw = dq;
+    a.n_cu = device_cus();
     a.dk = dk;
     a.dv = dv;
     a.dg = dg;
@@ -1544,7 +1566,7 @@ sf_status sf_gdn_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *
     for (int i = 0; i < n_seg; ++i) {
         sf::GdnArgs &a = seg[i];
         a = gdn_seg_args(r, tok, seg_len[i], p.ts[i], q, k, v, g, beta);
-        a.o = (void *)offset_x(r, o, tok);
+        a.o = a.tw = (void *)offset_x(r, o, tok);
         a.v_new = v_new ? (void *)offset_x(r, v_new, tok) : nullptr;
         a.S_in = S_bnd + i * SSB;
         a.S_out = S_bnd + (i + 1) * SSB;
@@ -1573,6 +1595,12 @@ sf_status sf_gdn_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *
     // A single-superchunk segment's walk produces its S_out on main.  Out(i-1)
     // waits on main for ST(i-1), queued before Pre(i+1) overwrites workspace set
     // (i+1) % 2 = (i-1) % 2.
+    // T of every segment's chunks first, in one launch.
+    {
+        sf::GdnArgs t = gdn_seg_args(r, 0, r.L, 64, q, k, v, g, beta);
+        t.tw = o;
+        TRY(gdn_launch(sf::GDN_TPREP, t, r.D, mn, timing_of(tuning)));
+    }
     int pending = -1;
     for (int i = 0; i < n_seg; ++i) {
         sf::GdnArgs &a = seg[i];
@@ -1644,7 +1672,7 @@ sf_status sf_gdn_chain_bwd(const sf_shape *shape, int32_t n_seg, const int64_t *
         a = gdn_seg_args(r, tok, seg_len[i], p.ts[i], q, k, v, g, beta);
         a.S_in = S_bnd + i * SSB;
         a.dO = offset_x(r, dO, tok);
-        a.dq = (void *)offset_x(r, dq, tok);
+        a.dq = a.tw = (void *)offset_x(r, dq, tok);
         a.dk = (void *)offset_x(r, dk, tok);
         a.dv = (void *)offset_x(r, dv, tok);
         a.dg = (float *)offset_g(r, dg, tok);
@@ -1684,6 +1712,11 @@ sf_status sf_gdn_chain_bwd(const sf_shape *shape, int32_t n_seg, const int64_t *
     // (overlapping the state-storing walk).  One workspace set serves every
     // segment: the next segment's prep follows this one's gradients on main,
     // and they follow both scans.
+    {  // T of every segment's chunks first, in one launch
+        sf::GdnArgs t = gdn_seg_args(r, 0, r.L, 64, q, k, v, g, beta);
+        t.tw = dq;
+        TRY(gdn_launch(sf::GDN_TPREP, t, r.D, mn, timing_of(tuning)));
+    }
     for (int i = n_seg - 1; i >= 0; --i) {
         sf::GdnArgs &a = seg[i];
         if (a.n_super > 1) {

@@ -112,7 +112,7 @@ __device__ __forceinline__ frag_t<T> ldfragT(const T *base, int ldt, int row0, i
 // X[m0+16..m0+31][n] (a1): as an A operand it is X^T rows n, contraction over m.
 template <typename T>
 __device__ __forceinline__ frag_t<T> frag_from_acc(const f32x4 &a0, const f32x4 &a1) {
-    frag_t<T> f;
+    frag_t<T> f = {};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         f[j] = cvt<T>(a0[j]);

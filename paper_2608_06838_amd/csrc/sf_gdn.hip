@@ -16,23 +16,21 @@
 // S_t = a_t S_{t-1} + k_t u_t^T is a plain gated linear recurrence in u, and
 // solving the within-chunk dependence of u on the earlier u's.
 //
-// One workgroup walks the chunks of one (batch, head) superchunk with the state
-// in registers: wave w owns the 16 state columns [16w, 16w+16) (D/16 waves).
-// Per chunk: the q, k, v tiles are staged in LDS; the KK^T and QK^T scores run
-// on MFMA (10 causal 16x16 tiles each); T = (I + A)^{-1} is formed in fp32 by
-// 16 x 16 blocks (gdn_tinv) and [W | Ubar] = T R on MFMA (gdn_wu); U, the
-// output and the state update are MFMA products whose computed operands
-// (S, W, U) go in as bf16 hi/lo pairs, U straight from its accumulators (rows t,
-// columns v), which two lane-row swaps make into operand fragments with the
-// tokens as contraction.
+// T = (I + A)^{-1} needs k, g and beta alone: k_gdn_tprep forms it for every
+// chunk in parallel and the walks read it (D = 64 walks form it themselves).  One
+// workgroup walks the chunks of one (batch, head) superchunk with the state in
+// registers, each wave on its own state columns; with T given, U = T diag(beta)
+// (V - diag(gamma) K S) needs no product shared between waves.  U, the output and
+// the state update are MFMA products whose computed operands (S, T, P, U) go in
+// as bf16 hi/lo pairs, straight from their accumulators where they are a wave's
+// own.
 //
 // Superchunk parallelism (the Pre / ST / Out split of Sec. 2.2 with the delta
 // rule's matrix-valued transition): the chunk map S -> gamma_C S + K~^T (Ubar - W S)
 // is affine in S, so a superchunk of chunks maps S_J to S_{J+1} = M_J S_J + N_J
 // with dense M_J, N_J in R^{Dk x Dk}, R^{Dk x Dv}.
-//   k_gdn_walk<W_PREP>: walks the superchunk's chunks with the state [M | N]
-//     (wave w owns columns [16w, 16w+16) of both; M from the identity with
-//     Ubar = 0, N from zero) and writes M_J, N_J.  No outputs.
+//   k_gdn_walk<W_PREP>: walks the superchunk's chunks with the state M (from the
+//     identity, V = 0) or N (from zero), one workgroup each.  No outputs.
 //   k_gdn_scan: S_{J+1} = M_J S_J + N_J in fp32, sequential over J, 16 state
 //     columns per workgroup; writes every S_J and S_out.
 //   k_gdn_walk<W_OUT>: the output walk above from S_J over superchunk J;
@@ -48,6 +46,7 @@ namespace {
 // holds k = 4q .. 4q+3 of column n; the accumulator holds rows 4q .. 4q+3 of
 // column n, the same slots as a B operand.
 typedef short s4v __attribute__((ext_vector_type(4)));
+typedef int s4v2 __attribute__((ext_vector_type(4)));  // a 16-byte block
 __device__ __forceinline__ void mma16(f32x4 &c, s4v a, s4v b) {
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
@@ -163,31 +162,34 @@ __device__ __forceinline__ void gdn_tinv(int tid, const float *sA, float *sT, co
     }
 }
 
-// The walks' T = (I + A)^{-1} (A = M in sA, pitch C + 4), stored as the bf16
-// hi/lo pair that every consumer splits it into (sTh, sTl: raw 16-bit
-// patterns, pitch C + 16, zero above the diagonal): the four diagonal blocks
-// by forward substitution in fp32 (64 threads, one column each), the
+// The triangular 64 x 64 pair tiles of the walks (T, P, P^T as bf16 hi/lo) hold
+// the three 32 x 32 quadrants that are not all zero, each 64-byte rows with
+// their four 16-byte blocks XOR-swizzled by the row, hi then lo: 12 KB instead of
+// the 20 of two padded square tiles, which is what lets two walk workgroups share
+// a CU.  Quadrants (0,0), off-diagonal, (1,1) in that order, for a lower (r >= c)
+// and an upper triangle alike; the all-zero 16 x 16 blocks inside the diagonal
+// quadrants are stored.  SW: the swizzle for the way the rows are read, 0 for
+// fragment rows arow(tt, n) (8 apart in fours), 1 for 16 consecutive rows.
+constexpr int TRI = 3 * 32 * 32;  // elements of one half (hi or lo)
+template <int SW>
+__device__ __forceinline__ int tri_pos(int r, int c) {
+    const int sw = SW ? (r >> 1) & 3 : ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
+    return ((r >> 5) + (c >> 5)) * 1024 + (r & 31) * 32 + ((((c & 31) >> 3) ^ sw) << 3) + (c & 7);
+}
+
+// T = (I + A)^{-1} (A in sA, pitch C + 4) as the bf16 hi/lo pair that every
+// consumer splits it into (tri_pos<0>, raw 16-bit patterns): the four diagonal
+// blocks by forward substitution in fp32 (64 threads, one column each), the
 // off-diagonal blocks level by level as in gdn_tinv, reading the stored pairs.
 // (A diagonal block N is nilpotent, and (I + N)^{-1} = (I + N^8)(I + N^4)
-// (I + N^2)(I - N) on MFMA ran the walks 4% faster; but the series' partial
-// sums grow like binomial coefficients when neighbouring keys are nearly
-// parallel with little decay, and the outputs then lost up to 1e-1 (bf16
-// hi/lo operands) or 1e-3 (fp32 MFMA) against the oracle, where substitution
-// keeps them at output rounding.)  NT >= 256 threads; ends with a barrier.
-template <int NT>
+// (I + N^2)(I - N) on MFMA is faster; but the series' partial sums grow like
+// binomial coefficients when neighbouring keys are nearly parallel with little
+// decay, and the outputs then lost up to 1e-1 (bf16 hi/lo operands) or 1e-3
+// (fp32 MFMA) against the oracle, where substitution keeps them at output
+// rounding.)  Four waves; ends with a barrier.
 __device__ __forceinline__ void gdn_tinv_hl(int tid, const float *sA, short *sTh, short *sTl) {
-    constexpr int LA = C + 4, LTB = C + 16;
+    constexpr int LA = C + 4;
     const int w = tid >> 6, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
-    // rows row0 .. row0+3 of column col (the B layout), as hi/lo
-    auto put = [&](int row0, int col, const f32x4 &x) {
-        s4v h, l;
-        split4(x, h, l);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            sTh[(row0 + r) * LTB + col] = h[r];
-            sTl[(row0 + r) * LTB + col] = l[r];
-        }
-    };
     if (tid < 64) {  // one column of a diagonal block per thread
         const int o = 16 * (tid >> 4), c = tid & 15;
         float x[16];
@@ -195,15 +197,14 @@ __device__ __forceinline__ void gdn_tinv_hl(int tid, const float *sA, short *sTh
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const __bf16 h = (__bf16)x[r];
-            sTh[(o + r) * LTB + o + c] = __builtin_bit_cast(short, h);
-            sTl[(o + r) * LTB + o + c] = __builtin_bit_cast(short, (__bf16)(x[r] - (float)h));
+            const int p = tri_pos<0>(o + r, o + c);
+            sTh[p] = __builtin_bit_cast(short, h);
+            sTl[p] = __builtin_bit_cast(short, (__bf16)(x[r] - (float)h));
         }
-    }
-    for (int e = tid; e < 6 * 256; e += NT) {  // blocks (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-        const int b = e >> 8, rr = (e >> 4) & 15, cc = e & 15;
-        const int bi = b < 3 ? 0 : (b < 5 ? 1 : 2), bj = b < 3 ? b + 1 : (b < 5 ? b - 1 : 3);
-        sTh[(16 * bi + rr) * LTB + 16 * bj + cc] = 0;
-        sTl[(16 * bi + rr) * LTB + 16 * bj + cc] = 0;
+    } else if (tid < 192) {  // the zero blocks (0,1) and (2,3) of the diagonal quadrants
+        const int e = tid - 64, b = e >> 6, r = 32 * b + ((e >> 2) & 15), c = 32 * b + 16 + 4 * (e & 3);
+        *reinterpret_cast<s4v *>(&sTh[tri_pos<0>(r, c)]) = s4v{0, 0, 0, 0};
+        *reinterpret_cast<s4v *>(&sTl[tri_pos<0>(r, c)]) = s4v{0, 0, 0, 0};
     }
     __syncthreads();
 #pragma unroll
@@ -217,451 +218,636 @@ __device__ __forceinline__ void gdn_tinv_hl(int tid, const float *sA, short *sTh
                 split4(av, ah, al);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    bh[u] = sTh[(16 * k + 4 * q4 + u) * LTB + 16 * j + n16];
-                    bl[u] = sTl[(16 * k + 4 * q4 + u) * LTB + 16 * j + n16];
+                    const int p = tri_pos<0>(16 * k + 4 * q4 + u, 16 * j + n16);
+                    bh[u] = sTh[p];
+                    bl[u] = sTl[p];
                 }
                 mma16(y, ah, bh);
                 mma16(y, ah, bl);
                 mma16(y, al, bh);
             }
-            const s4v th = *reinterpret_cast<const s4v *>(&sTh[(16 * i + n16) * LTB + 16 * i + 4 * q4]);
-            const s4v tl = *reinterpret_cast<const s4v *>(&sTl[(16 * i + n16) * LTB + 16 * i + 4 * q4]);
-            s4v yh, yl;
+            const int p = tri_pos<0>(16 * i + n16, 16 * i + 4 * q4);
+            const s4v th = *reinterpret_cast<const s4v *>(&sTh[p]);
+            const s4v tl = *reinterpret_cast<const s4v *>(&sTl[p]);
+            s4v yh, yl, h, l;
             split4(y, yh, yl);
             f32x4 t = {0.f, 0.f, 0.f, 0.f};
             mma16(t, th, yh);
             mma16(t, th, yl);
             mma16(t, tl, yh);
-            put(16 * i + 4 * q4, 16 * j + n16, -t);
+            split4(-t, h, l);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {  // rows 16i + 4 q4 + r of column 16j + n16
+                const int p2 = tri_pos<0>(16 * i + 4 * q4 + r, 16 * j + n16);
+                sTh[p2] = h[r];
+                sTl[p2] = l[r];
+            }
         }
         __syncthreads();
     }
 }
 
-// [W | Ubar] = T [diag(beta gamma) K | diag(beta) V] on MFMA: wave w forms
-// columns [16w, 16w+16) of W (and of Ubar when sU is given); T enters as its
-// stored hi/lo pair (gdn_tinv_hl), the scaled K and V columns as hi/lo pairs too (K, V exact in bf16 times an fp32
-// factor).  Results: -W as a bf16 hi/lo pair (sWh, sWl: natural [t][k] tiles,
-// pitch LDN, channel blocks of rows with bit 3 set XOR-swizzled by SWX, the
-// layout of the staged q/k tiles), split once here for every wave that reads
-// it; Ubar to sU (fp32, pitch LDU).
-template <typename T, int D, int LDN, int LDU, int SWX>
-__device__ __forceinline__ void gdn_wu(int w, int lane, const LaneOff &tro, const short *sTh, const short *sTl,
-                                       const T *sK, const T *sV,
-                                       const float *sbeta, const float *sq, T *sWh, T *sWl, float *sU) {
-    constexpr int LTB = C + 16;
-    const int q4 = lane >> 4, n16 = lane & 15, c0 = 16 * w;
-    f32x4 cw[4], cu[4];
+// A[t][s] = beta_t e^{b_t - b_s} k_t.k_s (s < t) of a staged chunk on the causal
+// tiles, 10 over the four waves, into sA (fp32, pitch C + 4)
+template <typename T, int D, int LDN, int SWX>
+__device__ __forceinline__ void gdn_a_scores(int w, int lane, const T *sK, const float *sb, const float *sbeta, float *sA) {
+    constexpr int LDA = C + 4;
+    const int q4 = lane >> 4, n16 = lane & 15;
+    const LaneOff swo = swz_off<T, LDN, SWX>(lane);
+    for (int i = w; i < 10; i += 4) {
+        int tt, st;
+        tri_tile(i, tt, st);
+        f32x4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) cw[tt] = cu[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < D / 32; ++ks)
+            mma(p, ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * st, 32 * ks), ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * tt, 32 * ks));
+        const int t = 16 * tt + n16;
+        const float bt = sb[t], be = sbeta[t];
+        const f32x4 bs = *reinterpret_cast<const f32x4 *>(&sb[16 * st + 4 * q4]);
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < C / 32; ++ks) {
-        float fw[8], fu[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int s2 = 32 * ks + 8 * q4 + j;
-            fu[j] = sbeta[s2];
-            fw[j] = sbeta[s2] * sq[s2];
-        }
-        frag_t<T> kh, kl, vh, vl;
-        split_scaled<T, true>(ldfragTR<T, LDN, SWX>(sK, tro, 32 * ks, c0), fw, kh, kl);
-        if (sU) split_scaled<T, true>(ldfragTR<T, LDN, SWX>(sV, tro, 32 * ks, c0), fu, vh, vl);
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
-            if (32 * ks > 16 * tt + 15) continue;  // T is lower triangular
-            const int pt = (16 * tt + n16) * LTB + 32 * ks + 8 * q4;
-            const frag_t<T> th = *reinterpret_cast<const frag_t<T> *>(sTh + pt);
-            const frag_t<T> tl = *reinterpret_cast<const frag_t<T> *>(sTl + pt);
-            mma(cw[tt], th, kh);
-            mma(cw[tt], th, kl);
-            mma(cw[tt], tl, kh);
-            if (sU) {
-                mma(cu[tt], th, vh);
-                mma(cu[tt], th, vl);
-                mma(cu[tt], tl, vh);
-            }
-        }
+        for (int r = 0; r < 4; ++r) v[r] = 16 * st + 4 * q4 + r < t ? be * p[r] * fexp2(bt - bs[r]) : 0.f;
+        *reinterpret_cast<f32x4 *>(&sA[t * LDA + 16 * st + 4 * q4]) = v;
     }
+}
+
+// T of every chunk, all chunks in parallel, into the rows of an output tensor
+// that a later kernel overwrites (o forward, dq backward): token row t of the
+// chunk holds T[t][0..63] hi, then lo, 256 bytes (so D = 128 only; the walks of
+// D = 64 form T themselves).  T depends on k, g and beta alone, and its
+// substitution is a serial chain: inside the walks it was half of every chunk's
+// latency, and each pass of the backward formed it again.  Here four workgroups
+// per CU (36 KB of LDS) hide the chain of one behind the others'.
+template <typename T, int D>
+__global__ void __launch_bounds__(256) k_gdn_tprep(GdnArgs a) {
+    static_assert(D == 128 && sizeof(T) == 2, "T's pair fills a row of 128 bf16");
+    constexpr int LDN = D + pad<T>(), SWX = swx<T, D>();
+    __shared__ __attribute__((aligned(16))) T sK[C * LDN];  // then T's pair
+    __shared__ __attribute__((aligned(16))) float sA[C * (C + 4)];
+    __shared__ __attribute__((aligned(16))) float sb[C], sbeta[C];
+    static_assert(2 * TRI <= C * LDN, "T's pair fits the key tile");
+    short *const sTh = reinterpret_cast<short *>(sK), *const sTl = sTh + TRI;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nc = (int)(a.L / C), bh = blockIdx.x / nc, c = blockIdx.x % nc, bb = bh / a.H, hh = bh % a.H;
+    const int64_t xo = bb * a.sx_b + hh * a.sx_h + (int64_t)c * C * a.sx_l;
+    const int64_t go = bb * a.sg_b + hh * a.sg_h + (int64_t)c * C * a.sg_l;
+    Tile<T, D, 256> t;
+    t.load((const T *)a.k + xo, a.sx_l, tid);
+    if (w == 0) {
+        sb[lane] = wave_scan_dpp(a.g[go + lane * a.sg_l] * LOG2E);
+        sbeta[lane] = a.beta[go + lane * a.sg_l];
+    }
+    t.store_swz(sK, LDN, tid, SWX);
+    __syncthreads();
+    gdn_a_scores<T, D, LDN, SWX>(w, lane, sK, sb, sbeta, sA);
+    __syncthreads();
+    gdn_tinv_hl(tid, sA, sTh, sTl);
+    T *out = (T *)a.tw + xo;
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int t = 16 * tt + 4 * q4 + r, pw = t * LDN + swz_col(t, c0 + n16, SWX);
-            const float x = -cw[tt][r];
-            const T h = cvt<T>(x);
-            sWh[pw] = h;
-            sWl[pw] = cvt<T>(x - tof<T>(h));
-            if (sU) sU[t * LDU + c0 + n16] = cu[tt][r];
-        }
+    for (int i = 0; i < 4; ++i) {  // 16-byte blocks: row u / 16, then hi 0-7, lo 0-7
+        const int u = 256 * i + tid, r = u >> 4, j = u & 15, cc = 8 * (j & 7);
+        if (r < 32 && cc >= 32) continue;  // the zero quadrant, never read
+        *reinterpret_cast<s4v2 *>(out + r * a.sx_l + 8 * j) =
+            *reinterpret_cast<const s4v2 *>((j < 8 ? sTh : sTl) + tri_pos<0>(r, cc));
+    }
 }
 
 enum { W_OUT = 0, W_PREP = 1, W_STORE = 2 };
 
+// Registers and LDS of the walks.  D = 128: four waves of two 16-column tiles
+// each, so every shared operand fragment read from LDS feeds both, and two
+// workgroups per CU (<= 256 registers, <= 80 KB of LDS) cover each other's
+// barriers.  D = 64: four waves of one tile.  Column n of tile m is channel
+// 32w + 8 (n / 4) + 4m + n % 4 (two tiles), so that a lane's output rows of the
+// two tiles are 8 consecutive channels, one 16-byte store.
+template <int D>
+struct GdnCols {
+    static constexpr int NCT = D / 64;
+    int c0, n16;
+    __device__ __forceinline__ int col(int m) const { return NCT == 2 ? c0 + 8 * (n16 >> 2) + 4 * m + (n16 & 3) : c0 + n16; }
+    __device__ __forceinline__ int base(int m) const { return c0 + 4 * m; }  // ldfragTR column of tile m
+};
+
+// A D x D fp32 state in the walks' register layout (slot [m][i][r] = row
+// prow(i, r), column col(m)) through a buffer resource: one lane offset, the rest
+// of the address uniform (64 flat addresses would spill).
+template <int D>
+struct StateIO {
+    static constexpr int NCT = GdnCols<D>::NCT, NK = D / 16;
+    uint32_t off;
+    __device__ __forceinline__ StateIO(const GdnCols<D> &cl, int q4) : off((uint32_t)(8 * q4 * D + cl.col(0)) * 4) {}
+    __device__ __forceinline__ static uint32_t at(int m, int i, int r) {
+        return (uint32_t)((32 * (i >> 1) + 4 * (i & 1) + r) * D + 4 * m) * 4;
+    }
+    __device__ __forceinline__ void load(f32x4 (&S)[NCT][NK], const float *src) const {
+        const rsrc_t rs = buf_rsrc(src, D * D * 4);
+#pragma unroll
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int i = 0; i < NK; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S[m][i][r] = buf_ld<float>(rs, off, at(m, i, r));
+    }
+    __device__ __forceinline__ void store(const f32x4 (&S)[NCT][NK], float *dst) const {
+        const rsrc_t rs = buf_rsrc(dst, D * D * 4);
+#pragma unroll
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int i = 0; i < NK; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) buf_st(rs, off, at(m, i, r), S[m][i][r]);
+    }
+};
+
+// The fragment reads' positions in a triangular tile are one lane offset plus a
+// constant (the swizzle does not see the tile index); spelled out, since the
+// compiler would keep every position in a register of its own.
+//   rows ar + roff(tt), columns 32 ks + 8 q4 ..   (tri_pos<0>, base ar, 8 q4)
+__device__ __forceinline__ constexpr int tri_a(int tt, int ks) { return ((tt >> 1) + ks) * 1024 + 4 * (tt & 1) * 32; }
+//   rows 16 tt + n16, columns 32 ks + 8 q4 ..     (tri_pos<1>, base n16, 8 q4)
+__device__ __forceinline__ constexpr int tri_b(int tt, int ks) { return ((tt >> 1) + ks) * 1024 + 16 * (tt & 1) * 32; }
+
+// the 16-byte blocks of T's pair that this thread moves between the rows of the
+// tensor that holds it and LDS (see k_gdn_tprep): row 16 i + tid / 16, block tid % 16
+template <typename T>
+struct TriTile {
+    s4v2 r[4];
+    __device__ __forceinline__ void load(rsrc_t rs, uint32_t off, uint32_t step, int tid) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i >= 2 || (tid & 7) < 4) r[i] = buf_ld<s4v2>(rs, off, i * step);
+    }
+    __device__ __forceinline__ static int base(int tid) { return ((tid & 8) ? TRI : 0) + tri_pos<0>(tid >> 4, 8 * (tid & 7)); }
+    __device__ __forceinline__ void store(short *t, int base, int tid) const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i >= 2 || (tid & 7) < 4) *reinterpret_cast<s4v2 *>(t + base + (i >> 1) * 1024 + (i & 1) * 512) = r[i];
+    }
+};
+
+// A chunk tile copied from memory straight into LDS, 1 KB per wave and
+// instruction (lane l's 16 bytes to base + 16 l), without passing registers: rows
+// of D bf16 unpadded, the 16-byte blocks of row r XOR-swizzled by f(r) = (r % 8) ^
+// 4 (r / 8 % 2) through the source addresses, so that fragment reads over 16 rows
+// (and the transposing ones over rows 8 apart) touch every bank once.
+template <typename T, int D>
+struct DmaTile {
+    static constexpr int BPR = D / 8, RPI = 64 / BPR, NI = C / RPI / 4;  // blocks per row, rows per instruction
+    uint32_t v0, v1;  // source offsets; v1 for the instructions whose rows flip f's bit 2
+    __device__ __forceinline__ DmaTile(int lane, int64_t ld) {
+        const int r = lane / BPR, b = (lane % BPR) ^ r;  // r < RPI <= 8: f(r) = r
+        v0 = (uint32_t)((r * ld + 8 * b) * (int64_t)sizeof(T));
+        v1 = (uint32_t)((r * ld + 8 * (b ^ 4)) * (int64_t)sizeof(T));
+    }
+    __device__ __forceinline__ void issue(rsrc_t rs, T *lds, int w, uint32_t row_bytes) const {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int k = NI * w + i;
+            const bool flip = D == 128 ? (i ^ (i >> 1)) & 1 : i & 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + 512 * k), 16,
+                                                     flip ? v1 : v0, (int)(RPI * k * row_bytes), 0, 0);
+        }
+    }
+    // fragment rows 16 tt + n16, columns 32 ks + 8 q4: base[ks & 1] + row0 D + 64 (ks >> 1)
+    __device__ __forceinline__ static void row_base(int lane, int (&o)[2]) {
+        const int q = lane >> 4, n = lane & 15, f = (n & 7) ^ (((n >> 3) & 1) << 2);
+        o[0] = n * D + 8 * (q ^ f);
+        o[1] = n * D + 8 * (q ^ 4 ^ f);
+    }
+};
+// T's packed pair the same way (tri_pos<0>): 12 instructions, three per wave
+struct DmaTri {
+    uint32_t v;
+    __device__ __forceinline__ DmaTri(int lane, int64_t ld) {
+        const int r = lane >> 2, sw = ((r >> 1) & 1) | (((r >> 3) & 1) << 1);
+        v = (uint32_t)(r * ld * 2 + 16 * ((lane & 3) ^ sw));
+    }
+    __device__ __forceinline__ void issue(rsrc_t rs, short *lds, int w, uint32_t row_bytes) const {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int k = 3 * w + i, h = k / 6, qd = (k % 6) >> 1, rows = 16 * (k & 1) + (qd > 0 ? 32 : 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + 512 * k), 16, v,
+                                                     (int)(rows * row_bytes) + h * 128 + (qd == 2 ? 64 : 0), 0, 0);
+        }
+    }
+};
+
+// The forward walks.  Per chunk, each wave on its own state columns:
+//   X = V - gamma o (K S),   U = T (beta o X),   O = gamma o (Q S) + P U,
+//   S = gamma_C S + K^T (e^{b_C - b} o U)
+// (U = Ubar - W S with the products regrouped: K enters exactly, S and X as hi/lo
+// pairs, and neither W nor Ubar is formed).  V joins X's accumulators through an
+// MFMA with the identity, which is exact and needs no 2-byte LDS reads.  Nothing
+// but P and the staged tiles is shared between waves, so a chunk has two barriers
+// (three with P).
 template <typename T, int D, int MODE>
-__global__ void __launch_bounds__(64 * D / 16) k_gdn_walk(GdnArgs a) {
+__global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     constexpr bool PREP = MODE == W_PREP, OUTP = MODE == W_OUT;  // STORE: states only
-    constexpr int NW = D / 16, NT = 64 * NW, NK = D / 16, NS = PREP ? 2 : 1;
-    constexpr int LDN = D + pad<T>(), LDT = C + pad<T>(), SWX = swx<T, D>();
-    constexpr int LDA = C + 4, LDU = D + 4;  // 16-byte-odd pitches: conflict-free row-varying reads
-    __shared__ __attribute__((aligned(16))) T sQ[OUTP ? C * LDN : 8];    // plain
-    __shared__ __attribute__((aligned(16))) T sK[C * LDN];               // plain, swizzled
-    __shared__ __attribute__((aligned(16))) T sV[C * LDN];               // plain
-    // (Q K^T o Gamma)[t][s] hi, then lo; T = (I + A)^{-1} lives here before the P tiles
-    __shared__ __attribute__((aligned(16))) T sPP[OUTP ? 2 * C * LDT : 8];
-    __shared__ __attribute__((aligned(16))) T sTx[OUTP ? 8 : 2 * C * LDT];
-    static_assert(LDT == C + 16, "T's hi/lo pair has the P tiles' pitch");
-    T *sP = sPP, *sPl = sPP + (OUTP ? C * LDT : 0);
-    short *const sTh = reinterpret_cast<short *>(OUTP ? sPP : sTx), *const sTl = sTh + C * LDT;
-    // A = beta_t e^{b_t-b_s} k_t.k_s (s < t, fp32) until the inverse is formed; then -W
-    // as a hi/lo pair of bf16 tiles in the same bytes
-    constexpr int AWB = C * LDA * 4 > 2 * C * LDN * (int)sizeof(T) ? C * LDA * 4 : 2 * C * LDN * (int)sizeof(T);
-    __shared__ __attribute__((aligned(16))) char sAW[AWB];
-    float *const sA = reinterpret_cast<float *>(sAW);
-    T *const sWh = reinterpret_cast<T *>(sAW), *const sWl = sWh + C * LDN;
-    __shared__ __attribute__((aligned(16))) float sU[C * LDU];    // Ubar [t][v], fp32
+    constexpr bool TPRE = D == 128;                              // T comes from k_gdn_tprep
+    constexpr int NT = 256, NK = D / 16, NCT = GdnCols<D>::NCT;
+    constexpr int LDN = D + pad<T>(), SWX = swx<T, D>(), LDA = C + 4;
+    __shared__ __attribute__((aligned(16))) T sQ[OUTP ? C * D : 8];    // DmaTile
+    __shared__ __attribute__((aligned(16))) T sK[C * LDN];             // swizzled
+    __shared__ __attribute__((aligned(16))) T sV[C * LDN];             // swizzled
+    __shared__ __attribute__((aligned(16))) short sT[2 * TRI];         // T, hi then lo
+    __shared__ __attribute__((aligned(16))) T sP[OUTP ? 2 * TRI : 8];  // P[t][s] = e^{b_t-b_s} q_t.k_s, hi then lo
+    __shared__ __attribute__((aligned(16))) float sA[TPRE ? 4 : C * LDA];
     __shared__ __attribute__((aligned(16))) float sb[C], sq[C], se[C], sbeta[C];
 
     const int tid = threadIdx.x, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c0 = 16 * w;
-    // items: (b, h, J) with J < n_super (walk) or J < n_super - 1 (prep)
+    const GdnCols<D> cl{16 * NCT * w, n16};
+    // items: (b, h, J) with J < n_super (walk) or J < n_prep (prep).  The prep's M
+    // (role 0) and N (role 1) are walks of their own, 8 apart in dispatch order (one XCD).
     const int nJ = PREP ? a.n_prep : a.n_super;
-    const int item = blockIdx.x, bh = item / nJ, J = item % nJ;
+    int item = blockIdx.x, role = 1;
+    if constexpr (PREP) {
+        role = (item >> 3) & 1;
+        item = (item >> 4) * 8 + (item & 7);
+        if (item >= a.B * a.H * nJ) return;
+    }
+    const int bh = item / nJ, J = item % nJ;
     const int bb = bh / a.H, hh = bh % a.H;
     const int64_t tok0 = (int64_t)J * a.ts;
     const int64_t xo = bb * a.sx_b + hh * a.sx_h + tok0 * a.sx_l;
     const T *Q = (const T *)a.q + xo;
     const T *K = (const T *)a.k + xo;
     const T *V = (const T *)a.v + xo;
+    const T *TW = TPRE ? (const T *)a.tw + xo : nullptr;
     T *Y = (T *)a.o + xo;
-    T *VN = a.v_new ? (T *)a.v_new + xo : nullptr;
+    T *VN = OUTP && a.v_new ? (T *)a.v_new + xo : nullptr;
     const int64_t go = bb * a.sg_b + hh * a.sg_h + tok0 * a.sg_l;
     const float *gp = a.g + go;
     const float *bp = a.beta + go;
     const int64_t SS = (int64_t)D * D;
     const int nch = (int)((a.L - tok0 < a.ts ? a.L - tok0 : a.ts) / C);
-    const LaneOff tro = tr_off<T, LDN, SWX>(lane), swo = swz_off<T, LDN, SWX>(lane);
-    const LaneOff tro8 = tr_off8<T, LDN, SWX>(lane);
-    auto asw = [](int row) { return sizeof(T) == 2 ? 8 * ((row >> 2) & 1) : 0; };
-    // Accumulator pairs (2m, 2m+1) of the state (rows: key channels) and of U
+    const LaneOff swo = swz_off<T, LDN, SWX>(lane), tro8 = tr_off8<T, LDN, SWX>(lane);
+    const LaneOff tro = NCT == 2 ? tro8 : tr_off<T, LDN, SWX>(lane);  // this wave's own columns
+    // Accumulator pairs (2m, 2m+1) of the state (rows: key channels) and of X, U
     // (rows: tokens) hold, in lane row q4, indices 32m + 8 q4 .. +7 (slot r of
     // tile i: prow(i, r)), so each pair splits into an operand fragment in plain
     // order with no lane swaps.  The products that build them read their A rows
-    // in that order: fragment row n of tile i is prow(i, n / 4, n % 4).
+    // in that order: fragment row n of tile i is arow(i, n).
     auto prow = [&](int i, int r) { return 32 * (i >> 1) + 8 * q4 + 4 * (i & 1) + r; };
-    auto arow = [](int i, int n) { return 32 * (i >> 1) + 8 * (n >> 2) + 4 * (i & 1) + (n & 3); };
-    auto roff = [](int i) { return 32 * (i >> 1) + 4 * (i & 1); };  // ldfragTR column for tro8
+    const int ar = 8 * (n16 >> 2) + (n16 & 3);                      // arow(i, n16) = ar + roff(i)
+    auto roff = [](int i) { return 32 * (i >> 1) + 4 * (i & 1); };  // (also ldfragTR's column for tro8)
+    const LaneOff ko = {ar * LDN + 8 * q4 + ((n16 >> 2) & 1) * SWX, ar * LDN + 8 * q4 - ((n16 >> 2) & 1) * SWX};
+    const int ta = tri_pos<0>(ar, 8 * q4), pb = tri_pos<1>(n16, 8 * q4);
+    // identity fragments: row arow(tt, n16) of tile tt against its own 32 tokens
+    frag_t<T> eye[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) eye[h][j] = (T)(q4 == (n16 >> 2) && j == 4 * h + (n16 & 3) ? 1.f : 0.f);
 
-    // S[m][prow(i, r)][c0 + n16]: the walk's state starts from S_J (S_in for
-    // one superchunk); the prep's M (m = 0) from I and its N (m = 1) from 0
+    // S[m][i][r] = S[prow(i, r)][col(m)]: the walk's state starts from S_J (S_in for
+    // one superchunk); the prep's M from I and its N from 0
     const float *src = a.n_super == 1 ? a.S_in + (a.S_in ? bh * SS : 0) : a.wsS + (int64_t)item * SS;
-    f32x4 S[NS][NK];
+    const StateIO<D> sio(cl, q4);
+    f32x4 S[NCT][NK];
 #pragma unroll
-    for (int i = 0; i < NK; ++i)
+    for (int m = 0; m < NCT; ++m)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = prow(i, r);
-            if constexpr (PREP) {
-                S[0][i][r] = row == c0 + n16 ? 1.f : 0.f;
-                S[1][i][r] = 0.f;
-            } else {
-                S[0][i][r] = (a.n_super > 1 || a.S_in) ? src[(int64_t)row * D + c0 + n16] : 0.f;
-            }
-        }
+        for (int i = 0; i < NK; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[m][i][r] = PREP && role == 0 && prow(i, r) == cl.col(m) ? 1.f : 0.f;
+    if (!PREP && (a.n_super > 1 || a.S_in)) sio.load(S, src);
 
     using TT = Tile<T, D, NT>;
-    TT t1, t2, t3;
+    TT t2, t3;
+    const DmaTile<T, D> dq(lane, a.sx_l);
+    const DmaTri dt(lane, a.sx_l);
+    const uint32_t rowb = (uint32_t)(a.sx_l * (int64_t)sizeof(T));
+    int qb[2];
+    DmaTile<T, D>::row_base(lane, qb);
+    TriTile<T> t4;
     float gl, bl;
     const int64_t cstep = (int64_t)C * a.sx_l;
     const uint32_t cspan = chunk_span<T, D>(a.sx_l), gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4);
     uint32_t toff[TT::RPT];
     TT::offsets(toff, a.sx_l, tid);
     const uint32_t goff = (uint32_t)(lane * a.sg_l * 4);
-    const uint32_t voff = (uint32_t)((n16 * a.sx_l + c0 + 4 * q4) * (int64_t)sizeof(T));
     const uint32_t tstep = (uint32_t)(16 * a.sx_l * (int64_t)sizeof(T));
+    const int t4base = TriTile<T>::base(tid);
+    const uint32_t t4off = (uint32_t)(((tid >> 4) * a.sx_l + 8 * (tid & 15)) * (int64_t)sizeof(T));
+    const uint32_t voff = (uint32_t)((n16 * a.sx_l + cl.c0 + 4 * NCT * q4) * (int64_t)sizeof(T));
     auto issue = [&](int c) {
         const int64_t nx = c * cstep;
-        if constexpr (OUTP) t1.load_buf(buf_rsrc(Q + nx, cspan), toff, 0);
         t2.load_buf(buf_rsrc(K + nx, cspan), toff, 0);
-        t3.load_buf(buf_rsrc(V + nx, cspan), toff, 0);
+        if constexpr (TPRE && !OUTP) t4.load(buf_rsrc(TW + nx, cspan), t4off, tstep, tid);
         gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
         bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        if (!PREP || role) t3.load_buf(buf_rsrc(V + nx, cspan), toff, 0);
+        if constexpr (OUTP) dq.issue(buf_rsrc(Q + nx, cspan), sQ, w, rowb);
+        if constexpr (OUTP && TPRE) dt.issue(buf_rsrc(TW + nx, cspan), sT, w, rowb);
     };
     if (nch > 0) issue(0);
 
+    const unsigned par = pair_parity(a.n_cu);
     for (int c = 0; c < nch; ++c) {
-        if constexpr (MODE == W_STORE) {
-            float *dst = a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS;
-#pragma unroll
-            for (int i = 0; i < NK; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[(int64_t)prow(i, r) * D + c0 + n16] = S[0][i][r];
-        }
+        pair_turn(par);
+        if constexpr (MODE == W_STORE) sio.store(S, a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS);
         const float b2 = wave_scan_dpp(gl * LOG2E);
         const float b63 = lane_value(b2, 63);
         const float betal = bl;
+        if constexpr (OUTP) vm_wait_all();  // this wave's part of Q and T is in LDS
         __syncthreads();  // the previous chunk is done with every LDS tile
-        if constexpr (OUTP) t1.store_swz(sQ, LDN, tid, 0);
         t2.store_swz(sK, LDN, tid, SWX);
-        t3.store_swz(sV, LDN, tid, SWX);
-        if (w == 0) {
+        if (!PREP || role) t3.store_swz(sV, LDN, tid, SWX);
+        if constexpr (TPRE && !OUTP) t4.store(sT, t4base, tid);
+        if (w == 3) {
             sb[lane] = b2;
             sq[lane] = fexp2(b2);
             se[lane] = fexp2(b63 - b2);
             sbeta[lane] = betal;
         }
         __syncthreads();
-        if (c + 1 < nch) issue(c + 1);
 
-        // scores on the causal tiles: k_s . k_t (A) first; k_s . q_t (P) after the
-        // solve, whose T occupies the P tiles' LDS
-        auto scores = [&](int i0) {
-            for (int i = i0 + w; i < i0 + 10; i += NW) {
-                const bool kk = i >= 10;
+        if constexpr (OUTP) {  // P on the causal tiles
+            for (int i = w; i < 10; i += 4) {
                 int tt, st;
-                tri_tile(kk ? i - 10 : i, tt, st);
+                tri_tile(i, tt, st);
                 f32x4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int ks = 0; ks < D / 32; ++ks) {
-                    const frag_t<T> kf = ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * st, 32 * ks);
-                    const frag_t<T> xf = kk ? ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * tt, 32 * ks)
-                                            : ldfrag(sQ, LDN, 16 * tt, 32 * ks, lane);
-                    mma(p, kf, xf);
-                }
+                for (int ks = 0; ks < D / 32; ++ks)
+                    mma(p, ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * st, 32 * ks), *reinterpret_cast<const frag_t<T> *>(&sQ[qb[ks & 1] + 16 * tt * D + 64 * (ks >> 1)]));
                 const int t = 16 * tt + n16;
                 const float bt = sb[t];
                 const f32x4 bs = *reinterpret_cast<const f32x4 *>(&sb[16 * st + 4 * q4]);
                 float v4[4];
-                if (!kk) {
-                    if constexpr (OUTP) {
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int s = 16 * st + 4 * q4 + r;
-                            v4[r] = s <= t ? p[r] * fexp2(bt - bs[r]) : 0.f;
-                        }
-                        const int o = t * LDT + ((16 * st + 4 * q4) ^ asw(t));
-                        st4_split<T, true>(&sP[o], &sPl[o], v4);
-                    }
-                } else {
-                    const float be = sbeta[t];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int s = 16 * st + 4 * q4 + r;
-                        v4[r] = s < t ? be * p[r] * fexp2(bt - bs[r]) : 0.f;
-                    }
-                    *reinterpret_cast<f32x4 *>(&sA[t * LDA + 16 * st + 4 * q4]) = f32x4{v4[0], v4[1], v4[2], v4[3]};
-                }
+                for (int r = 0; r < 4; ++r) v4[r] = 16 * st + 4 * q4 + r <= t ? p[r] * fexp2(bt - bs[r]) : 0.f;
+                const int o = tri_pos<1>(t, 16 * st + 4 * q4);
+                st4_split<T, true>(&sP[o], &sP[TRI + o], v4);
             }
-        };
-        scores(10);
-        __syncthreads();
-        gdn_tinv_hl<NT>(tid, sA, sTh, sTl);
-        gdn_wu<T, D, LDN, LDU, SWX>(w, lane, tro, sTh, sTl, sK, sV, sbeta, sq, sWh, sWl, sU);
-        __syncthreads();
-        if constexpr (OUTP) {
-            scores(0);
-            // P tiles above the diagonal that the output product reads are zero
-            for (int e = tid; e < (OUTP ? 512 : 0); e += NT) {
-                const int tile = e >> 8, rr = (e >> 4) & 15, cc = e & 15;
-                const int row = tile ? 32 + rr : rr, col = tile ? 48 + cc : 16 + cc;
-                sP[row * LDT + (col ^ asw(row))] = cvt<T>(0.f);
-                sPl[row * LDT + (col ^ asw(row))] = cvt<T>(0.f);
+            if (tid < 128) {  // the zero blocks (0,1) and (2,3) of the diagonal quadrants
+                const int b = tid >> 6, o = tri_pos<1>(32 * b + ((tid >> 2) & 15), 32 * b + 16 + 4 * (tid & 3));
+                *reinterpret_cast<s4v *>(&sP[o]) = s4v{0, 0, 0, 0};
+                *reinterpret_cast<s4v *>(&sP[TRI + o]) = s4v{0, 0, 0, 0};
             }
         }
-        __syncthreads();
+        if constexpr (!TPRE) {
+            gdn_a_scores<T, D, LDN, SWX>(w, lane, sK, sb, sbeta, sA);
+            __syncthreads();
+            gdn_tinv_hl(tid, sA, sT, sT + TRI);
+        }
 
-        // U[t][v] = Ubar[t][v] - sum_k W[t][k] S[k][v]  (rows t = prow(tt, r), column v = c0 + n16);
-        // the prep's M columns take Ubar = 0
-        f32x4 U[NS][4];
+        // X[t][v] = V[t][v] - gamma_t sum_k K[t][k] S[k][v] (rows t = prow(tt, r));
+        // O^T[v][t] = sum_k S[k][v] Q[t][k]
+        f32x4 X[NCT][4], O[NCT][4];
 #pragma unroll
-        for (int m = 0; m < NS; ++m)
+        for (int m = 0; m < NCT; ++m)
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    U[m][tt][r] = PREP && m == 0 ? 0.f : sU[prow(tt, r) * LDU + c0 + n16];
-        // O^T[v][t] = gamma_t sum_k S[k][v] Q[t][k] + sum_s U[s][v] P[t][s]
-        f32x4 O[4];
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) O[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int tt = 0; tt < 4; ++tt) X[m][tt] = O[m][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < D / 32; ++ks) {
-            frag_t<T> fh[NS], fl[NS];
+            frag_t<T> fh[NCT], fl[NCT];
 #pragma unroll
-            for (int m = 0; m < NS; ++m) split_acc<T, true>(S[m][2 * ks], S[m][2 * ks + 1], fh[m], fl[m]);
+            for (int m = 0; m < NCT; ++m) split_acc<T, true>(S[m][2 * ks], S[m][2 * ks + 1], fh[m], fl[m]);
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
-                // -W[t][32ks + 8q4 .. +7], t = arow(tt, n16), as its hi/lo pair
-                const int t = arow(tt, n16), pw = t * LDN + swz_col(t, 32 * ks + 8 * q4, SWX);
-                const frag_t<T> wh = *reinterpret_cast<const frag_t<T> *>(&sWh[pw]);
-                const frag_t<T> wl = *reinterpret_cast<const frag_t<T> *>(&sWl[pw]);
+                const frag_t<T> kf = *reinterpret_cast<const frag_t<T> *>(
+                    &sK[(((32 * ks) & SWX) ? ko.hi : ko.lo) + roff(tt) * LDN + 32 * ks]);
 #pragma unroll
-                for (int m = 0; m < NS; ++m) {
-                    mma(U[m][tt], wh, fh[m]);
-                    mma(U[m][tt], wh, fl[m]);
-                    mma(U[m][tt], wl, fh[m]);
+                for (int m = 0; m < NCT; ++m) {
+                    mma(X[m][tt], kf, fh[m]);
+                    mma(X[m][tt], kf, fl[m]);
                 }
-                if constexpr (OUTP) mma2<T, true>(O[tt], fh[0], fl[0], ldfrag(sQ, LDN, 16 * tt, 32 * ks, lane));
+                if constexpr (OUTP) {
+                    const frag_t<T> qf = *reinterpret_cast<const frag_t<T> *>(&sQ[qb[ks & 1] + 16 * tt * D + 64 * (ks >> 1)]);
+#pragma unroll
+                    for (int m = 0; m < NCT; ++m) mma2<T, true>(O[m][tt], fh[m], fl[m], qf);
+                }
+            }
+            if constexpr (OUTP) sched_fence();
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 gq = *reinterpret_cast<const f32x4 *>(&sq[prow(tt, 0)]);
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) X[m][tt] *= -gq;
+        }
+        if (!PREP || role) {
+#pragma unroll
+            for (int ks = 0; ks < C / 32; ++ks)
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    const frag_t<T> vf = ldfragTR<T, LDN, SWX>(sV, tro, 32 * ks, cl.base(m));
+                    mma(X[m][2 * ks], eye[0], vf);
+                    mma(X[m][2 * ks + 1], eye[1], vf);
+                }
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 be = *reinterpret_cast<const f32x4 *>(&sbeta[prow(tt, 0)]);
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) X[m][tt] *= be;
+        }
+        if constexpr (OUTP) sched_fence();
+        // U = T (beta o X)
+        f32x4 U[NCT][4];
+#pragma unroll
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) U[m][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            frag_t<T> xh[NCT], xl[NCT];
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) split_acc<T, true>(X[m][2 * ks], X[m][2 * ks + 1], xh[m], xl[m]);
+#pragma unroll
+            for (int tt = 2 * ks; tt < 4; ++tt) {
+                const frag_t<T> th = *reinterpret_cast<const frag_t<T> *>(&sT[ta + tri_a(tt, ks)]);
+                const frag_t<T> tl = *reinterpret_cast<const frag_t<T> *>(&sT[ta + TRI + tri_a(tt, ks)]);
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    mma(U[m][tt], th, xh[m]);
+                    mma(U[m][tt], th, xl[m]);
+                    mma(U[m][tt], tl, xh[m]);
+                }
             }
         }
         if constexpr (OUTP) {
+            __syncthreads();  // P is complete
+            sched_fence();
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) O[tt] *= sq[16 * tt + n16];
+            for (int tt = 0; tt < 4; ++tt) {
+                const float gt = sq[16 * tt + n16];
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) O[m][tt] *= gt;
+            }
 #pragma unroll
             for (int ks = 0; ks < C / 32; ++ks) {
-                frag_t<T> uh, ul;
-                split_acc<T, true>(U[0][2 * ks], U[0][2 * ks + 1], uh, ul);
+                frag_t<T> uh[NCT], ul[NCT];
 #pragma unroll
-                for (int tt = 0; tt < 4; ++tt) {
-                    if (32 * ks > 16 * tt + 15) continue;
-                    const int aw = asw(lane & 15);
-                    const frag_t<T> ph = *reinterpret_cast<const frag_t<T> *>(sP + (16 * tt + (lane & 15)) * LDT + ((32 * ks + 8 * (lane >> 4)) ^ aw));
-                    const frag_t<T> pl = *reinterpret_cast<const frag_t<T> *>(sPl + (16 * tt + (lane & 15)) * LDT + ((32 * ks + 8 * (lane >> 4)) ^ aw));
-                    mma(O[tt], uh, ph);
-                    mma(O[tt], uh, pl);
-                    mma(O[tt], ul, ph);
+                for (int m = 0; m < NCT; ++m) split_acc<T, true>(U[m][2 * ks], U[m][2 * ks + 1], uh[m], ul[m]);
+#pragma unroll
+                for (int tt = 2 * ks; tt < 4; ++tt) {
+                    const frag_t<T> ph = *reinterpret_cast<const frag_t<T> *>(&sP[pb + tri_b(tt, ks)]);
+                    const frag_t<T> pl = *reinterpret_cast<const frag_t<T> *>(&sP[pb + TRI + tri_b(tt, ks)]);
+#pragma unroll
+                    for (int m = 0; m < NCT; ++m) {
+                        mma(O[m][tt], uh[m], ph);
+                        mma(O[m][tt], uh[m], pl);
+                        mma(O[m][tt], ul[m], ph);
+                    }
                 }
             }
+            // V^new (optional): U[prow(tt, r)][col(m)]
+            if (VN) {
+                typedef short s1;
+                const rsrc_t rn = buf_rsrc(VN + c * cstep, cspan);
+                const uint32_t no = (uint32_t)((8 * q4 * a.sx_l + cl.col(0)) * (int64_t)sizeof(T));
+#pragma unroll
+                for (int m = 0; m < NCT; ++m)
+#pragma unroll
+                    for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            __builtin_amdgcn_raw_buffer_store_b16(
+                                __builtin_bit_cast(s1, cvt<T>(U[m][tt][r])), rn, no,
+                                (uint32_t)(((roff(tt) + r) * a.sx_l + 4 * m) * (int64_t)sizeof(T)), 0);
+            }
+        }
+        if constexpr (OUTP) {  // lane (q4, n16): channels c0 + 4 NCT q4 .. of token 16 tt + n16
             const rsrc_t ro = buf_rsrc(Y + c * cstep, cspan);
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) st4_buf<T>(ro, voff, tt * tstep, O[tt]);
-        }
-
-        // V^new (optional): U[prow(tt, r)][c0 + n16]
-        if (OUTP && VN) {
+            for (int tt = 0; tt < 4; ++tt) {
+                if constexpr (NCT == 2) {
+                    typedef T v8 __attribute__((ext_vector_type(8)));
+                    v8 o = {};
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    VN[(int64_t)(c * C + prow(tt, r)) * a.sx_l + c0 + n16] = cvt<T>(U[0][tt][r]);
+                    for (int r = 0; r < 4; ++r) {
+                        o[r] = cvt<T>(O[0][tt][r]);
+                        o[4 + r] = cvt<T>(O[1][tt][r]);
+                    }
+                    buf_st(ro, voff, tt * tstep, o);
+                } else {
+                    st4_buf<T>(ro, voff, tt * tstep, O[0][tt]);
+                }
+            }
         }
+        if constexpr (OUTP) sched_fence();
+        if (c + 1 < nch) issue(c + 1);
 
         // S = gamma_C S + K^T (e^{b_C - b} o U)
         const float gam = fexp2(b63);
 #pragma unroll
-        for (int m = 0; m < NS; ++m) {
+        for (int m = 0; m < NCT; ++m)
 #pragma unroll
             for (int i = 0; i < NK; ++i) S[m][i] *= gam;
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt)
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 ev = *reinterpret_cast<const f32x4 *>(&se[prow(tt, 0)]);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) U[m][tt][r] *= se[prow(tt, r)];
+            for (int m = 0; m < NCT; ++m) U[m][tt] *= ev;
         }
 #pragma unroll
         for (int ks = 0; ks < C / 32; ++ks) {
-            frag_t<T> uh[NS], ul[NS];
+            frag_t<T> uh[NCT], ul[NCT];
 #pragma unroll
-            for (int m = 0; m < NS; ++m) split_acc<T, true>(U[m][2 * ks], U[m][2 * ks + 1], uh[m], ul[m]);
+            for (int m = 0; m < NCT; ++m) split_acc<T, true>(U[m][2 * ks], U[m][2 * ks + 1], uh[m], ul[m]);
 #pragma unroll
             for (int i = 0; i < NK; ++i) {
                 const frag_t<T> kf = ldfragTR<T, LDN, SWX>(sK, tro8, 32 * ks, roff(i));
 #pragma unroll
-                for (int m = 0; m < NS; ++m) mma2b<T, true>(S[m][i], kf, uh[m], ul[m]);
+                for (int m = 0; m < NCT; ++m) mma2b<T, true>(S[m][i], kf, uh[m], ul[m]);
             }
         }
     }
-    // prep: M_J, N_J; walk: S_out after the last superchunk
+    // prep: M_J or N_J; walk: S_out after the last superchunk
     if (PREP || (OUTP && J == a.n_super - 1 && !(a.scan_out && a.n_super > 1))) {
-#pragma unroll
-        for (int m = 0; m < NS; ++m) {
-            float *dst = PREP ? (m == 0 ? a.wsM : a.wsN) + (int64_t)item * SS : a.S_out + bh * SS;
-#pragma unroll
-            for (int i = 0; i < NK; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[(int64_t)prow(i, r) * D + c0 + n16] = S[m][i][r];
-        }
+        sio.store(S, PREP ? (role == 0 ? a.wsM : a.wsN) + (int64_t)item * SS : a.S_out + bh * SS);
     }
 }
 
+// (batch, head) and columns of a scan workgroup: the D / 16 column blocks of a head
+// are 8 apart in dispatch order, on one XCD, whose L2 then reads the head's maps
+// once for all of them
+template <int D>
+__device__ __forceinline__ bool scan_item(const GdnArgs &a, int &bh, int &col0) {
+    const int x = blockIdx.x, r = x % (D / 2);
+    bh = x / (D / 2) * 8 + r % 8;
+    col0 = 16 * (r / 8);
+    return bh < a.B * a.H;
+}
+template <int D>
+dim3 scan_grid(unsigned bh) { return dim3((bh + 7) / 8 * (D / 2)); }
+
 // S_{J+1} = M_J S_J + N_J for J = 0 .. n_super - 2 in fp32, S_0 = S_in (or 0);
 // writes S_J (J < n_super) to wsS; with scan_out (maps of every superchunk)
-// one more step gives S_out.  Workgroup (b, h, 16-column block), four waves;
-// wave w owns the row tiles RTW w .. RTW w + RTW - 1 of the block, and the
-// product runs on the fp32 MFMA (16x16x4, fp32 products and sums): in step m
-// of the contraction lane (q4, n16) supplies M[row n16][KQ q4 + m] and
-// S[KQ q4 + m][col n16], the same order on both sides, so a lane's M operands
-// are KQ consecutive floats of its row.  M_J is staged in LDS (row pitch
-// D + 4 floats) with the next one prefetched in registers; S_J sits in LDS
-// (pitch 17) for the B operands.
+// one more step gives S_out.  Workgroup (b, h, 16-column block), D / 16 waves;
+// wave w owns the rows [16w, 16w + 16) of the block on the fp32 MFMA (16x16x4,
+// fp32 products and sums): slot (j, u) of the contraction is k = 32 (j / 2) + 8 q4 +
+// 4 (j % 2) + u on both sides, so a lane's M operands are 32-byte pieces of its row, loaded
+// straight into registers two steps ahead (two sets used alternately; no wave
+// reads another's rows, so M needs no LDS), and S_J, the only thing the waves
+// exchange, sits in LDS by columns (two buffers, one barrier a step).  A step is
+// bound by the fp32 MFMA rate of its CU (D^2 x 16 products, 1 us): 31 steps at D =
+// 128, H 8 take 75 us with M staged in LDS by four waves, 62 in this form.
 template <int D>
-__global__ void __launch_bounds__(256) k_gdn_scan(GdnArgs a) {
-    constexpr int NT = 256, LDM = D + 4, MV = D * D / 4 / NT, RTW = D / 64, KQ = D / 4, LS = 17;
-    __shared__ __attribute__((aligned(16))) float sM[D * LDM];
-    __shared__ float sS[D * LS];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
-    const int bh = blockIdx.x / (D / 16), col0 = 16 * (blockIdx.x % (D / 16));
+__global__ void __launch_bounds__(4 * D) k_gdn_scan(GdnArgs a) {
+    constexpr int NJ = D / 16, LS = D + 4;
+    __shared__ __attribute__((aligned(16))) float sS[2][16 * LS];  // [column][row]
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
+    int bh, col0;
+    if (!scan_item<D>(a, bh, col0)) return;
     const int64_t SS = (int64_t)D * D;
-    const int nJ = a.n_super;
+    const int nJ = a.n_super, last = a.scan_out ? nJ : nJ - 1;  // steps taken
+    const float *wsM = a.wsM + (int64_t)bh * a.n_prep * SS, *wsN = a.wsN + (int64_t)bh * a.n_prep * SS;
     float *wsS = a.wsS + (int64_t)bh * nJ * SS;
-    const float *wsM = a.wsM + (int64_t)bh * a.n_prep * SS;
-    const float *wsN = a.wsN + (int64_t)bh * a.n_prep * SS;
-    auto row = [&](int i, int r) { return 16 * (RTW * w + i) + 4 * q4 + r; };
-    f32x4 acc[RTW];  // S[row(i, r)][col0 + n16]
+    // the wave's rows 16w + 4 q4 + r of the state, column col0 + n16 (byte offsets)
+    const uint32_t so = (uint32_t)(((16 * w + 4 * q4) * D + col0 + n16) * 4);
+    const uint32_t mo = (uint32_t)(((16 * w + n16) * D + 8 * q4) * 4);
+    auto get = [&](const float *src) {
+        const rsrc_t rs = buf_rsrc(src, (uint32_t)(SS * 4));
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < RTW; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][r] = a.S_in ? a.S_in[bh * SS + (int64_t)row(i, r) * D + col0 + n16] : 0.f;
-    // M_J and N_J two steps ahead, in two register sets used alternately
-    f32x4 mA[MV], mB[MV];
-    float nA[RTW][4], nB[RTW][4];
-    auto fetch = [&](f32x4 (&mr)[MV], float (&nr)[RTW][4], int J) {
-        const f32x4 *m = reinterpret_cast<const f32x4 *>(wsM + (int64_t)J * SS);
-#pragma unroll
-        for (int i = 0; i < MV; ++i) mr[i] = m[tid + NT * i];
-#pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) nr[i][r] = wsN[(int64_t)J * SS + (int64_t)row(i, r) * D + col0 + n16];
+        for (int r = 0; r < 4; ++r) x[r] = buf_ld<float>(rs, so, r * D * 4);
+        return x;
     };
-    const int last = a.scan_out ? nJ : nJ - 1;  // steps taken
-    // S_J and S_out go out through buffer stores (32-bit lane offsets)
-    const rsrc_t rS = buf_rsrc(wsS, (uint32_t)(nJ * SS * 4));
+    auto put = [&](float *dst, const f32x4 &x) {
+        const rsrc_t rs = buf_rsrc(dst, (uint32_t)(SS * 4));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) buf_st(rs, so, r * D * 4, x[r]);
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (a.S_in) acc = get(a.S_in + bh * SS);
+    f32x4 mA[NJ], mB[NJ], nA = acc, nB = acc;
+    auto fetch = [&](f32x4 (&mr)[NJ], f32x4 &nr, int J) {
+        const rsrc_t rs = buf_rsrc(wsM + (int64_t)J * SS, (uint32_t)(SS * 4));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) mr[j] = buf_ld<f32x4>(rs, mo, 128 * (j >> 1) + 16 * (j & 1));
+        nr = get(wsN + (int64_t)J * SS);
+    };
     // step J: store S_J; unless J is the last, S_{J+1} = M_J S_J + N_J from
     // (mr, nr), which then take the maps of J + 2; false after the last store
-    auto step = [&](int J, f32x4 (&mr)[MV], float (&nr)[RTW][4]) {
-#pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sS[row(i, r) * LS + n16] = acc[i][r];
-                buf_st(rS, (uint32_t)((row(i, r) * D + col0 + n16) * 4), (uint32_t)(J * SS * 4), acc[i][r]);
-            }
+    auto step = [&](int J, f32x4 (&mr)[NJ], f32x4 &nr) {
+        if (J < nJ) put(wsS + (int64_t)J * SS, acc);
         if (J == last) return false;
-#pragma unroll
-        for (int i = 0; i < MV; ++i) {
-            const int e = 4 * (tid + NT * i);
-            *reinterpret_cast<f32x4 *>(&sM[(e / D) * LDM + e % D]) = mr[i];
-        }
+        float *const s = sS[J & 1];
+        *reinterpret_cast<f32x4 *>(&s[n16 * LS + 16 * w + 4 * q4]) = acc;
         __syncthreads();
+        acc = nr;
+        f32x4 acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < RTW; ++i) acc[i] = f32x4{nr[i][0], nr[i][1], nr[i][2], nr[i][3]};
-        if (J + 2 < last) fetch(mr, nr, J + 2);
-#pragma unroll 2
-        for (int m = 0; m < KQ; m += 4) {
-            float bv[4];
+        for (int j = 0; j < NJ; ++j) {
+            const f32x4 b = *reinterpret_cast<const f32x4 *>(&s[n16 * LS + 32 * (j >> 1) + 8 * q4 + 4 * (j & 1)]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) bv[u] = sS[(KQ * q4 + m + u) * LS + n16];
-#pragma unroll
-            for (int i = 0; i < RTW; ++i) {
-                const f32x4 av = *reinterpret_cast<const f32x4 *>(&sM[(16 * (RTW * w + i) + n16) * LDM + KQ * q4 + m]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u], acc[i], 0, 0, 0);
+            for (int u = 0; u < 4; u += 2) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(mr[j][u], b[u], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(mr[j][u + 1], b[u + 1], acc2, 0, 0, 0);
             }
         }
-        __syncthreads();  // every read of sM and sS is done
+        acc += acc2;
+        if (J + 2 < last) fetch(mr, nr, J + 2);
         return true;
     };
     if (last > 0) fetch(mA, nA, 0);
     if (last > 1) fetch(mB, nB, 1);
     for (int J = 0;; J += 2)
         if (!step(J, mA, nA) || !step(J + 1, mB, nB)) break;
-    if (a.scan_out) {  // the state after the last superchunk
-        const rsrc_t rO = buf_rsrc(a.S_out + bh * SS, (uint32_t)(SS * 4));
-#pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) buf_st(rO, (uint32_t)((row(i, r) * D + col0 + n16) * 4), 0u, acc[i][r]);
-    }
+    if (a.scan_out) put(a.S_out + bh * SS, acc);  // the state after the last superchunk
 }
 
 
@@ -687,29 +873,29 @@ __global__ void __launch_bounds__(256) k_gdn_scan(GdnArgs a) {
 //   k_gdn_dchunk:       the parameter gradients of every chunk, all chunks in
 //                       parallel, from the stored S and dS' (fp32 arithmetic).
 
+// The backward's state-gradient walk, its waves, columns and tiles as the forward
+// walks'.  Per chunk, each wave on its own columns:
+//   dU = e^{b_C - b} o (K dS') + P^T dO,   G_U = T^T dU,   dv = beta o G_U,
+//   dS = gamma_C dS' + Q^T (gamma o dO) - K^T (beta gamma o G_U)
+// (W^T dU = K^T diag(beta gamma) T^T dU, so W is not formed).  dv leaves through
+// an MFMA with the identity that turns its rounded values around, so a lane
+// stores consecutive channels of a token.
 template <typename T, int D, bool PREP>
-__global__ void __launch_bounds__(64 * D / 16) k_gdn_dwalk(GdnArgs a) {
-    constexpr int NW = D / 16, NT = 64 * NW, NK = D / 16;
-    constexpr int LDN = D + pad<T>(), LDT = C + pad<T>(), SWX = swx<T, D>();
-    constexpr int LDA = C + 4, LDU = D + 4;
-    __shared__ __attribute__((aligned(16))) T sQ[C * LDN];   // swizzled
-    __shared__ __attribute__((aligned(16))) T sK[C * LDN];   // swizzled
-    __shared__ __attribute__((aligned(16))) T sO[C * LDN];   // dO, swizzled
-    // P^T[s][t] = e^{b_t-b_s} k_s.q_t (s <= t) hi, then lo; T = (I + A)^{-1} lives here first
-    __shared__ __attribute__((aligned(16))) T sPP[2 * C * LDT];
-    static_assert(LDT == C + 16, "T's hi/lo pair has the P tiles' pitch");
-    T *sP = sPP, *sPl = sPP + C * LDT;
-    short *const sTh = reinterpret_cast<short *>(sPP), *const sTl = sTh + C * LDT;
-    // A until the inverse is formed, then -W as a hi/lo pair of bf16 tiles (see the walk)
-    constexpr int AWB = C * LDA * 4 > 2 * C * LDN * (int)sizeof(T) ? C * LDA * 4 : 2 * C * LDN * (int)sizeof(T);
-    __shared__ __attribute__((aligned(16))) char sAW[AWB];
-    float *const sA = reinterpret_cast<float *>(sAW);
-    T *const sWh = reinterpret_cast<T *>(sAW), *const sWl = sWh + C * LDN;
+__global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
+    constexpr bool TPRE = D == 128;
+    constexpr int NT = 256, NK = D / 16, NCT = GdnCols<D>::NCT;
+    constexpr int LDN = D + pad<T>(), SWX = swx<T, D>(), LDA = C + 4;
+    __shared__ __attribute__((aligned(16))) T sQ[C * LDN];      // swizzled
+    __shared__ __attribute__((aligned(16))) T sK[C * LDN];      // swizzled
+    __shared__ __attribute__((aligned(16))) T sO[C * LDN];      // dO, swizzled
+    __shared__ __attribute__((aligned(16))) short sT[2 * TRI];  // T, hi then lo
+    __shared__ __attribute__((aligned(16))) T sP[2 * TRI];      // P^T[s][t] = e^{b_t-b_s} k_s.q_t (s <= t), hi then lo
+    __shared__ __attribute__((aligned(16))) float sA[TPRE ? 4 : C * LDA];
     __shared__ __attribute__((aligned(16))) float sb[C], sq[C], se[C], sbeta[C];
 
     const int tid = threadIdx.x, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c0 = 16 * w;
+    const GdnCols<D> cl{16 * NCT * w, n16};
     const int nJ = PREP ? a.n_super - 1 : a.n_super;
     const int item = blockIdx.x, bh = item / nJ, J = (PREP ? 1 : 0) + item % nJ;
     const int bb = bh / a.H, hh = bh % a.H;
@@ -718,61 +904,66 @@ __global__ void __launch_bounds__(64 * D / 16) k_gdn_dwalk(GdnArgs a) {
     const T *Q = (const T *)a.q + xo;
     const T *K = (const T *)a.k + xo;
     const T *DO = (const T *)a.dO + xo;
+    const T *TW = TPRE ? (const T *)a.tw + xo : nullptr;
+    T *DV = (T *)a.dv + xo;
     const int64_t go = bb * a.sg_b + hh * a.sg_h + tok0 * a.sg_l;
     const float *gp = a.g + go;
     const float *bp = a.beta + go;
     const int64_t SS = (int64_t)D * D;
     const int nch = (int)((a.L - tok0 < a.ts ? a.L - tok0 : a.ts) / C);
-    const LaneOff tro = tr_off<T, LDN, SWX>(lane), swo = swz_off<T, LDN, SWX>(lane);
-    const LaneOff tro8 = tr_off8<T, LDN, SWX>(lane);
-    auto asw = [](int row) { return sizeof(T) == 2 ? 8 * ((row >> 2) & 1) : 0; };
-    // Accumulator pairs (2m, 2m+1) of dS (rows: key channels) and of dU (rows:
-    // tokens) hold, in lane row q4, indices 32m + 8 q4 .. +7 (slot r of tile i:
-    // prow(i, r)), so each pair splits into an operand fragment in plain order
-    // with no lane swaps; the products that build them read their A rows in that
-    // order (fragment row n of tile i: arow(i, n)).
+    const LaneOff swo = swz_off<T, LDN, SWX>(lane), tro8 = tr_off8<T, LDN, SWX>(lane);
+    const LaneOff tro = NCT == 2 ? tro8 : tr_off<T, LDN, SWX>(lane);  // this wave's own columns
+    // rows of the accumulators and of the fragments that build them: see the forward walk
     auto prow = [&](int i, int r) { return 32 * (i >> 1) + 8 * q4 + 4 * (i & 1) + r; };
-    auto arow = [](int i, int n) { return 32 * (i >> 1) + 8 * (n >> 2) + 4 * (i & 1) + (n & 3); };
-    auto roff = [](int i) { return 32 * (i >> 1) + 4 * (i & 1); };  // ldfragTR column for tro8
+    const int ar = 8 * (n16 >> 2) + (n16 & 3);
+    auto roff = [](int i) { return 32 * (i >> 1) + 4 * (i & 1); };
+    const LaneOff ko = {ar * LDN + 8 * q4 + ((n16 >> 2) & 1) * SWX, ar * LDN + 8 * q4 - ((n16 >> 2) & 1) * SWX};
 
-    // dS[prow(i, r)][c0 + n16]: from dS_end(J) (dS_out for one superchunk), or 0 (prep)
-    f32x4 dS[NK];
-    {
+    const int ta = tri_pos<0>(ar, 8 * q4);
+    const int tt8 = tri_pos<0>(8 * q4 + (n16 >> 2), 8 * (n16 & 3));  // T's transposing reads
+
+    // dS[m][i][r] = dS[prow(i, r)][col(m)]: from dS_end(J) (dS_out for one superchunk), or 0 (prep)
+    const StateIO<D> sio(cl, q4);
+    f32x4 dS[NCT][NK];
+#pragma unroll
+    for (int m = 0; m < NCT; ++m)
+#pragma unroll
+        for (int i = 0; i < NK; ++i) dS[m][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!PREP) {
         const float *src = a.n_super == 1 ? (a.dS_out ? a.dS_out + bh * SS : nullptr)
                                           : a.wsDe + ((int64_t)bh * a.n_super + J) * SS;
-#pragma unroll
-        for (int i = 0; i < NK; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                dS[i][r] = (!PREP && src) ? src[(int64_t)prow(i, r) * D + c0 + n16] : 0.f;
+        if (src) sio.load(dS, src);
     }
 
     using TT = Tile<T, D, NT>;
     TT t1, t2, t3;
+    TriTile<T> t4;
     float gl, bl;
     const int64_t cstep = (int64_t)C * a.sx_l;
     const uint32_t cspan = chunk_span<T, D>(a.sx_l), gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4);
     uint32_t toff[TT::RPT];
     TT::offsets(toff, a.sx_l, tid);
     const uint32_t goff = (uint32_t)(lane * a.sg_l * 4);
+    const uint32_t tstep = (uint32_t)(16 * a.sx_l * (int64_t)sizeof(T));
+    const int t4base = TriTile<T>::base(tid);
+    const uint32_t t4off = (uint32_t)(((tid >> 4) * a.sx_l + 8 * (tid & 15)) * (int64_t)sizeof(T));
+    const uint32_t voff = (uint32_t)((n16 * a.sx_l + cl.c0 + 4 * NCT * q4) * (int64_t)sizeof(T));
     auto issue = [&](int c) {
         const int64_t nx = c * cstep;
         t1.load_buf(buf_rsrc(Q + nx, cspan), toff, 0);
         t2.load_buf(buf_rsrc(K + nx, cspan), toff, 0);
-        t3.load_buf(buf_rsrc(DO + nx, cspan), toff, 0);
         gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
         bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        if constexpr (TPRE) t4.load(buf_rsrc(TW + nx, cspan), t4off, tstep, tid);
+        t3.load_buf(buf_rsrc(DO + nx, cspan), toff, 0);
     };
     if (nch > 0) issue(nch - 1);
 
+    const unsigned par = pair_parity(a.n_cu);
     for (int c = nch - 1; c >= 0; --c) {
-        if constexpr (!PREP) {  // dS' of chunk c: the gradient of the state leaving it
-            float *dst = a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS;
-#pragma unroll
-            for (int i = 0; i < NK; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dst[(int64_t)prow(i, r) * D + c0 + n16] = dS[i][r];
-        }
+        pair_turn(par);
+        if constexpr (!PREP)  // dS' of chunk c: the gradient of the state leaving it
+            sio.store(dS, a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS);
         const float b2 = wave_scan_dpp(gl * LOG2E);
         const float b63 = lane_value(b2, 63);
         const float betal = bl;
@@ -780,203 +971,262 @@ __global__ void __launch_bounds__(64 * D / 16) k_gdn_dwalk(GdnArgs a) {
         t1.store_swz(sQ, LDN, tid, SWX);
         t2.store_swz(sK, LDN, tid, SWX);
         t3.store_swz(sO, LDN, tid, SWX);
-        if (w == 0) {
+        if constexpr (TPRE) t4.store(sT, t4base, tid);
+        if (w == 3) {
             sb[lane] = b2;
             sq[lane] = fexp2(b2);
             se[lane] = fexp2(b63 - b2);
             sbeta[lane] = betal;
         }
         __syncthreads();
-        if (c > 0) issue(c - 1);
 
-        // scores on the causal tiles: k_s . k_t -> A first; k_s . q_t -> P^T after the
-        // solve, whose T occupies the P tiles' LDS
-        auto scores = [&](int i0) {
-        for (int i = i0 + w; i < i0 + 10; i += NW) {
-            const bool kk = i >= 10;
+        // P^T on the causal tiles: rows t of the accumulator, 4 of one row s of P^T
+        for (int i = w; i < 10; i += 4) {
             int tt, st;
-            tri_tile(kk ? i - 10 : i, tt, st);
+            tri_tile(i, tt, st);
             f32x4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < D / 32; ++ks) {
-                const frag_t<T> kf = ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * st, 32 * ks);
-                const frag_t<T> xf = ldfrag_swz<T, LDN, SWX>(kk ? sK : sQ, swo, 16 * tt, 32 * ks);
-                mma(p, kf, xf);
-            }
-            const int t = 16 * tt + n16;
-            const float bt = sb[t];
-            const f32x4 bs = *reinterpret_cast<const f32x4 *>(&sb[16 * st + 4 * q4]);
-            if (!kk) {
+            for (int ks = 0; ks < D / 32; ++ks)
+                mma(p, ldfrag_swz<T, LDN, SWX>(sQ, swo, 16 * tt, 32 * ks), ldfrag_swz<T, LDN, SWX>(sK, swo, 16 * st, 32 * ks));
+            const int s = 16 * st + n16;
+            const float bs = sb[s];
+            const f32x4 bt = *reinterpret_cast<const f32x4 *>(&sb[16 * tt + 4 * q4]);
+            float v4[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int s = 16 * st + 4 * q4 + r;
-                    const float v = s <= t ? p[r] * fexp2(bt - bs[r]) : 0.f;
-                    const T h = cvt<T>(v);
-                    sP[s * LDT + (t ^ asw(s))] = h;
-                    sPl[s * LDT + (t ^ asw(s))] = cvt<T>(v - tof<T>(h));
-                }
-            } else {
-                const float be = sbeta[t];
-                float v4[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int s = 16 * st + 4 * q4 + r;
-                    v4[r] = s < t ? be * p[r] * fexp2(bt - bs[r]) : 0.f;
-                }
-                *reinterpret_cast<f32x4 *>(&sA[t * LDA + 16 * st + 4 * q4]) = f32x4{v4[0], v4[1], v4[2], v4[3]};
-            }
+            for (int r = 0; r < 4; ++r) v4[r] = s <= 16 * tt + 4 * q4 + r ? p[r] * fexp2(bt[r] - bs) : 0.f;
+            const int o = tri_pos<0>(s, 16 * tt + 4 * q4);
+            st4_split<T, true>(&sP[o], &sP[TRI + o], v4);
         }
-        };
-        scores(10);
-        __syncthreads();
-        gdn_tinv_hl<NT>(tid, sA, sTh, sTl);
-        gdn_wu<T, D, LDN, LDU, SWX>(w, lane, tro, sTh, sTl, sK, (const T *)nullptr, sbeta, sq, sWh, sWl, nullptr);
-        __syncthreads();
-        scores(0);
-        // P^T tiles below the diagonal that the dU product reads are zero
-        for (int e = tid; e < 512; e += NT) {
-            const int tile = e >> 8, rr = (e >> 4) & 15, cc = e & 15;
-            const int row = tile ? 48 + rr : 16 + rr, col = tile ? 32 + cc : cc;
-            sP[row * LDT + (col ^ asw(row))] = cvt<T>(0.f);
-            sPl[row * LDT + (col ^ asw(row))] = cvt<T>(0.f);
+        if (tid < 128) {  // the zero blocks (1,0) and (3,2) of the diagonal quadrants
+            const int b = tid >> 6, o = tri_pos<0>(32 * b + 16 + ((tid >> 2) & 15), 32 * b + 4 * (tid & 3));
+            *reinterpret_cast<s4v *>(&sP[o]) = s4v{0, 0, 0, 0};
+            *reinterpret_cast<s4v *>(&sP[TRI + o]) = s4v{0, 0, 0, 0};
         }
-        __syncthreads();
+        if constexpr (!TPRE) {
+            gdn_a_scores<T, D, LDN, SWX>(w, lane, sK, sb, sbeta, sA);
+            __syncthreads();
+            gdn_tinv_hl(tid, sA, sT, sT + TRI);
+        }
 
         // dU[t][v] = e^{b_C - b_t} sum_k K[t][k] dS[k][v] + sum_{t' >= t} P^T[t][t'] dO[t'][v]
-        // (rows t = prow(tt, r), column v = c0 + n16)
-        f32x4 dU[4];
+        // (rows t = prow(tt, r))
+        f32x4 dU[NCT][4];
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt) dU[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) dU[m][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < D / 32; ++ks) {
-            frag_t<T> fh, fl;
-            split_acc<T, true>(dS[2 * ks], dS[2 * ks + 1], fh, fl);
+            frag_t<T> fh[NCT], fl[NCT];
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) split_acc<T, true>(dS[m][2 * ks], dS[m][2 * ks + 1], fh[m], fl[m]);
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
-                const int t = arow(tt, n16);  // K[t][32ks + 8q4 ..] (swizzled rows)
-                const frag_t<T> kf =
-                    *reinterpret_cast<const frag_t<T> *>(&sK[t * LDN + swz_col(t, 32 * ks + 8 * q4, SWX)]);
-                mma(dU[tt], kf, fh);
-                mma(dU[tt], kf, fl);
+                const frag_t<T> kf = *reinterpret_cast<const frag_t<T> *>(
+                    &sK[(((32 * ks) & SWX) ? ko.hi : ko.lo) + roff(tt) * LDN + 32 * ks]);
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    mma(dU[m][tt], kf, fh[m]);
+                    mma(dU[m][tt], kf, fl[m]);
+                }
             }
         }
 #pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 ev = *reinterpret_cast<const f32x4 *>(&se[prow(tt, 0)]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dU[tt][r] *= se[prow(tt, r)];
+            for (int m = 0; m < NCT; ++m) dU[m][tt] *= ev;
+        }
+        __syncthreads();  // P^T is complete
 #pragma unroll
         for (int ks = 0; ks < C / 32; ++ks) {
-            const frag_t<T> of = ldfragTR<T, LDN, SWX>(sO, tro, 32 * ks, c0);
+            frag_t<T> of[NCT];
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                if (32 * ks + 31 < 16 * tt) continue;
-                const int row = arow(tt, n16);
-                const int o = row * LDT + ((32 * ks + 8 * (lane >> 4)) ^ asw(row));
-                mma(dU[tt], *reinterpret_cast<const frag_t<T> *>(sP + o), of);
-                mma(dU[tt], *reinterpret_cast<const frag_t<T> *>(sPl + o), of);
+            for (int m = 0; m < NCT; ++m) of[m] = ldfragTR<T, LDN, SWX>(sO, tro, 32 * ks, cl.base(m));
+#pragma unroll
+            for (int tt = 0; tt < 2 * ks + 2; ++tt) {
+                const frag_t<T> ph = *reinterpret_cast<const frag_t<T> *>(&sP[ta + tri_a(tt, ks)]);
+                const frag_t<T> pl = *reinterpret_cast<const frag_t<T> *>(&sP[ta + TRI + tri_a(tt, ks)]);
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    mma(dU[m][tt], ph, of[m]);
+                    mma(dU[m][tt], pl, of[m]);
+                }
+            }
+        }
+        // G_U[s][v] = sum_{t >= s} T[t][s] dU[t][v] (rows s = prow(tt, r))
+        f32x4 G[NCT][4];
+#pragma unroll
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) G[m][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // rows s = ar + roff(tt), contraction t = 32 ks + 8 q4 + j (the swizzle ignores row bit 2)
+        auto t_tr = [&](const short *M, int ks, int tt) {
+            typedef short s8 __attribute__((ext_vector_type(8)));
+            const short *p = M + tt8 + (ks + (tt >> 1)) * 1024 + 4 * (tt & 1);
+            const s4v x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)p);
+            const s4v x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)(p + 4 * 32));
+            const s8 v = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
+            return __builtin_bit_cast(frag_t<T>, v);
+        };
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            frag_t<T> xh[NCT], xl[NCT];
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) split_acc<T, true>(dU[m][2 * ks], dU[m][2 * ks + 1], xh[m], xl[m]);
+#pragma unroll
+            for (int tt = 0; tt < 2 * ks + 2; ++tt) {
+                const frag_t<T> th = t_tr(sT, ks, tt), tl = t_tr(sT + TRI, ks, tt);
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    mma(G[m][tt], th, xh[m]);
+                    mma(G[m][tt], th, xl[m]);
+                    mma(G[m][tt], tl, xh[m]);
+                }
+            }
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 be = *reinterpret_cast<const f32x4 *>(&sbeta[prow(tt, 0)]);
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) G[m][tt] *= be;
+        }
+        if constexpr (!PREP) {  // dv[s][v], turned to rows v, columns s = 16 tt + n16
+            const rsrc_t rv = buf_rsrc(DV + c * cstep, cspan);
+            frag_t<T> eye[2];  // column 16 tt + n16 of tile tt against its own 32 tokens
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) eye[h][j] = (T)(q4 == 2 * h + (n16 >> 3) && j == (n16 & 7) ? 1.f : 0.f);
+#pragma unroll
+            for (int ks = 0; ks < C / 32; ++ks) {
+                frag_t<T> vf[NCT];
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) vf[m] = frag_from_acc<T>(G[m][2 * ks], G[m][2 * ks + 1]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    f32x4 o[NCT];
+#pragma unroll
+                    for (int m = 0; m < NCT; ++m) {
+                        o[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        mma(o[m], vf[m], eye[h]);
+                    }
+                    if constexpr (NCT == 2) {
+                        typedef T v8 __attribute__((ext_vector_type(8)));
+                        v8 x = {};
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            x[r] = cvt<T>(o[0][r]);
+                            x[4 + r] = cvt<T>(o[1][r]);
+                        }
+                        buf_st(rv, voff, (2 * ks + h) * tstep, x);
+                    } else {
+                        st4_buf<T>(rv, voff, (2 * ks + h) * tstep, o[0]);
+                    }
+                }
             }
         }
 
-        // dS = gamma_C dS + Q^T diag(gamma) dO - W^T dU
+        if (c > 0) issue(c - 1);
+
+        // dS = gamma_C dS + Q^T (gamma o dO) - K^T (beta gamma o G_U)
         const float gam = fexp2(b63);
 #pragma unroll
-        for (int i = 0; i < NK; ++i) dS[i] *= gam;
+        for (int m = 0; m < NCT; ++m)
+#pragma unroll
+            for (int i = 0; i < NK; ++i) dS[m][i] *= gam;
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const f32x4 gq = *reinterpret_cast<const f32x4 *>(&sq[prow(tt, 0)]);
+#pragma unroll
+            for (int m = 0; m < NCT; ++m) G[m][tt] *= -gq;
+        }
 #pragma unroll
         for (int ks = 0; ks < C / 32; ++ks) {
-            f32x4 g0, g1;  // gamma_t dO[t][c0 + n16], t = 32ks + 8q4 + 4h + r
+            const f32x4 g0 = *reinterpret_cast<const f32x4 *>(&sq[32 * ks + 8 * q4]);
+            const f32x4 g1 = *reinterpret_cast<const f32x4 *>(&sq[32 * ks + 8 * q4 + 4]);
+            const float gt[8] = {g0[0], g0[1], g0[2], g0[3], g1[0], g1[1], g1[2], g1[3]};
+            frag_t<T> gh[NCT], glo[NCT], uh[NCT], ul[NCT];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int ta = 32 * ks + 8 * q4 + r, tb = ta + 4;
-                g0[r] = sq[ta] * tof<T>(sO[ta * LDN + swz_col(ta, c0 + n16, SWX)]);
-                g1[r] = sq[tb] * tof<T>(sO[tb * LDN + swz_col(tb, c0 + n16, SWX)]);
+            for (int m = 0; m < NCT; ++m) {
+                split_scaled<T, true>(ldfragTR<T, LDN, SWX>(sO, tro, 32 * ks, cl.base(m)), gt, gh[m], glo[m]);
+                split_acc<T, true>(G[m][2 * ks], G[m][2 * ks + 1], uh[m], ul[m]);
             }
-            frag_t<T> gh, glo, uh, ul;
-            split_acc<T, true>(g0, g1, gh, glo);
-            split_acc<T, true>(dU[2 * ks], dU[2 * ks + 1], uh, ul);
 #pragma unroll
             for (int i = 0; i < NK; ++i) {
-                mma2b<T, true>(dS[i], ldfragTR<T, LDN, SWX>(sQ, tro8, 32 * ks, roff(i)), gh, glo);
-                // -W[t][k] hi/lo, k = arow(i, lane % 16), t = 32ks + 8 (lane / 16) + j
-                const frag_t<T> wh = ldfragTR<T, LDN, SWX>(sWh, tro8, 32 * ks, roff(i));
-                const frag_t<T> wl = ldfragTR<T, LDN, SWX>(sWl, tro8, 32 * ks, roff(i));
-                mma(dS[i], wh, uh);
-                mma(dS[i], wh, ul);
-                mma(dS[i], wl, uh);
+                const frag_t<T> qf = ldfragTR<T, LDN, SWX>(sQ, tro8, 32 * ks, roff(i));
+                const frag_t<T> kf = ldfragTR<T, LDN, SWX>(sK, tro8, 32 * ks, roff(i));
+#pragma unroll
+                for (int m = 0; m < NCT; ++m) {
+                    mma2b<T, true>(dS[m][i], qf, gh[m], glo[m]);
+                    mma2b<T, true>(dS[m][i], kf, uh[m], ul[m]);
+                }
             }
         }
     }
     float *dst = PREP ? a.wsE + ((int64_t)bh * (a.n_super - 1) + J - 1) * SS : (J == 0 ? a.dS_in + bh * SS : nullptr);
-    if (dst) {
-#pragma unroll
-        for (int i = 0; i < NK; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) dst[(int64_t)prow(i, r) * D + c0 + n16] = dS[i][r];
-    }
+    if (dst) sio.store(dS, dst);
 }
 
 // dS_end(n-1) = dS_out (or 0); dS_end(J-1) = M_J^T dS_end(J) + E_J, written to
-// wsDe for every J.  Same shape of work as k_gdn_scan, with M_J read
-// transposed: in step m lane (q4, n16) supplies M[4 m + q4][row n16] (the
-// pitch D + 16 spreads the four q4 rows over the banks) and dS[4 m + q4][col].
+// wsDe for every J.  Same shape of work as k_gdn_scan, with M_J read transposed:
+// slot m of the contraction is k = 4 m + q4, so a lane loads one column of M_J, the
+// lanes of a row 64 consecutive bytes.
 template <int D>
-__global__ void __launch_bounds__(256) k_gdn_dscan(GdnArgs a) {
-    constexpr int NT = 256, LDM = D + 16, MV = D * D / 4 / NT, RTW = D / 64, LS = 17;
-    __shared__ __attribute__((aligned(16))) float sM[D * LDM];
-    __shared__ float sS[D * LS];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
-    const int bh = blockIdx.x / (D / 16), col0 = 16 * (blockIdx.x % (D / 16));
+__global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
+    constexpr int NM = D / 4, LS = D + 4;
+    __shared__ __attribute__((aligned(16))) float sS[2][16 * LS];  // [column][slot]: slot NM q4 + m is row 4 m + q4
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
+    int bh, col0;
+    if (!scan_item<D>(a, bh, col0)) return;
     const int64_t SS = (int64_t)D * D;
     const int nJ = a.n_super;
     float *wsDe = a.wsDe + (int64_t)bh * nJ * SS;
-    const float *wsM = a.wsM + (int64_t)bh * a.n_prep * SS;
-    const float *wsE = a.wsE + (int64_t)bh * (nJ - 1) * SS;
-    auto row = [&](int i, int r) { return 16 * (RTW * w + i) + 4 * q4 + r; };
-    f32x4 acc[RTW];  // dS[row(i, r)][col0 + n16]
+    const float *wsM = a.wsM + (int64_t)bh * a.n_prep * SS, *wsE = a.wsE + (int64_t)bh * (nJ - 1) * SS;
+    const uint32_t so = (uint32_t)(((16 * w + 4 * q4) * D + col0 + n16) * 4);
+    const uint32_t mo = (uint32_t)((q4 * D + 16 * w + n16) * 4);
+    auto get = [&](const float *src) {
+        const rsrc_t rs = buf_rsrc(src, (uint32_t)(SS * 4));
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < RTW; ++i)
+        for (int r = 0; r < 4; ++r) x[r] = buf_ld<float>(rs, so, r * D * 4);
+        return x;
+    };
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (a.dS_out) acc = get(a.dS_out + bh * SS);
+    float mA[NM], mB[NM];
+    f32x4 nA = acc, nB = acc;
+    auto fetch = [&](float (&mr)[NM], f32x4 &nr, int J) {
+        const rsrc_t rs = buf_rsrc(wsM + (int64_t)J * SS, (uint32_t)(SS * 4));
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[i][r] = a.dS_out ? a.dS_out[bh * SS + (int64_t)row(i, r) * D + col0 + n16] : 0.f;
-    // M_J and E_{J-1} two steps ahead, in two register sets used alternately
-    f32x4 mA[MV], mB[MV];
-    float nA[RTW][4], nB[RTW][4];
-    auto fetch = [&](f32x4 (&mr)[MV], float (&nr)[RTW][4], int J) {
-        const f32x4 *m = reinterpret_cast<const f32x4 *>(wsM + (int64_t)J * SS);
-#pragma unroll
-        for (int i = 0; i < MV; ++i) mr[i] = m[tid + NT * i];
-#pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) nr[i][r] = wsE[(int64_t)(J - 1) * SS + (int64_t)row(i, r) * D + col0 + n16];
+        for (int m = 0; m < NM; ++m) mr[m] = buf_ld<float>(rs, mo, 4 * m * D * 4);
+        nr = get(wsE + (int64_t)(J - 1) * SS);
     };
     // step J: store dS_end(J); unless J = 0, dS_end(J-1) = M_J^T dS_end(J) +
     // E_{J-1} from (mr, nr), which then take the maps of J - 2; false after J = 0
-    auto step = [&](int J, f32x4 (&mr)[MV], float (&nr)[RTW][4]) {
+    auto step = [&](int J, float (&mr)[NM], f32x4 &nr) {
+        const rsrc_t rs = buf_rsrc(wsDe + (int64_t)J * SS, (uint32_t)(SS * 4));
+        float *const s = sS[J & 1];
 #pragma unroll
-        for (int i = 0; i < RTW; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                sS[row(i, r) * LS + n16] = acc[i][r];
-                wsDe[(int64_t)J * SS + (int64_t)row(i, r) * D + col0 + n16] = acc[i][r];
-            }
+        for (int r = 0; r < 4; ++r) {
+            buf_st(rs, so, r * D * 4, acc[r]);
+            s[n16 * LS + NM * r + 4 * w + q4] = acc[r];  // row 16w + 4 q4 + r
+        }
         if (J == 0) return false;
-#pragma unroll
-        for (int i = 0; i < MV; ++i) {
-            const int e = 4 * (tid + NT * i);
-            *reinterpret_cast<f32x4 *>(&sM[(e / D) * LDM + e % D]) = mr[i];
-        }
         __syncthreads();
+        acc = nr;
+        f32x4 acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < RTW; ++i) acc[i] = f32x4{nr[i][0], nr[i][1], nr[i][2], nr[i][3]};
+        for (int m = 0; m < NM; m += 4) {
+            const f32x4 b = *reinterpret_cast<const f32x4 *>(&s[n16 * LS + NM * q4 + m]);
+#pragma unroll
+            for (int u = 0; u < 4; u += 2) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(mr[m + u], b[u], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_16x16x4f32(mr[m + u + 1], b[u + 1], acc2, 0, 0, 0);
+            }
+        }
+        acc += acc2;
         if (J - 2 >= 1) fetch(mr, nr, J - 2);
-#pragma unroll 4
-        for (int m = 0; m < D / 4; ++m) {
-            const float bv = sS[(4 * m + q4) * LS + n16];
-#pragma unroll
-            for (int i = 0; i < RTW; ++i)
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(sM[(4 * m + q4) * LDM + 16 * (RTW * w + i) + n16], bv, acc[i],
-                                                              0, 0, 0);
-        }
-        __syncthreads();
         return true;
     };
     if (nJ > 1) fetch(mA, nA, nJ - 1);
@@ -997,7 +1247,7 @@ __global__ void __launch_bounds__(256) k_gdn_dscan(GdnArgs a) {
 //   G_W = T^T (-dU S^T) = -G_U S^T,   dA = -(G_W W^T + G_U Ubar^T) = -G_U U^T.
 // Per block J, waves 0-7 (group A) and 8-15 (group B):
 //   A: Y = K S_J, R = diag(beta) (V_J - diag(gamma) Y), U_J = T R;
-//   B: dU_J = diag(e) K dS'_J + P^T dO_J, G_U,J = T^T dU_J (dv_J = beta G_U,J);
+//   B: dU_J = diag(e) K dS'_J + P^T dO_J, G_U,J = T^T dU_J (dv is the dS walk's);
 //   A: G_W -= G_U,J S_J^T, dK_S += U_J dS'_J^T;
 //   B: dQ_S += dO_J S_J^T, dA -= G_U,J U_J^T, dP += dO_J U_J^T.
 // After the blocks (Gamma[t][s] = e^{b_t - b_s}, Ah = dA o beta_t Gamma):
@@ -1239,7 +1489,7 @@ __global__ void __launch_bounds__(1024) k_gdn_dchunk(GdnArgs a) {
         float rGUv[4] = {0.f, 0.f, 0.f, 0.f};  // B: sum_v G_U v over the blocks
 
         for (int jb = 0; jb < NBLK; ++jb) {
-            const int v0 = jb * VB, nb = half;  // the wave's 16 columns of the block
+            const int nb = half;  // the wave's 16 columns of the block
             asm volatile("" : "+v"(lane));      // (as at the top of the item loop)
             q4 = lane >> 4;
             n16 = lane & 15;
@@ -1296,7 +1546,7 @@ __global__ void __launch_bounds__(1024) k_gdn_dchunk(GdnArgs a) {
                 }
 #pragma unroll
                 for (int r = 0; r < 4; ++r) sU[(16 * mt + 4 * q4 + r) * LDU + 16 * nb + n16] = u[r];
-            } else {  // G_U,J = T^T dU_J;  dv_J = beta G_U,J
+            } else {  // G_U,J = T^T dU_J
                 f32x4 gu = z4;
 #pragma unroll 1
                 for (int kk = 0; kk < C; kk += 32) {
@@ -1310,7 +1560,6 @@ __global__ void __launch_bounds__(1024) k_gdn_dchunk(GdnArgs a) {
                 for (int r = 0; r < 4; ++r) {
                     const int t = 16 * mt + 4 * q4 + r, v = 16 * nb + n16;
                     sGU[t * LDU + v] = gu[r];
-                    ((T *)a.dv)[xo0 + (int64_t)t * a.sx_l + v0 + v] = cvt<T>(sbe[t] * gu[r]);
                     rGUv[r] = fmaf(gu[r], tof<T>(sV[t * LDV + v]), rGUv[r]);
                 }
             }
@@ -1503,12 +1752,17 @@ __global__ void __launch_bounds__(1024) k_gdn_dchunk(GdnArgs a) {
 template <int D>
 hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const unsigned bh = (unsigned)(a.B * a.H);
-    const dim3 wblk(64 * D / 16);
+    const dim3 wblk(256);
     switch (phase) {
-    case GDN_PREP:
-        hipExtLaunchKernelGGL((k_gdn_walk<__bf16, D, W_PREP>), dim3(bh * a.n_prep), wblk, 0, s, e0, e1, 0, a);
+    case GDN_TPREP:
+        if constexpr (D == 128)
+            hipExtLaunchKernelGGL((k_gdn_tprep<__bf16, D>), dim3((unsigned)(bh * (a.L / C))), wblk, 0, s, e0, e1, 0, a);
         break;
-    case GDN_SCAN: hipExtLaunchKernelGGL((k_gdn_scan<D>), dim3(bh * (D / 16)), dim3(256), 0, s, e0, e1, 0, a); break;
+    case GDN_PREP:  // M_J and N_J of 8 items per 16 workgroups
+        hipExtLaunchKernelGGL((k_gdn_walk<__bf16, D, W_PREP>), dim3((bh * a.n_prep + 7) / 8 * 16), wblk, 0, s, e0, e1, 0,
+                              a);
+        break;
+    case GDN_SCAN: hipExtLaunchKernelGGL((k_gdn_scan<D>), scan_grid<D>(bh), dim3(4 * D), 0, s, e0, e1, 0, a); break;
     case GDN_OUT:
         hipExtLaunchKernelGGL((k_gdn_walk<__bf16, D, W_OUT>), dim3(bh * a.n_super), wblk, 0, s, e0, e1, 0, a);
         break;
@@ -1518,7 +1772,7 @@ hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0
     case GDN_DPREP:
         hipExtLaunchKernelGGL((k_gdn_dwalk<__bf16, D, true>), dim3(bh * (a.n_super - 1)), wblk, 0, s, e0, e1, 0, a);
         break;
-    case GDN_DSCAN: hipExtLaunchKernelGGL((k_gdn_dscan<D>), dim3(bh * (D / 16)), dim3(256), 0, s, e0, e1, 0, a); break;
+    case GDN_DSCAN: hipExtLaunchKernelGGL((k_gdn_dscan<D>), scan_grid<D>(bh), dim3(4 * D), 0, s, e0, e1, 0, a); break;
     case GDN_DWALK:
         hipExtLaunchKernelGGL((k_gdn_dwalk<__bf16, D, false>), dim3(bh * a.n_super), wblk, 0, s, e0, e1, 0, a);
         break;
@@ -1541,7 +1795,12 @@ hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0
 hipError_t launch_gdn_phase(int phase, const GdnArgs &a, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (a.n_super < 1) return hipErrorInvalidValue;
     const bool multi = a.n_super > 1;
+    if (D == 128 && phase != GDN_SCAN && phase != GDN_DSCAN && phase != GDN_DCHUNK && a.L >= C && !a.tw)
+        return hipErrorInvalidValue;
     switch (phase) {
+    case GDN_TPREP:
+        if (D != 128 || a.L < C) return hipErrorInvalidValue;
+        break;
     case GDN_PREP:
     case GDN_SCAN:
         if (!multi || !a.wsS || !a.wsM || !a.wsN || a.n_prep < a.n_super - 1) return hipErrorInvalidValue;
