@@ -61,107 +61,22 @@ __device__ __forceinline__ void split4(const f32x4 &x, s4v &hi, s4v &lo) {
     }
 }
 
-// Column c of (I + diag(rs) M)^{-1} for a strictly lower 16 x 16 block M
-// (row pitch ld; rs == nullptr: rs = 1) by forward substitution in fp32:
-// x[r] = [r == c] - rs[r] sum_{s < r} M[r][s] x[s].  Right-looking: once x[s]
+// Column c of (I + M)^{-1} for a strictly lower 16 x 16 block M (row pitch ld) by
+// forward substitution in fp32: x[r] = [r == c] - sum_{s < r} M[r][s] x[s].  Right-looking: once x[s]
 // is final, every later row takes its term, so the 120 products form 16
 // dependent steps of independent updates instead of one chain.  Each row's sum
 // still runs over s in increasing order.
-__device__ __forceinline__ void gdn_diag_column(const float *M, int ld, int c, const float *rs, float (&x)[16]) {
+__device__ __forceinline__ void gdn_diag_column(const float *M, int ld, int c, float (&x)[16]) {
     float acc[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
     for (int s2 = 0; s2 < 16; ++s2) {
-        x[s2] = s2 == c ? 1.f : (s2 > c ? -(rs ? rs[s2] : 1.f) * acc[s2] : 0.f);
+        x[s2] = s2 == c ? 1.f : (s2 > c ? -acc[s2] : 0.f);
 #pragma unroll
         for (int r = s2 + 1; r < 16; ++r) acc[r] = fmaf(M[r * ld + s2], x[s2], acc[r]);
     }
 }
-// The same column, the same sums in the same order (so the same bits), row by
-// row for a kernel short of registers (ld a multiple of 4, M 16-byte aligned):
-// row r's part left of the diagonal is read with 16-byte loads that do not
-// depend on x, and the row scales are read up front, so the rows are selected
-// arithmetically (a load under the per-lane condition r > c made every row a
-// branch with its own wait).
-__device__ __forceinline__ void gdn_diag_column_rows(const float *M, int ld, int c, const float *rs, float (&x)[16]) {
-    float rv[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) rv[r] = rs ? rs[r] : 1.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        float acc = 0.f;
-#pragma unroll
-        for (int m = 0; 4 * m < r; ++m) {
-            const f32x4 mv = *reinterpret_cast<const f32x4 *>(M + r * ld + 4 * m);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (4 * m + u < r) acc = fmaf(mv[u], x[4 * m + u], acc);
-        }
-        const float y = -rv[r] * acc;
-        x[r] = r > c ? y : (r == c ? 1.f : 0.f);
-    }
-}
-
-// T = (I + A)^{-1} for the strictly lower 64 x 64 A = diag(rs) M with M in sA
-// (pitch C + 4; rs == nullptr: A = M), into sT (fp32, pitch C + 4, zero above
-// the diagonal), by 16 x 16 blocks: the four diagonal blocks by forward
-// substitution in fp32 (64 threads, one column each); then level by level
-// (i - j = 1, 2, 3) wave j forms T_ij = -T_ii sum_{k=j}^{i-1} A_ik T_kj on
-// 16x16x16 MFMA with hi/lo operands, the inner sum staying in its
-// accumulator, which is already the B operand of the T_ii product.  NT >= 256
-// threads (four waves); ends with a barrier.  (The per-chunk gradient kernel's
-// form; the walks use gdn_tinv_hl below.)
-template <int NT>
-__device__ __forceinline__ void gdn_tinv(int tid, const float *sA, float *sT, const float *rs = nullptr) {
-    constexpr int LA = C + 4, LT = C + 4;
-    if (tid < 64) {
-        const int o = 16 * (tid >> 4), c = tid & 15;
-        float x[16];
-        gdn_diag_column_rows(sA + o * LA + o, LA, c, rs ? rs + o : nullptr, x);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sT[(o + r) * LT + o + c] = x[r];
-    }
-    for (int e = tid; e < 6 * 256; e += NT) {  // blocks (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
-        const int b = e >> 8, rr = (e >> 4) & 15, cc = e & 15;
-        const int bi = b < 3 ? 0 : (b < 5 ? 1 : 2), bj = b < 3 ? b + 1 : (b < 5 ? b - 1 : 3);
-        sT[(16 * bi + rr) * LT + 16 * bj + cc] = 0.f;
-    }
-    __syncthreads();
-    const int w = tid >> 6, lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
-#pragma unroll
-    for (int d = 1; d < 4; ++d) {
-        if (w < 4 - d) {  // block (i, j) = (d + w, w)
-            const int i = d + w, j = w;
-            f32x4 y = {0.f, 0.f, 0.f, 0.f};
-            for (int k = j; k < i; ++k) {
-                f32x4 av = *reinterpret_cast<const f32x4 *>(&sA[(16 * i + n16) * LA + 16 * k + 4 * q4]);
-                if (rs) av *= rs[16 * i + n16];
-                f32x4 tb;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) tb[u] = sT[(16 * k + 4 * q4 + u) * LT + 16 * j + n16];
-                s4v ah, al, bh, bl;
-                split4(av, ah, al);
-                split4(tb, bh, bl);
-                mma16(y, ah, bh);
-                mma16(y, ah, bl);
-                mma16(y, al, bh);
-            }
-            const f32x4 tv = *reinterpret_cast<const f32x4 *>(&sT[(16 * i + n16) * LT + 16 * i + 4 * q4]);
-            s4v th, tl, yh, yl;
-            split4(tv, th, tl);
-            split4(y, yh, yl);
-            f32x4 t = {0.f, 0.f, 0.f, 0.f};
-            mma16(t, th, yh);
-            mma16(t, th, yl);
-            mma16(t, tl, yh);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sT[(16 * i + 4 * q4 + r) * LT + 16 * j + n16] = -t[r];
-        }
-        __syncthreads();
-    }
-}
-
 // The triangular 64 x 64 pair tiles of the walks (T, P, P^T as bf16 hi/lo) hold
 // the three 32 x 32 quadrants that are not all zero, each 64-byte rows with
 // their four 16-byte blocks XOR-swizzled by the row, hi then lo: 12 KB instead of
@@ -180,7 +95,9 @@ __device__ __forceinline__ int tri_pos(int r, int c) {
 // T = (I + A)^{-1} (A in sA, pitch C + 4) as the bf16 hi/lo pair that every
 // consumer splits it into (tri_pos<0>, raw 16-bit patterns): the four diagonal
 // blocks by forward substitution in fp32 (64 threads, one column each), the
-// off-diagonal blocks level by level as in gdn_tinv, reading the stored pairs.
+// off-diagonal blocks level by level (i - j = 1, 2, 3; wave j forms T_ij = -T_ii
+// sum_{k=j}^{i-1} A_ik T_kj on 16x16x16 MFMA, the inner sum staying in its
+// accumulator, which is already the B operand of the T_ii product).
 // (A diagonal block N is nilpotent, and (I + N)^{-1} = (I + N^8)(I + N^4)
 // (I + N^2)(I - N) on MFMA is faster; but the series' partial sums grow like
 // binomial coefficients when neighbouring keys are nearly parallel with little
@@ -193,7 +110,7 @@ __device__ __forceinline__ void gdn_tinv_hl(int tid, const float *sA, short *sTh
     if (tid < 64) {  // one column of a diagonal block per thread
         const int o = 16 * (tid >> 4), c = tid & 15;
         float x[16];
-        gdn_diag_column(sA + o * LA + o, LA, c, nullptr, x);
+        gdn_diag_column(sA + o * LA + o, LA, c, x);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const __bf16 h = (__bf16)x[r];
@@ -348,6 +265,16 @@ struct StateIO {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) S[m][i][r] = buf_ld<float>(rs, off, at(m, i, r));
     }
+    // transposed ([v][k]): a lane's four rows of a column are one 16-byte store
+    __device__ __forceinline__ static void store_t(const f32x4 (&S)[NCT][NK], float *dst, const GdnCols<D> &cl, int q4) {
+        const rsrc_t rs = buf_rsrc(dst, D * D * 4);
+        const uint32_t o = (uint32_t)(cl.col(0) * D + 8 * q4) * 4;
+#pragma unroll
+        for (int i = 0; i < NK; ++i)
+#pragma unroll
+            for (int m = 0; m < NCT; ++m)
+                buf_st(rs, o, (uint32_t)(4 * m * D + 32 * (i >> 1) + 4 * (i & 1)) * 4, S[m][i]);
+    }
     __device__ __forceinline__ void store(const f32x4 (&S)[NCT][NK], float *dst) const {
         const rsrc_t rs = buf_rsrc(dst, D * D * 4);
 #pragma unroll
@@ -390,9 +317,9 @@ struct TriTile {
 // of D bf16 unpadded, the 16-byte blocks of row r XOR-swizzled by f(r) = (r % 8) ^
 // 4 (r / 8 % 2) through the source addresses, so that fragment reads over 16 rows
 // (and the transposing ones over rows 8 apart) touch every bank once.
-template <typename T, int D>
+template <typename T, int D, int NW>
 struct DmaTile {
-    static constexpr int BPR = D / 8, RPI = 64 / BPR, NI = C / RPI / 4;  // blocks per row, rows per instruction
+    static constexpr int BPR = D / 8, RPI = 64 / BPR, NI = C / RPI / NW;  // blocks per row, rows per instruction
     uint32_t v0, v1;  // source offsets; v1 for the instructions whose rows flip f's bit 2
     __device__ __forceinline__ DmaTile(int lane, int64_t ld) {
         const int r = lane / BPR, b = (lane % BPR) ^ r;  // r < RPI <= 8: f(r) = r
@@ -403,7 +330,7 @@ struct DmaTile {
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             const int k = NI * w + i;
-            const bool flip = D == 128 ? (i ^ (i >> 1)) & 1 : i & 1;
+            const bool flip = (D == 128 ? k ^ (k >> 1) : k) & 1;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + 512 * k), 16,
                                                      flip ? v1 : v0, (int)(RPI * k * row_bytes), 0, 0);
         }
@@ -515,11 +442,11 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
 
     using TT = Tile<T, D, NT>;
     TT t2, t3;
-    const DmaTile<T, D> dq(lane, a.sx_l);
+    const DmaTile<T, D, 4> dq(lane, a.sx_l);
     const DmaTri dt(lane, a.sx_l);
     const uint32_t rowb = (uint32_t)(a.sx_l * (int64_t)sizeof(T));
     int qb[2];
-    DmaTile<T, D>::row_base(lane, qb);
+    DmaTile<T, D, 4>::row_base(lane, qb);
     TriTile<T> t4;
     float gl, bl;
     const int64_t cstep = (int64_t)C * a.sx_l;
@@ -546,7 +473,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     const unsigned par = pair_parity(a.n_cu);
     for (int c = 0; c < nch; ++c) {
         pair_turn(par);
-        if constexpr (MODE == W_STORE) sio.store(S, a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS);
+        if constexpr (MODE == W_STORE) sio.store_t(S, a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS, cl, q4);
         const float b2 = wave_scan_dpp(gl * LOG2E);
         const float b63 = lane_value(b2, 63);
         const float betal = bl;
@@ -963,7 +890,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
     for (int c = nch - 1; c >= 0; --c) {
         pair_turn(par);
         if constexpr (!PREP)  // dS' of chunk c: the gradient of the state leaving it
-            sio.store(dS, a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS);
+            sio.store_t(dS, a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS, cl, q4);
         const float b2 = wave_scan_dpp(gl * LOG2E);
         const float b63 = lane_value(b2, 63);
         const float betal = bl;
@@ -1235,516 +1162,544 @@ __global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
         if (!step(J, mA, nA) || !step(J - 1, mB, nB)) break;
 }
 
-// Parameter gradients of one chunk per item (b, h, chunk), items in a
-// grid-stride loop, one workgroup of 16 waves per CU.  S is the state entering
-// the chunk and dS' the gradient of the state leaving it (both stored per chunk
-// by the walks).  The value channels go in blocks of VB = 32 columns: each
-// block of S and dS' is read from memory once and staged in LDS, and every
-// contraction over the value channels accumulates in registers across the
-// blocks.  Two identities keep W = T diag(beta gamma) K and Ubar out of the
-// kernel (and out of memory):
-//   U_J = Ubar_J - W S_J = T diag(beta) (V_J - diag(gamma) K S_J),
+// Parameter gradients of one chunk per item (b, h, chunk), items in a grid-stride
+// loop, one workgroup of D / 16 waves per CU.  S is the state entering the chunk
+// and dS' the gradient of the state leaving it, both stored per chunk and
+// transposed ([v][k] fp32) by the walks.  Three identities keep W, Ubar and a
+// second inverse out of the kernel:
+//   U = T diag(beta) (V - diag(gamma) K S),   G_U = T^T dU,
 //   G_W = T^T (-dU S^T) = -G_U S^T,   dA = -(G_W W^T + G_U Ubar^T) = -G_U U^T.
-// Per block J, waves 0-7 (group A) and 8-15 (group B):
-//   A: Y = K S_J, R = diag(beta) (V_J - diag(gamma) Y), U_J = T R;
-//   B: dU_J = diag(e) K dS'_J + P^T dO_J, G_U,J = T^T dU_J (dv is the dS walk's);
-//   A: G_W -= G_U,J S_J^T, dK_S += U_J dS'_J^T;
-//   B: dQ_S += dO_J S_J^T, dA -= G_U,J U_J^T, dP += dO_J U_J^T.
-// After the blocks (Gamma[t][s] = e^{b_t - b_s}, Ah = dA o beta_t Gamma):
-//   dq = diag(gamma) dQ_S + (dP o Gamma) K                                (B)
-//   dk = diag(e) dK_S + (dP o Gamma)^T Q + diag(beta gamma) G_W + (Ah + Ah^T) K   (A)
-// and dbeta and the log-decay gradient from row and column sums in a fixed
-// order (no atomics).  q, k, v, dO enter the products exactly (bf16); the
-// computed fp32 operands (S, dS', T, P, R, U, dU, G_U, dP o Gamma, Ah) as
-// hi/lo bf16 pairs (three products, lo x lo dropped).
+// Wave w owns the 16 channels [16w, 16w + 16) throughout:
+//   1. of v: Y = K S, dU = e o (K dS') + P^T dO on its own columns of S and dS',
+//      which go from memory straight into its registers; U^T and G_U^T (rows v)
+//      leave their accumulators as four consecutive channels of a token, into LDS
+//      as hi/lo pairs;
+//   2. the causal 16 x 16 tiles of dA and dP = dO U^T, shared out over the waves,
+//      become E1 = dP o Gamma and E2 = Ah + Ah^T (Ah = dA o beta Gamma) in LDS;
+//   3. of k: dQ_S^T = S dO^T, G_W^T = -S G_U^T, dK_S^T = dS' U^T on its own rows
+//      of S and dS', again straight from memory (the second read finds most of
+//      both in L2);
+//   4. dq = gamma dQ_S + E1 K,  dk = e dK_S + E1^T Q + beta gamma G_W + E2 K, turned
+//      into whole rows through LDS.
+// Five barriers per item.  dbeta and the log-decay gradient come from row and
+// column sums in a fixed order (no atomics).  q, k, v, dO enter the products
+// exactly (bf16); the computed fp32 operands (S, dS', T, P, X, U, dU, G_U, E1, E2)
+// as hi/lo bf16 pairs (three products, lo x lo dropped).  The next item's q, k, T
+// wait in registers and its v, dO are copied into LDS during step 4.
+// D = 128, 65536 tokens of 40 heads: 7.6 ms with S and dS' staged through LDS in
+// blocks of 32 channels by 16 waves (16 barriers, and T formed again), XX ms so.
 template <typename T, int D>
-__global__ void __launch_bounds__(1024) k_gdn_dchunk(GdnArgs a) {
-    constexpr int NTH = 1024, VB = 32, NBLK = D / VB, NTW = D / 32;
-    constexpr int LDX = D + 8, LD6 = C + 4, LDB = VB + 4, LDV = VB + 8, LDOT = C + 8, LDU = VB + 4, LDR = VB + 1;
-    constexpr int NBLKF = 2 * D * LDB > 2 * C * LD6 ? 2 * D * LDB : 2 * C * LD6;
-    static_assert(2 * C * LDR <= C * LD6, "R and dU fit in the scores' buffer");
-    __shared__ __attribute__((aligned(16))) T xq[C * LDX], xk[C * LDX];
-    __shared__ __attribute__((aligned(16))) float sT[C * LD6];  // T = (I + A)^{-1}
-    __shared__ __attribute__((aligned(16))) float sP[C * LD6];  // P[t][s] = e^{b_t - b_s} q_t.k_s, s <= t
-    __shared__ __attribute__((aligned(16))) float sX[C * LD6];  // KK o Gamma (s < t) for the inverse; then R, dU
-    __shared__ __attribute__((aligned(16))) float sBlk[NBLKF];  // S_J, dS'_J; after the blocks dP o Gamma, Ah + Ah^T
-    __shared__ __attribute__((aligned(16))) T sV[C * LDV], sO[C * LDV], sOt[VB * LDOT];
-    __shared__ __attribute__((aligned(16))) float sU[C * LDU], sGU[C * LDU];
-    __shared__ float sb[C], sg[C], se[C], sbe[C];
-    __shared__ float sRow[6][2][C];  // row-sum partials, two waves per row tile
-    __shared__ float sCol[4][C];     // column-sum partials, one per row tile
-    __shared__ float sWav[16];
-
-    // S_J and dS'_J of the block as hi/lo bf16 pairs, split once when staged:
-    // [k'][v] tiles of VB = 32 channels (64-byte rows), the 16-byte channel blocks
-    // of row r XOR-swizzled by (r / 4) % 4
-    static_assert(VB == 32 && 4 * D * VB * (int)sizeof(T) <= NBLKF * 4, "block tiles fit sBlk");
-    T *const sSh = reinterpret_cast<T *>(sBlk), *const sSl = sSh + D * VB;
-    T *const sDh = sSl + D * VB, *const sDl = sDh + D * VB;
-    auto bpos = [](int r, int ch) { return r * VB + ((((ch >> 3) ^ (r >> 2)) & 3) << 3) + (ch & 7); };
-    // T, once formed, as a hi/lo pair of C x C bf16 tiles in its own bytes (128-byte
-    // rows, the 16-byte blocks of row r XOR-swizzled by r % 8)
-    static_assert(2 * C * C * (int)sizeof(T) <= C * LD6 * 4, "T's pair fits its fp32 bytes");
-    T *const sTh = reinterpret_cast<T *>(sT), *const sTl = sTh + C * C;
-    auto tpos = [](int r, int c) { return r * C + ((((c >> 3) ^ r) & 7) << 3) + (c & 7); };
-    float *const sE1 = sBlk, *const sE2 = sBlk + C * LD6;      // dP o Gamma, Ah + Ah^T
-    float *const sR = sX, *const sdU = sX + C * LDR;           // [t][v] of the block
+__global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
+    constexpr int NW = D / 16, NT = 4 * D, KS = D / 32, BPR = D / 8;
+    constexpr bool TPRE = D == 128;
+    constexpr int XT = C * D;          // elements of a chunk tile
+    // tiles in DmaTile's layout; G_U's hi half takes v's place (a lane overwrites
+    // the values that it alone has read)
+    __shared__ __attribute__((aligned(16))) T sQ[XT], sK[XT], sO[XT], sUh[XT], sUl[XT], sGh[XT], sGl[XT];
+    // T then E1 (tri, 12 KB), P^T then part of E2 (full C x C pair)
+    __shared__ __attribute__((aligned(16))) short sR[2 * TRI + 2 * C * C];
+    __shared__ __attribute__((aligned(16))) float sb[C], sg[C], se[C], sbe[C];
+    __shared__ float sGv[NW][C], sZ[NW][C], sW[NW][C], sY[NW][C];  // per wave: G_U.v, G_W.k, dK_S.k, gamma q.dQ_S
+    __shared__ float sRX[4][C], sXr[2][4][C], sXc[2][4][C];        // per tile column / row: see the sums below
+    __shared__ float sWav[NW];
+    __shared__ __attribute__((aligned(16))) float sA[TPRE ? 4 : C * (C + 4)];
+    T *const sV = sGh;
+    short *const sT = sR;
+    T *const sP = reinterpret_cast<T *>(sR + 2 * TRI);
+    T *const sE1 = reinterpret_cast<T *>(sR), *const sE2 = reinterpret_cast<T *>(sR + 2 * TRI);
 
     const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
-    const bool grpB = w >= 8;
-    const int wg = w & 7, mt = wg & 3, half = wg >> 2;  // row tile; which half of the column tiles
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t SS = (int64_t)D * D;
     const int nc = (int)(a.L / C);
     const int64_t items = (int64_t)a.B * a.H * nc;
 
-    // fragments: rows row0 + n16, contraction k0 + 8 q4 + j (j < 8)
-    auto x_rm = [&](const T *M, int ld, int row0, int k0) {  // exact, M[row][k]
-        return *reinterpret_cast<const frag_t<T> *>(M + (row0 + n16) * ld + k0 + 8 * q4);
+    // --- positions (see DmaTile for the swizzle)
+    auto xpos = [](int r, int c) { return r * D + (((c >> 3) ^ (r & 7) ^ (((r >> 3) & 1) << 2)) << 3) + (c & 7); };
+    auto epos = [](int r, int c) { return r * C + (((c >> 3) ^ (r & 7)) << 3) + (c & 7); };  // E2
+    auto roff = [](int i) { return 32 * (i >> 1) + 4 * (i & 1); };
+    auto prow = [&](int i, int r) { return 32 * (i >> 1) + 8 * q4 + 4 * (i & 1) + r; };
+    // The lane's positions, and the lane index itself, opaque to the compiler: it
+    // would otherwise form every LDS address ahead of the item loop and keep them
+    // all (180 registers spilled).
+    int rb[2], kb[2], tb[2], ub[2], eb[2], ar, own, trb, tra, xb;
+    auto positions = [&]() {
+        asm volatile("" : "+v"(lane));
+        q4 = lane >> 4;
+        n16 = lane & 15;
+        DmaTile<T, D, NW>::row_base(lane, rb);  // rows 16 tt + n16: rb[ks & 1] + 16 tt D + 64 (ks >> 1)
+        ar = 8 * (n16 >> 2) + (n16 & 3);        // rows ar + roff(tt): kb[(ks ^ tt) & 1] + roff(tt) D + 64 (ks >> 1)
+        kb[0] = ar * D + 8 * ((q4 ^ (n16 & 3)) | (4 * ((n16 >> 2) & 1)));
+        kb[1] = ar * D + 8 * ((q4 ^ (n16 & 3)) | (4 * (1 ^ ((n16 >> 2) & 1))));
+        const int r0 = 8 * q4 + (n16 >> 2), ch = 4 * (n16 & 3);
+        tb[0] = xpos(r0, 16 * w + ch);  // transposing reads of the wave's own channels: tb[0] + 32 ks D, tb[1] four rows on
+        tb[1] = xpos(r0 + 4, 16 * w + ch);
+        ub[0] = tri_pos<0>(r0, ch);     // ... of a triangular tile's columns 16 i ..: ub[i & 1] + (ks + i / 2) 1024
+        ub[1] = tri_pos<0>(r0, 16 + ch);
+        trb = tri_pos<0>(n16, 8 * q4);  // its rows 16 tt + n16: trb + tri_b; rows ar + roff(tt): tra + tri_a
+        tra = tri_pos<0>(ar, 8 * q4);
+        eb[0] = epos(n16, 8 * q4);      // E2: rows 16 tt + n16, columns 32 ks + 8 q4 ..: eb[ks] + 16 tt C
+        eb[1] = epos(n16, 32 + 8 * q4);
+        own = 16 * w + 4 * q4;          // accumulator rows: channels own + r
+        xb = xpos(n16, own);            // token 16 tt + n16, channels own ..: xb + 16 tt D
     };
-    auto x_tr = [&](const T *M, int ld, int row0, int k0) {  // exact, M[k][row]
-        frag_t<T> f = {};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = M[(k0 + 8 * q4 + j) * ld + row0 + n16];
-        return f;
-    };
-    auto f_rm = [&](const float *M, int ld, int row0, int k0, frag_t<T> &h, frag_t<T> &l) {  // M[row][k], split
-        const float *p = M + (row0 + n16) * ld + k0 + 8 * q4;
-        const f32x4 x0 = *reinterpret_cast<const f32x4 *>(p), x1 = *reinterpret_cast<const f32x4 *>(p + 4);
-        const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-        split8<T, true>(x, h, l);
-    };
-    auto f_tr = [&](const float *M, int ld, int row0, int k0, frag_t<T> &h, frag_t<T> &l) {  // M[k][row], split
-        float x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = M[(k0 + 8 * q4 + j) * ld + row0 + n16];
-        split8<T, true>(x, h, l);
-    };
-    // from a block tile [k'][v] (bpos layout): rows row0 + n16 over channels
-    // 8 q4 .. +7 (b_rm), or rows = channels c0 + n16 over k0 + 8 q4 + j through
-    // two transposing reads (b_tr; the lane map of ldfragTR)
-    auto b_rm = [&](const T *M, int row0) {
-        return *reinterpret_cast<const frag_t<T> *>(M + bpos(row0 + n16, 8 * q4));
-    };
-    auto b_tr = [&](const T *M, int k0, int c0) {
-        typedef short s4 __attribute__((ext_vector_type(4)));
+    positions();
+    auto rd = [](const T *M, int p) { return *reinterpret_cast<const frag_t<T> *>(M + p); };
+    auto rows = [&](const T *M, int tt, int ks) { return rd(M, rb[ks & 1] + 16 * tt * D + 64 * (ks >> 1)); };
+    auto tr2 = [](const void *p0, const void *p1) {
         typedef short s8 __attribute__((ext_vector_type(8)));
-        const int ch = c0 + 4 * (lane & 3), r0 = k0 + 8 * q4 + ((lane & 15) >> 2);
-        const s4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)(M + bpos(r0, ch)));
-        const s4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)(M + bpos(r0 + 4, ch)));
+        const s4v x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)p0);
+        const s4v x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)p1);
         const s8 v = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(frag_t<T>, v);
     };
-    // the same two forms from T's tiles (tpos layout)
-    auto t_rm = [&](const T *M, int row0, int k0) {
-        return *reinterpret_cast<const frag_t<T> *>(M + tpos(row0 + n16, k0 + 8 * q4));
+    auto cols = [&](const T *M, int ks) { return tr2(M + tb[0] + 32 * ks * D, M + tb[1] + 32 * ks * D); };
+    auto tri_tr = [&](const short *M, int ks, int i) {  // rows 16 i + n16 of M^T, contraction 32 ks + 8 q4 + j
+        const short *p = M + ub[i & 1] + (ks + (i >> 1)) * 1024;
+        return tr2(p, p + 4 * 32);
     };
-    auto t_tr = [&](const T *M, int k0, int c0) {
-        typedef short s4 __attribute__((ext_vector_type(4)));
-        typedef short s8 __attribute__((ext_vector_type(8)));
-        const int ch = c0 + 4 * (lane & 3), r0 = k0 + 8 * q4 + ((lane & 15) >> 2);
-        const s4 x0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)(M + tpos(r0, ch)));
-        const s4 x1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4 *)(M + tpos(r0 + 4, ch)));
-        const s8 v = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_bit_cast(frag_t<T>, v);
+    auto tri_rows = [&](const short *M, int tt, int ks) {  // rows 16 tt + n16, columns 32 ks + 8 q4 ..
+        return rd(reinterpret_cast<const T *>(M), trb + tri_b(tt, ks));
     };
     auto mma3 = [](f32x4 &c, const frag_t<T> &ah, const frag_t<T> &al, const frag_t<T> &bh, const frag_t<T> &bl) {
         mma(c, ah, bh);
         mma(c, ah, bl);
         mma(c, al, bh);
     };
-    auto rowsum16 = [](float v) {  // sum over the 16 lanes of a row group
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
+    auto sum16 = [](float v) {  // over the 16 lanes of a row, in every lane
+        v += dpp_or0<0x128>(v);
+        v += dpp_or0<0x124>(v);
+        v += dpp_or0<0x122>(v);
+        v += dpp_or0<0x121>(v);
         return v;
     };
+    // four values of four consecutive channels / columns as a hi/lo pair
+    auto put4 = [](T *h, T *l, int p, const f32x4 &x) {
+        const float v[4] = {x[0], x[1], x[2], x[3]};
+        st4_split<T, true>(h + p, l + p, v);
+    };
     const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        // the lane index, opaque per item: the many per-lane LDS addresses are
-        // recomputed where they are used instead of being hoisted out of the
-        // item loop (where they would not fit the 128 registers of 16 waves)
-        asm volatile("" : "+v"(lane));
-        q4 = lane >> 4;
-        n16 = lane & 15;
-        const int bh = (int)(it / nc), ch = (int)(it % nc), bb = bh / a.H, hh = bh % a.H;
-        const int64_t xo0 = bb * a.sx_b + hh * a.sx_h + (int64_t)ch * C * a.sx_l;
-        const int64_t go0 = bb * a.sg_b + hh * a.sg_h + (int64_t)ch * C * a.sg_l;
-        const float *Sg = a.wsSc + ((int64_t)bh * nc + ch) * SS;
-        const float *dSg = a.wsDc + ((int64_t)bh * nc + ch) * SS;
-        const T *Vg = (const T *)a.v + xo0, *Og = (const T *)a.dO + xo0;
-
-        // block staging: S_J and dS'_J as D x VB floats (one 16-byte unit of
-        // each per thread), V_J and dO_J as C x VB bf16 (threads 0-255 and 256-511)
-        constexpr int NSU = D * VB / 4;
-        int tidv = tid;
-        asm volatile("" : "+v"(tidv));
-        const int su_r = tidv / (VB / 4), su_c = 4 * (tidv % (VB / 4));
-        const int vu = tidv & 255, vu_t = vu / (VB / 8), vu_c = 8 * (vu % (VB / 8));
-        f32x4 pS = z4, pD = z4;
-        frag_t<T> pX = {};
-        auto fetch = [&](int jb) {
-            const int v0 = jb * VB;
-            if (tid < NSU) {
-                pS = *reinterpret_cast<const f32x4 *>(Sg + (int64_t)su_r * D + v0 + su_c);
-                pD = *reinterpret_cast<const f32x4 *>(dSg + (int64_t)su_r * D + v0 + su_c);
-            }
-            if (tid < 512) {
-                const T *src = (tid < 256 ? Vg : Og) + (int64_t)vu_t * a.sx_l + v0 + vu_c;
-                pX = *reinterpret_cast<const frag_t<T> *>(src);
-            }
-        };
-        float sd = 0.f;  // <dS', S> over this thread's units
-        auto stage = [&]() {
-            if (tid < NSU) {
-                typedef T t4 __attribute__((ext_vector_type(4)));
-                t4 sh = {}, sl = {}, dh = {}, dl = {};
+    // --- loads of an item
+    typedef s4v2 blk;
+    const DmaTile<T, D, NW> dma(lane, a.sx_l);
+    const uint32_t rowb = (uint32_t)(a.sx_l * (int64_t)sizeof(T)), span = chunk_span<T, D>(a.sx_l);
+    const uint32_t xoff = (uint32_t)((tid / BPR) * (uint64_t)rowb + 16 * (tid % BPR));  // block tid of a tile
+    const int sp = xpos(tid / BPR, 8 * (tid % BPR));
+    const uint32_t toff = (uint32_t)((tid >> 4) * (uint64_t)rowb + 16 * (tid & 15));
+    blk pq[2], pk[2], pt[2];
+    float gl, bl;
+    f32x4 s1[2 * KS], d1[2 * KS];  // S, dS' of the wave's own v: [own v][32 ks + 8 q4 + 4 h ..]
+    auto xo_of = [&](int64_t it) {
+        const int bh = (int)(it / nc), ch = (int)(it % nc);
+        return (int64_t)(bh / a.H) * a.sx_b + (int64_t)(bh % a.H) * a.sx_h + (int64_t)ch * C * a.sx_l;
+    };
+    auto go_of = [&](int64_t it) {
+        const int bh = (int)(it / nc), ch = (int)(it % nc);
+        return (int64_t)(bh / a.H) * a.sg_b + (int64_t)(bh % a.H) * a.sg_h + (int64_t)ch * C * a.sg_l;
+    };
+    constexpr uint32_t RS = NT / BPR, RT = NT / 16;  // rows per round of blocks: tiles, T
+    auto load_regs = [&](int64_t it) {
+        const int64_t xo = xo_of(it), go = go_of(it);
+        const rsrc_t rq = buf_rsrc((const T *)a.q + xo, span), rk = buf_rsrc((const T *)a.k + xo, span);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    sh[j] = cvt<T>(pS[j]);
-                    sl[j] = cvt<T>(pS[j] - tof<T>(sh[j]));
-                    dh[j] = cvt<T>(pD[j]);
-                    dl[j] = cvt<T>(pD[j] - tof<T>(dh[j]));
-                }
-                const int pb = bpos(su_r, su_c);
-                *reinterpret_cast<t4 *>(&sSh[pb]) = sh;
-                *reinterpret_cast<t4 *>(&sSl[pb]) = sl;
-                *reinterpret_cast<t4 *>(&sDh[pb]) = dh;
-                *reinterpret_cast<t4 *>(&sDl[pb]) = dl;
-                sd = fmaf(pS[0], pD[0], fmaf(pS[1], pD[1], fmaf(pS[2], pD[2], fmaf(pS[3], pD[3], sd))));
-            }
-            if (tid < 256) {
-                *reinterpret_cast<frag_t<T> *>(&sV[vu_t * LDV + vu_c]) = pX;
-            } else if (tid < 512) {
-                *reinterpret_cast<frag_t<T> *>(&sO[vu_t * LDV + vu_c]) = pX;
+        for (int i = 0; i < 2; ++i) {
+            pq[i] = buf_ld<blk>(rq, xoff, i * RS * rowb);
+            pk[i] = buf_ld<blk>(rk, xoff, i * RS * rowb);
+        }
+        if constexpr (TPRE) {
+            const rsrc_t rt = buf_rsrc((const T *)a.tw + xo, span);
+            if ((tid & 7) < 4) pt[0] = buf_ld<blk>(rt, toff, 0);
+            pt[1] = buf_ld<blk>(rt, toff, RT * rowb);
+        }
+        const uint32_t gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4), goff = (uint32_t)(lane * a.sg_l * 4);
+        gl = buf_ld<float>(buf_rsrc(a.g + go, gspan), goff, 0);
+        bl = buf_ld<float>(buf_rsrc(a.beta + go, gspan), goff, 0);
+    };
+    auto load_vo = [&](int64_t it) {
+        const int64_t xo = xo_of(it);
+        dma.issue(buf_rsrc((const T *)a.v + xo, span), sV, w, rowb);
+        dma.issue(buf_rsrc((const T *)a.dO + xo, span), sO, w, rowb);
+    };
+    auto load_s1 = [&](int64_t it) {
+        const rsrc_t rs = buf_rsrc(a.wsSc + it * SS, (uint32_t)(SS * 4)), rd = buf_rsrc(a.wsDc + it * SS, (uint32_t)(SS * 4));
+        const uint32_t o = (uint32_t)(((16 * w + n16) * D + 8 * q4) * 4);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) sOt[(vu_c + j) * LDOT + vu_t] = pX[j];
-            }
-        };
+        for (int j = 0; j < 2 * KS; ++j) {
+            s1[j] = buf_ld<f32x4>(rs, o, 128 * (j >> 1) + 16 * (j & 1));
+            d1[j] = buf_ld<f32x4>(rd, o, 128 * (j >> 1) + 16 * (j & 1));
+        }
+    };
 
-        __syncthreads();  // the previous item is done with LDS
-        for (int e = tid; e < C * D / 8; e += NTH) {
-            const int t = e / (D / 8), c8 = 8 * (e % (D / 8));
-            const int64_t off = xo0 + (int64_t)t * a.sx_l + c8;
-            *reinterpret_cast<frag_t<T> *>(&xq[t * LDX + c8]) = *reinterpret_cast<const frag_t<T> *>((const T *)a.q + off);
-            *reinterpret_cast<frag_t<T> *>(&xk[t * LDX + c8]) = *reinterpret_cast<const frag_t<T> *>((const T *)a.k + off);
+    int64_t it = blockIdx.x;
+    if (it >= items) return;
+    load_regs(it);
+    load_vo(it);
+    load_s1(it);
+    for (; it < items; it += gridDim.x) {
+        const int64_t nx = it + gridDim.x;
+        positions();
+        // --- stage
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int p = sp + i * RS * D;  // (RS a multiple of 16: the swizzle repeats)
+            *reinterpret_cast<blk *>(sQ + p) = pq[i];
+            *reinterpret_cast<blk *>(sK + p) = pk[i];
         }
-        fetch(0);
-        if (tid < 64) {
-            const float b = wave_scan_dpp(a.g[go0 + (int64_t)tid * a.sg_l]);
-            const float bC = lane_value(b, 63);
-            sb[tid] = b;
-            sg[tid] = expf(b);
-            se[tid] = expf(bC - b);
-            sbe[tid] = a.beta[go0 + (int64_t)tid * a.sg_l];
+        if constexpr (TPRE) {
+            const int j = tid & 15, c8 = 8 * (j & 7);
+            short *const t = sT + (j < 8 ? 0 : TRI);
+            if ((tid & 7) < 4) *reinterpret_cast<blk *>(t + tri_pos<0>(tid >> 4, c8)) = pt[0];
+            *reinterpret_cast<blk *>(t + tri_pos<0>(32 + (tid >> 4), c8)) = pt[1];
         }
+        if (w == 0) {
+            const float b2 = wave_scan_dpp(gl * LOG2E);
+            const float b63 = lane_value(b2, 63);
+            sb[lane] = b2;
+            sg[lane] = fexp2(b2);
+            se[lane] = fexp2(b63 - b2);
+            sbe[lane] = bl;
+        }
+        vm_wait_all();  // this wave's part of v and dO is in LDS
         __syncthreads();
 
-        // scores: wave w forms tile (w % 4, w / 4) of K K^T and of Q K^T
-        {
-            const int st = w >> 2;
-            f32x4 pk = z4, pq = z4;
-#pragma unroll 1
-            for (int kk = 0; kk < D; kk += 32) {
-                const frag_t<T> bk = x_rm(xk, LDX, 16 * st, kk);
-                mma(pk, x_rm(xk, LDX, 16 * mt, kk), bk);
-                mma(pq, x_rm(xq, LDX, 16 * mt, kk), bk);
+        // --- P^T on the causal tiles (as in the dS walk)
+        for (int i = w; i < 10; i += NW) {
+            int tt, st;
+            tri_tile(i, tt, st);
+            f32x4 p = z4;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) mma(p, rows(sQ, tt, ks), rows(sK, st, ks));
+            const int s = 16 * st + n16;
+            const float bs = sb[s];
+            const f32x4 bt = *reinterpret_cast<const f32x4 *>(&sb[16 * tt + 4 * q4]);
+            f32x4 v = z4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = s <= 16 * tt + 4 * q4 + r ? p[r] * fexp2(bt[r] - bs) : 0.f;
+            put4(sP, sP + TRI, tri_pos<0>(s, 16 * tt + 4 * q4), v);
+        }
+        if (tid < 128) {
+            const int b = tid >> 6, o = tri_pos<0>(32 * b + 16 + ((tid >> 2) & 15), 32 * b + 4 * (tid & 3));
+            *reinterpret_cast<s4v *>(&sP[o]) = s4v{0, 0, 0, 0};
+            *reinterpret_cast<s4v *>(&sP[TRI + o]) = s4v{0, 0, 0, 0};
+        }
+        if constexpr (!TPRE) {  // T formed here
+            for (int i = w; i < 10; i += NW) {
+                int tt, st;
+                tri_tile(i, tt, st);
+                f32x4 p = z4;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) mma(p, rows(sK, st, ks), rows(sK, tt, ks));
+                const int t = 16 * tt + n16;
+                const float bt = sb[t], be = sbe[t];
+                const f32x4 bs = *reinterpret_cast<const f32x4 *>(&sb[16 * st + 4 * q4]);
+                f32x4 v = z4;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = 16 * st + 4 * q4 + r < t ? be * p[r] * fexp2(bt - bs[r]) : 0.f;
+                *reinterpret_cast<f32x4 *>(&sA[t * (C + 4) + 16 * st + 4 * q4]) = v;
             }
+            __syncthreads();
+            gdn_tinv_hl(tid, sA, sT, sT + TRI);
+        }
+
+        positions();
+        // --- 1. Y = K S, dU = e o (K dS') on the wave's own v (rows t = prow(tt, r))
+        f32x4 x[4], du[4];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) x[tt] = du[tt] = z4;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            frag_t<T> sh, sl, dh, dl;
+            split_acc<T, true>(s1[2 * ks], s1[2 * ks + 1], sh, sl);
+            split_acc<T, true>(d1[2 * ks], d1[2 * ks + 1], dh, dl);
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                const frag_t<T> kf = rd(sK, kb[(ks ^ tt) & 1] + roff(tt) * D + 64 * (ks >> 1));
+                mma(x[tt], kf, sh);
+                mma(x[tt], kf, sl);
+                mma(du[tt], kf, dh);
+                mma(du[tt], kf, dl);
+            }
+            sched_fence();
+        }
+        // S and dS' again, the wave's own k as rows: s2[kv][j] = S[k'][32 kv + 8 q4 + j]
+        float s2[8 * KS], d2[8 * KS];
+        {
+            const rsrc_t rs = buf_rsrc(a.wsSc + it * SS, (uint32_t)(SS * 4)), rdd = buf_rsrc(a.wsDc + it * SS, (uint32_t)(SS * 4));
+            const uint32_t o = (uint32_t)((8 * q4 * D + 16 * w + n16) * 4);
+#pragma unroll
+            for (int j = 0; j < 8 * KS; ++j) {
+                s2[j] = buf_ld<float>(rs, o, (uint32_t)((32 * (j >> 3) + (j & 7)) * D * 4));
+                d2[j] = buf_ld<float>(rdd, o, (uint32_t)((32 * (j >> 3) + (j & 7)) * D * 4));
+            }
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            x[tt] *= -*reinterpret_cast<const f32x4 *>(&sg[prow(tt, 0)]);
+            du[tt] *= *reinterpret_cast<const f32x4 *>(&se[prow(tt, 0)]);
+        }
+        frag_t<T> eye[2];  // as in the forward walk
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) eye[h][j] = (T)(q4 == (n16 >> 2) && j == 4 * h + (n16 & 3) ? 1.f : 0.f);
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {  // X = V - gamma Y
+            const frag_t<T> vf = cols(sV, ks);
+            mma(x[2 * ks], eye[0], vf);
+            mma(x[2 * ks + 1], eye[1], vf);
+        }
+        sched_fence();
+        // U^T[v][t] = sum_s (beta X)^T[v][s] T[t][s]: rows v = own + r, columns t = 16 tt + n16
+        f32x4 ut[4];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            x[tt] *= *reinterpret_cast<const f32x4 *>(&sbe[prow(tt, 0)]);
+            ut[tt] = z4;
+        }
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            frag_t<T> xh, xl;
+            split_acc<T, true>(x[2 * ks], x[2 * ks + 1], xh, xl);
+#pragma unroll
+            for (int tt = 2 * ks; tt < 4; ++tt) mma3(ut[tt], xh, xl, tri_rows(sT, tt, ks), tri_rows(sT + TRI, tt, ks));
+        }
+        __syncthreads();  // P^T is complete
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) put4(sUh, sUl, xb + 16 * tt * D, ut[tt]);
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            const frag_t<T> of = cols(sO, ks);
+#pragma unroll
+            for (int tt = 0; tt < 2 * ks + 2; ++tt) {
+                const int o = tra + tri_a(tt, ks);
+                mma(du[tt], rd(sP, o), of);
+                mma(du[tt], rd(sP, TRI + o), of);
+            }
+        }
+        sched_fence();
+        positions();
+        // G_U^T[v][s] = sum_t dU^T[v][t] T[t][s]; v.G_U per token; G_U over v's place
+        f32x4 gt[4];
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) gt[tt] = z4;
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            frag_t<T> uh, ul;
+            split_acc<T, true>(du[2 * ks], du[2 * ks + 1], uh, ul);
+#pragma unroll
+            for (int tt = 0; tt < 2 * ks + 2; ++tt) mma3(gt[tt], uh, ul, tri_tr(sT, ks, tt), tri_tr(sT + TRI, ks, tt));
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const int p = xb + 16 * tt * D;
+            const f32x4 vv = ld4f(sV + p);
+            const float gv = sum_rows(gt[tt][0] * vv[0] + gt[tt][1] * vv[1] + gt[tt][2] * vv[2] + gt[tt][3] * vv[3]);
+            if (q4 == 0) sGv[w][16 * tt + n16] = gv;
+            put4(sGh, sGl, p, gt[tt]);
+        }
+        __syncthreads();
+        positions();
+        if (nx < items) load_regs(nx);
+
+        // --- 2. dA, dP on the causal tiles: rows s = 16 st + 4 q4 + r, column t = 16 tt + n16
+        auto tile = [&](int i, bool doA, bool doP) {
+            int tt, st;
+            tri_tile(i, tt, st);
+            f32x4 da = z4, dp = z4, kk = z4, qk = z4;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const frag_t<T> uh = rows(sUh, st, ks), ul = rows(sUl, st, ks), ks4 = rows(sK, st, ks);
+                if (doA) {
+                    mma3(da, uh, ul, rows(sGh, tt, ks), rows(sGl, tt, ks));
+                    mma(kk, ks4, rows(sK, tt, ks));
+                }
+                if (doP) {
+                    const frag_t<T> of = rows(sO, tt, ks);
+                    mma(dp, uh, of);
+                    mma(dp, ul, of);
+                    mma(qk, ks4, rows(sQ, tt, ks));
+                }
+                sched_fence();
+            }
+            const int t = 16 * tt + n16, s0 = 16 * st + 4 * q4;
+            const float bt = sb[t], be = sbe[t];
+            const f32x4 bs = *reinterpret_cast<const f32x4 *>(&sb[s0]);
+            f32x4 ah = z4, e1 = z4, exA = z4, exP = z4;
+            float rx = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int t = 16 * mt + 4 * q4 + r, s2 = 16 * st + n16;
-                const float ga = expf(sb[t] - sb[s2]);
-                sX[t * LD6 + s2] = s2 < t ? ga * pk[r] : 0.f;
-                sP[t * LD6 + s2] = s2 <= t ? ga * pq[r] : 0.f;
+                const float ga = s0 + r <= t ? fexp2(bt - bs[r]) : 0.f;
+                const float dav = s0 + r < t ? -da[r] : 0.f, dpv = s0 + r <= t ? dp[r] : 0.f;
+                rx = fmaf(dav, ga * kk[r], rx);  // sum_s dA KK o Gamma (dbeta)
+                ah[r] = dav * be * ga;
+                e1[r] = dpv * ga;
+                exA[r] = ah[r] * kk[r];  // dA o A
+                exP[r] = e1[r] * qk[r];  // dP o P
             }
-        }
-        __syncthreads();
-        gdn_tinv<NTH>(tid, sX, sT, sbe);  // T = (I + diag(beta) KK o Gamma)^{-1}; ends with a barrier
-        {  // T -> its hi/lo pair, split once for every wave that reads it
-            static_assert(4 * NTH == C * C, "four elements of T per thread");
-            typedef T t4 __attribute__((ext_vector_type(4)));
-            const int r = (4 * tid) / C, c = (4 * tid) % C;
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(&sT[r * LD6 + c]);
-            t4 h = {}, l = {};
+            if (doA) {
+                put4(sE2, sE2 + C * C, epos(t, s0), ah);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[j] = cvt<T>(x[j]);
-                l[j] = cvt<T>(x[j] - tof<T>(h[j]));
-            }
-            __syncthreads();  // every fp32 read of T is done
-            *reinterpret_cast<t4 *>(&sTh[tpos(r, c)]) = h;
-            *reinterpret_cast<t4 *>(&sTl[tpos(r, c)]) = l;
-        }
-
-        // one accumulator array, overlaid by role (both roles run the same code,
-        // so separate arrays would all stay live on every wave):
-        //   A: G_W = acc[0, NTW), dK_S = acc[NTW, 2 NTW)
-        //   B: dQ_S = acc[0, NTW), dA = acc[NTW, NTW + 2), dP = acc[NTW + 2, NTW + 4)
-        constexpr int NACC = 2 * NTW > NTW + 4 ? 2 * NTW : NTW + 4;
-        f32x4 acc[NACC];
-#pragma unroll
-        for (int j = 0; j < NACC; ++j) acc[j] = z4;
-        f32x4 *const accA = acc, *const accB = acc + NTW, *const dA2 = acc + NTW, *const dP2 = acc + NTW + 2;
-        float rGUv[4] = {0.f, 0.f, 0.f, 0.f};  // B: sum_v G_U v over the blocks
-
-        for (int jb = 0; jb < NBLK; ++jb) {
-            const int nb = half;  // the wave's 16 columns of the block
-            asm volatile("" : "+v"(lane));      // (as at the top of the item loop)
-            q4 = lane >> 4;
-            n16 = lane & 15;
-            if (jb > 0) __syncthreads();     // every read of the previous block is done
-            stage();
-            if (jb + 1 < NBLK) fetch(jb + 1);
-            __syncthreads();
-            if (!grpB) {  // Y = K S_J;  R = beta (V_J - gamma Y)
-                f32x4 y = z4;
-#pragma unroll 1
-                for (int kk = 0; kk < D; kk += 32) {
-                    const frag_t<T> bh = b_tr(sSh, kk, 16 * nb), bl = b_tr(sSl, kk, 16 * nb);  // B[v][k'] = S_J[k'][v]
-                    const frag_t<T> ak = x_rm(xk, LDX, 16 * mt, kk);
-                    mma(y, ak, bh);
-                    mma(y, ak, bl);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = 16 * mt + 4 * q4 + r, v = 16 * nb + n16;
-                    sR[t * LDR + v] = sbe[t] * (tof<T>(sV[t * LDV + v]) - sg[t] * y[r]);
-                }
-            } else {  // dU_J = e o K dS'_J + P^T dO_J
-                f32x4 u = z4;
-#pragma unroll 1
-                for (int kk = 0; kk < D; kk += 32) {
-                    const frag_t<T> bh = b_tr(sDh, kk, 16 * nb), bl = b_tr(sDl, kk, 16 * nb);  // B[v][k'] = dS'_J[k'][v]
-                    const frag_t<T> ak = x_rm(xk, LDX, 16 * mt, kk);
-                    mma(u, ak, bh);
-                    mma(u, ak, bl);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) u[r] *= se[16 * mt + 4 * q4 + r];
-#pragma unroll 1
-                for (int kk = 0; kk < C; kk += 32) {
-                    frag_t<T> ph, pl;
-                    f_tr(sP, LD6, 16 * mt, kk, ph, pl);                 // A[t][s] = P[s][t]
-                    const frag_t<T> bo = x_rm(sOt, LDOT, 16 * nb, kk);  // B[v][s] = dO_J[s][v]
-                    mma(u, ph, bo);
-                    mma(u, pl, bo);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sdU[(16 * mt + 4 * q4 + r) * LDR + 16 * nb + n16] = u[r];
-            }
-            __syncthreads();
-            if (!grpB) {  // U_J = T R
-                f32x4 u = z4;
-#pragma unroll 1
-                for (int kk = 0; kk < C; kk += 32) {
-                    frag_t<T> th, tl, rh, rl;
-                    th = t_rm(sTh, 16 * mt, kk);
-                    tl = t_rm(sTl, 16 * mt, kk);
-                    f_tr(sR, LDR, 16 * nb, kk, rh, rl);  // B[v][s] = R[s][v]
-                    mma3(u, th, tl, rh, rl);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sU[(16 * mt + 4 * q4 + r) * LDU + 16 * nb + n16] = u[r];
-            } else {  // G_U,J = T^T dU_J
-                f32x4 gu = z4;
-#pragma unroll 1
-                for (int kk = 0; kk < C; kk += 32) {
-                    frag_t<T> th, tl, dh, dl;
-                    th = t_tr(sTh, kk, 16 * mt);  // A[t][s] = T[s][t]
-                    tl = t_tr(sTl, kk, 16 * mt);
-                    f_tr(sdU, LDR, 16 * nb, kk, dh, dl);  // B[v][s] = dU[s][v]
-                    mma3(gu, th, tl, dh, dl);
-                }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = 16 * mt + 4 * q4 + r, v = 16 * nb + n16;
-                    sGU[t * LDU + v] = gu[r];
-                    rGUv[r] = fmaf(gu[r], tof<T>(sV[t * LDV + v]), rGUv[r]);
-                }
-            }
-            __syncthreads();
-            if (!grpB) {  // G_W -= G_U,J S_J^T;  dK_S += U_J dS'_J^T  (contraction over the block's 32 v)
-                frag_t<T> gh, gl, uh, ul;
-                f_rm(sGU, LDU, 16 * mt, 0, gh, gl);
-                f_rm(sU, LDU, 16 * mt, 0, uh, ul);
-                gh = -gh;
-                gl = -gl;
-#pragma unroll
-                for (int j = 0; j < NTW; ++j) {
-                    const int nt = NTW * half + j;
-                    mma3(accA[j], gh, gl, b_rm(sSh, 16 * nt), b_rm(sSl, 16 * nt));  // B[k'][v] = S_J[k'][v]
-                    mma3(accB[j], uh, ul, b_rm(sDh, 16 * nt), b_rm(sDl, 16 * nt));
-                    sched_fence();  // one tile's operands live at a time
-                }
-            } else {  // dQ_S += dO_J S_J^T;  dA -= G_U,J U_J^T;  dP += dO_J U_J^T
-                const frag_t<T> ao = x_rm(sO, LDV, 16 * mt, 0);
-#pragma unroll
-                for (int j = 0; j < NTW; ++j) {
-                    mma(accA[j], ao, b_rm(sSh, 16 * (NTW * half + j)));
-                    mma(accA[j], ao, b_rm(sSl, 16 * (NTW * half + j)));
-                    sched_fence();
-                }
-                frag_t<T> gh, gl;
-                f_rm(sGU, LDU, 16 * mt, 0, gh, gl);
-                gh = -gh;
-                gl = -gl;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    frag_t<T> uh, ul;
-                    f_rm(sU, LDU, 16 * (2 * half + j), 0, uh, ul);  // B[s][v] = U_J[s][v]
-                    mma3(dA2[j], gh, gl, uh, ul);
-                    mma(dP2[j], ao, uh);
-                    mma(dP2[j], ao, ul);
-                    sched_fence();
-                }
-            }
-        }
-        __syncthreads();  // the blocks are done: sBlk, sX are free
-        asm volatile("" : "+v"(lane));
-        q4 = lane >> 4;
-        n16 = lane & 15;
-
-        // B: dA and dP terms.  KK of the wave's two C x C tiles again (exact
-        // bf16 operands), dbeta and decay-gradient sums, dP o Gamma and
-        // Ah + Ah^T (Ah strictly lower, mirrored) to LDS.
-        float rowX[4] = {0.f, 0.f, 0.f, 0.f}, rowY[4] = {0.f, 0.f, 0.f, 0.f};
-        if (grpB) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int ns = 2 * half + j;
-                f32x4 kk4 = z4;
-#pragma unroll 1
-                for (int kk = 0; kk < D; kk += 32) mma(kk4, x_rm(xk, LDX, 16 * mt, kk), x_rm(xk, LDX, 16 * ns, kk));
-                float col = 0.f;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int t = 16 * mt + 4 * q4 + r, s2 = 16 * ns + n16;
-                    const float ge = expf(sb[t] - sb[s2]);
-                    const float dAv = s2 < t ? dA2[j][r] : 0.f;
-                    const float kkm = s2 < t ? ge * kk4[r] : 0.f;
-                    const float dPv = s2 <= t ? dP2[j][r] : 0.f;
-                    rowX[r] = fmaf(dAv, kkm, rowX[r]);                           // sum_s dA KK o Gamma (dbeta)
-                    const float ex = dAv * sbe[t] * kkm + dPv * sP[t * LD6 + s2];  // dA o A + dP o P
-                    rowY[r] += ex;
-                    col -= ex;
-                    sE1[t * LD6 + s2] = s2 <= t ? dPv * ge : 0.f;
-                    const float ah = dAv * sbe[t] * ge;
-                    if (s2 < t) {
-                        sE2[t * LD6 + s2] = ah;
-                        sE2[s2 * LD6 + t] = ah;
-                    } else if (s2 == t) {
-                        sE2[t * LD6 + t] = 0.f;
+                for (int r = 0; r < 4; ++r)
+                    if (s0 + r < t) {
+                        const T h = cvt<T>(ah[r]);
+                        sE2[epos(s0 + r, t)] = h;
+                        sE2[C * C + epos(s0 + r, t)] = cvt<T>(ah[r] - tof<T>(h));
                     }
+                rx = sum_rows(rx);
+                const float row = sum_rows(exA[0] + exA[1] + exA[2] + exA[3]);
+                if (q4 == 0) {
+                    sRX[st][t] = rx;
+                    sXr[0][st][t] = row;
                 }
-                col += __shfl_xor(col, 16);
-                col += __shfl_xor(col, 32);
-                if (q4 == 0) sCol[mt][16 * ns + n16] = col;
-            }
-        }
-        __syncthreads();
-        float rowZ[4] = {0.f, 0.f, 0.f, 0.f};  // A: sum G_W k;  B: gamma sum q dQ_S
-        float rowW[4] = {0.f, 0.f, 0.f, 0.f};  // A: sum dK_S k
-        if (!grpB) {  // dk
-            f32x4 dk[NTW];
-#pragma unroll
-            for (int j = 0; j < NTW; ++j) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int t = 16 * mt + 4 * q4 + r, c = 16 * (NTW * half + j) + n16;
-                    const float kv = tof<T>(xk[t * LDX + c]);
-                    rowZ[r] = fmaf(accA[j][r], kv, rowZ[r]);
-                    rowW[r] = fmaf(accB[j][r], kv, rowW[r]);
-                    dk[j][r] = se[t] * accB[j][r] + sbe[t] * sg[t] * accA[j][r];
+                    const float c = sum16(exA[r]);
+                    if (n16 == 0) sXc[0][tt][s0 + r] = c;
                 }
             }
-#pragma unroll 1
-            for (int kk = 0; kk < C; kk += 32) {
-                frag_t<T> eh, el, ah, al;
-                f_tr(sE1, LD6, 16 * mt, kk, eh, el);  // A[t][s] = (dP o Gamma)[s][t]
-                f_rm(sE2, LD6, 16 * mt, kk, ah, al);  // A[t][s] = (Ah + Ah^T)[t][s]
-#pragma unroll
-                for (int j = 0; j < NTW; ++j) {
-                    const int c0 = 16 * (NTW * half + j);
-                    const frag_t<T> bq = x_tr(xq, LDX, c0, kk), bk = x_tr(xk, LDX, c0, kk);  // B[c][s] = X[s][c]
-                    mma(dk[j], eh, bq);
-                    mma(dk[j], el, bq);
-                    mma(dk[j], ah, bk);
-                    mma(dk[j], al, bk);
-                    sched_fence();
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < NTW; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    ((T *)a.dk)[xo0 + (int64_t)(16 * mt + 4 * q4 + r) * a.sx_l + 16 * (NTW * half + j) + n16] =
-                        cvt<T>(dk[j][r]);
-        } else {  // dq
-            f32x4 dq[NTW];
-#pragma unroll
-            for (int j = 0; j < NTW; ++j) {
+            if (doP) {
+                put4(sE1, sE1 + TRI, tri_pos<0>(t, s0), e1);
+                const float row = sum_rows(exP[0] + exP[1] + exP[2] + exP[3]);
+                if (q4 == 0) sXr[1][st][t] = row;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int t = 16 * mt + 4 * q4 + r, c = 16 * (NTW * half + j) + n16;
-                    dq[j][r] = sg[t] * accA[j][r];
-                    rowZ[r] = fmaf(tof<T>(xq[t * LDX + c]), dq[j][r], rowZ[r]);
+                    const float c = sum16(exP[r]);
+                    if (n16 == 0) sXc[1][tt][s0 + r] = c;
                 }
             }
-#pragma unroll 1
-            for (int kk = 0; kk < C; kk += 32) {
-                frag_t<T> eh, el;
-                f_rm(sE1, LD6, 16 * mt, kk, eh, el);  // A[t][s] = (dP o Gamma)[t][s]
-#pragma unroll
-                for (int j = 0; j < NTW; ++j) {
-                    const frag_t<T> bk = x_tr(xk, LDX, 16 * (NTW * half + j), kk);
-                    mma(dq[j], eh, bk);
-                    mma(dq[j], el, bk);
-                    sched_fence();
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < NTW; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    ((T *)a.dq)[xo0 + (int64_t)(16 * mt + 4 * q4 + r) * a.sx_l + 16 * (NTW * half + j) + n16] =
-                        cvt<T>(dq[j][r]);
+        };
+        if constexpr (NW == 8) {  // one tile each; the last two cut in halves over waves 4 to 7
+            tile(w, true, true);
+            if (w >= 4) tile(8 + ((w >> 1) & 1), w & 1, !(w & 1));
+        } else {
+            for (int i = w; i < 10; i += NW) tile(i, true, true);
         }
-        // row sums over the 16 lanes of each row, two waves (halves) per row tile
-        //   sRow[0]: A sum G_W k        [1]: A sum dK_S k       [2]: B gamma sum q dQ_S
-        //   sRow[3]: B sum_v G_U v      [4]: B sum dA KK o Gamma [5]: B rows of dA o A + dP o P
+        if (tid < 128) {  // E1's zero blocks (0,1) and (2,3) inside the diagonal quadrants
+            const int b = tid >> 6, o = tri_pos<0>(32 * b + ((tid >> 2) & 15), 32 * b + 16 + 4 * (tid & 3));
+            *reinterpret_cast<s4v *>(&sE1[o]) = s4v{0, 0, 0, 0};
+            *reinterpret_cast<s4v *>(&sE1[TRI + o]) = s4v{0, 0, 0, 0};
+        }
+
+        sched_fence();
+        positions();
+        // --- 3. rows k' = own + r, columns t = 16 tt + n16
+        f32x4 aq[4], aw[4], ak[4];  // dQ_S^T, -G_W^T, dK_S^T
+        float sd = 0.f;             // <dS', S> over this lane's values
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int t = 16 * mt + 4 * q4 + r;
-            const float z = rowsum16(rowZ[r]), wv = rowsum16(rowW[r]);
-            const float x = rowsum16(rowX[r]), y = rowsum16(rowY[r]), u = rowsum16(rGUv[r]);
-            if (n16 == 0) {
-                if (!grpB) {
-                    sRow[0][half][t] = z;
-                    sRow[1][half][t] = wv;
-                } else {
-                    sRow[2][half][t] = z;
-                    sRow[3][half][t] = u;
-                    sRow[4][half][t] = x;
-                    sRow[5][half][t] = y;
-                }
+        for (int tt = 0; tt < 4; ++tt) aq[tt] = aw[tt] = ak[tt] = z4;
+#pragma unroll
+        for (int kv = 0; kv < KS; ++kv) {
+            frag_t<T> sh, sl, dh, dl;
+            split8<T, true>(&s2[8 * kv], sh, sl);
+            split8<T, true>(&d2[8 * kv], dh, dl);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sd = fmaf(s2[8 * kv + j], d2[8 * kv + j], sd);
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                const frag_t<T> of = rows(sO, tt, kv);
+                mma(aq[tt], sh, of);
+                mma(aq[tt], sl, of);
+                mma3(aw[tt], sh, sl, rows(sGh, tt, kv), rows(sGl, tt, kv));
+                mma3(ak[tt], dh, dl, rows(sUh, tt, kv), rows(sUl, tt, kv));
+                if (tt & 1) sched_fence();
             }
+        }
+        __syncthreads();  // E1, E2 are complete; v's and dO's tiles are free
+        if (nx < items) {
+            load_vo(nx);
+            load_s1(nx);
+        }
+
+        sched_fence();
+        positions();
+        // --- 4. dq, dk (rows c = own + r, columns t) and the row sums
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            const int t = 16 * tt + n16, p = xb + 16 * tt * D;
+            const f32x4 kv = ld4f(sK + p), qv = ld4f(sQ + p);
+            float z = 0.f, ww = 0.f, y = 0.f;
+            aq[tt] *= sg[t];
+            const float et = se[t], bg = sbe[t] * sg[t];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                z = fmaf(-aw[tt][r], kv[r], z);
+                ww = fmaf(ak[tt][r], kv[r], ww);
+                y = fmaf(qv[r], aq[tt][r], y);
+                ak[tt][r] = et * ak[tt][r] - bg * aw[tt][r];
+            }
+            z = sum_rows(z);
+            ww = sum_rows(ww);
+            y = sum_rows(y);
+            if (q4 == 0) {
+                sZ[w][t] = z;
+                sW[w][t] = ww;
+                sY[w][t] = y;
+            }
+        }
+#pragma unroll
+        for (int ks = 0; ks < C / 32; ++ks) {
+            const frag_t<T> kf = cols(sK, ks), qf = cols(sQ, ks);
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                if (tt >= 2 * ks) {  // E1[t][s]
+                    mma(aq[tt], kf, tri_rows((const short *)sE1, tt, ks));
+                    mma(aq[tt], kf, tri_rows((const short *)sE1 + TRI, tt, ks));
+                }
+                if (tt < 2 * ks + 2) {  // E1[s][t]
+                    mma(ak[tt], qf, tri_tr((const short *)sE1, ks, tt));
+                    mma(ak[tt], qf, tri_tr((const short *)sE1 + TRI, ks, tt));
+                }
+                const int o = eb[ks] + 16 * tt * C;
+                mma(ak[tt], kf, rd(sE2, o));
+                mma(ak[tt], kf, rd(sE2, C * C + o));
+            }
+        }
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {  // whole rows through U's tiles
+            const int p = xb + 16 * tt * D;
+            st4(sUh + p, aq[tt][0], aq[tt][1], aq[tt][2], aq[tt][3]);
+            st4(sUl + p, ak[tt][0], ak[tt][1], ak[tt][2], ak[tt][3]);
         }
         sd = wave_sum(sd);
         if (lane == 0) sWav[w] = sd;
         __syncthreads();
-        if (tid < 64) {  // per token, then dg_t = sum_{t' >= t} db_t' (one wave)
-            const int t = tid;
-            auto R = [&](int k) { return sRow[k][0][t] + sRow[k][1][t]; };
-            const float gwk = R(0), rt = se[t] * R(1);
-            a.dbeta[go0 + (int64_t)t * a.sg_l] = sg[t] * gwk + R(3) + R(4);
-            // sCol holds the column sums negated (rows minus columns of dA o A + dP o P)
-            float db = R(2) + R(5) + (sCol[0][t] + sCol[1][t] + sCol[2][t] + sCol[3][t]) + sbe[t] * sg[t] * gwk - rt;
-            float tot = 0.f;
-            for (int u = 0; u < 16; ++u) tot += sWav[u];
+        {
+            const int64_t xo = xo_of(it);
+            const rsrc_t rq = buf_rsrc((T *)a.dq + xo, span), rk = buf_rsrc((T *)a.dk + xo, span);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int p = sp + i * RS * D;
+                buf_st(rq, xoff, i * RS * rowb, *reinterpret_cast<const blk *>(sUh + p));
+                buf_st(rk, xoff, i * RS * rowb, *reinterpret_cast<const blk *>(sUl + p));
+            }
+        }
+        if (w == 0) {  // per token, then dg_t = sum_{t' >= t} db_t'
+            const int t = lane;
+            float gwk = 0.f, dk1 = 0.f, qd = 0.f, guv = 0.f, rx = 0.f, row = 0.f, col = 0.f, tot = 0.f;
+#pragma unroll
+            for (int u = 0; u < NW; ++u) {
+                gwk += sZ[u][t];
+                dk1 += sW[u][t];
+                qd += sY[u][t];
+                guv += sGv[u][t];
+                tot += sWav[u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (u <= t >> 4) {
+                    rx += sRX[u][t];
+                    row += sXr[0][u][t] + sXr[1][u][t];
+                }
+                if (u >= t >> 4) col += sXc[0][u][t] + sXc[1][u][t];
+            }
+            const int64_t go = go_of(it);
+            a.dbeta[go + (int64_t)t * a.sg_l] = sg[t] * gwk + guv + rx;
+            const float rt = se[t] * dk1;
+            float db = qd + (row - col) + sbe[t] * sg[t] * gwk - rt;
             const float rsum = wave_sum(rt);
             if (t == C - 1) db += rsum + sg[C - 1] * tot;
-            a.dg[go0 + (int64_t)t * a.sg_l] = wave_incl_suffix(db, lane);
+            a.dg[go + (int64_t)t * a.sg_l] = wave_incl_suffix(db, lane);
         }
     }
 }
@@ -1780,7 +1735,7 @@ hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0
         const int64_t items = (int64_t)bh * (a.L / C);
         if (items > 0)
             hipExtLaunchKernelGGL((k_gdn_dchunk<__bf16, D>), dim3((unsigned)std::min<int64_t>(items, a.n_x)),
-                                  dim3(1024), 0, s, e0, e1, 0, a);
+                                  dim3(4 * D), 0, s, e0, e1, 0, a);
         break;
     }
     default: return hipErrorInvalidValue;
