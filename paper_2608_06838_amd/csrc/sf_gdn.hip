@@ -265,16 +265,6 @@ struct StateIO {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) S[m][i][r] = buf_ld<float>(rs, off, at(m, i, r));
     }
-    // transposed ([v][k]): a lane's four rows of a column are one 16-byte store
-    __device__ __forceinline__ static void store_t(const f32x4 (&S)[NCT][NK], float *dst, const GdnCols<D> &cl, int q4) {
-        const rsrc_t rs = buf_rsrc(dst, D * D * 4);
-        const uint32_t o = (uint32_t)(cl.col(0) * D + 8 * q4) * 4;
-#pragma unroll
-        for (int i = 0; i < NK; ++i)
-#pragma unroll
-            for (int m = 0; m < NCT; ++m)
-                buf_st(rs, o, (uint32_t)(4 * m * D + 32 * (i >> 1) + 4 * (i & 1)) * 4, S[m][i]);
-    }
     __device__ __forceinline__ void store(const f32x4 (&S)[NCT][NK], float *dst) const {
         const rsrc_t rs = buf_rsrc(dst, D * D * 4);
 #pragma unroll
@@ -293,6 +283,17 @@ struct StateIO {
 __device__ __forceinline__ constexpr int tri_a(int tt, int ks) { return ((tt >> 1) + ks) * 1024 + 4 * (tt & 1) * 32; }
 //   rows 16 tt + n16, columns 32 ks + 8 q4 ..     (tri_pos<1>, base n16, 8 q4)
 __device__ __forceinline__ constexpr int tri_b(int tt, int ks) { return ((tt >> 1) + ks) * 1024 + 16 * (tt & 1) * 32; }
+
+// A chunk's state as the hi/lo pair that the products split it into, transposed:
+// two [v][k] planes of bf16 (the bytes of the fp32 state), written by the wave that
+// splits it anyway, a fragment per 16-byte store, and read by the per-chunk
+// gradients as fragments, with no splitting there.  Fragment ks of tile m: column
+// col(m), rows 32 ks + 8 q4 ..
+template <typename T, int D>
+__device__ __forceinline__ void put_state_pair(rsrc_t rs, uint32_t off, int m, int ks, const frag_t<T> &h, const frag_t<T> &l) {
+    buf_st(rs, off, (uint32_t)(4 * m * D + 32 * ks) * 2, h);
+    buf_st(rs, off, (uint32_t)(4 * m * D + 32 * ks + D * D) * 2, l);
+}
 
 // the 16-byte blocks of T's pair that this thread moves between the rows of the
 // tensor that holds it and LDS (see k_gdn_tprep): row 16 i + tid / 16, block tid % 16
@@ -448,7 +449,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     int qb[2];
     DmaTile<T, D, 4>::row_base(lane, qb);
     TriTile<T> t4;
-    float gl, bl;
+    float gl = 0.f, bl = 0.f;  // wave 3's: a load of a chunk's gates touches 64 cache lines
     const int64_t cstep = (int64_t)C * a.sx_l;
     const uint32_t cspan = chunk_span<T, D>(a.sx_l), gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4);
     uint32_t toff[TT::RPT];
@@ -458,12 +459,15 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     const int t4base = TriTile<T>::base(tid);
     const uint32_t t4off = (uint32_t)(((tid >> 4) * a.sx_l + 8 * (tid & 15)) * (int64_t)sizeof(T));
     const uint32_t voff = (uint32_t)((n16 * a.sx_l + cl.c0 + 4 * NCT * q4) * (int64_t)sizeof(T));
+    const uint32_t coff = (uint32_t)(cl.col(0) * D + 8 * q4) * 2;  // chunk state pairs
     auto issue = [&](int c) {
         const int64_t nx = c * cstep;
         t2.load_buf(buf_rsrc(K + nx, cspan), toff, 0);
         if constexpr (TPRE && !OUTP) t4.load(buf_rsrc(TW + nx, cspan), t4off, tstep, tid);
-        gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
-        bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        if (w == 3) {
+            gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+            bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        }
         if (!PREP || role) t3.load_buf(buf_rsrc(V + nx, cspan), toff, 0);
         if constexpr (OUTP) dq.issue(buf_rsrc(Q + nx, cspan), sQ, w, rowb);
         if constexpr (OUTP && TPRE) dt.issue(buf_rsrc(TW + nx, cspan), sT, w, rowb);
@@ -473,20 +477,18 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     const unsigned par = pair_parity(a.n_cu);
     for (int c = 0; c < nch; ++c) {
         pair_turn(par);
-        if constexpr (MODE == W_STORE) sio.store_t(S, a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS, cl, q4);
-        const float b2 = wave_scan_dpp(gl * LOG2E);
-        const float b63 = lane_value(b2, 63);
-        const float betal = bl;
         if constexpr (OUTP) vm_wait_all();  // this wave's part of Q and T is in LDS
         __syncthreads();  // the previous chunk is done with every LDS tile
         t2.store_swz(sK, LDN, tid, SWX);
         if (!PREP || role) t3.store_swz(sV, LDN, tid, SWX);
         if constexpr (TPRE && !OUTP) t4.store(sT, t4base, tid);
         if (w == 3) {
+            const float b2 = wave_scan_dpp(gl * LOG2E);
+            const float b63 = lane_value(b2, 63);
             sb[lane] = b2;
             sq[lane] = fexp2(b2);
             se[lane] = fexp2(b63 - b2);
-            sbeta[lane] = betal;
+            sbeta[lane] = bl;
         }
         __syncthreads();
 
@@ -521,6 +523,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
 
         // X[t][v] = V[t][v] - gamma_t sum_k K[t][k] S[k][v] (rows t = prow(tt, r));
         // O^T[v][t] = sum_k S[k][v] Q[t][k]
+        const rsrc_t rc = buf_rsrc(MODE == W_STORE ? a.wsSc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS : nullptr, D * D * 4);
         f32x4 X[NCT][4], O[NCT][4];
 #pragma unroll
         for (int m = 0; m < NCT; ++m)
@@ -530,7 +533,10 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
         for (int ks = 0; ks < D / 32; ++ks) {
             frag_t<T> fh[NCT], fl[NCT];
 #pragma unroll
-            for (int m = 0; m < NCT; ++m) split_acc<T, true>(S[m][2 * ks], S[m][2 * ks + 1], fh[m], fl[m]);
+            for (int m = 0; m < NCT; ++m) {
+                split_acc<T, true>(S[m][2 * ks], S[m][2 * ks + 1], fh[m], fl[m]);
+                if constexpr (MODE == W_STORE) put_state_pair<T, D>(rc, coff, m, ks, fh[m], fl[m]);
+            }
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
                 const frag_t<T> kf = *reinterpret_cast<const frag_t<T> *>(
@@ -658,7 +664,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
         if (c + 1 < nch) issue(c + 1);
 
         // S = gamma_C S + K^T (e^{b_C - b} o U)
-        const float gam = fexp2(b63);
+        const float gam = sq[C - 1];
 #pragma unroll
         for (int m = 0; m < NCT; ++m)
 #pragma unroll
@@ -865,7 +871,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
     using TT = Tile<T, D, NT>;
     TT t1, t2, t3;
     TriTile<T> t4;
-    float gl, bl;
+    float gl = 0.f, bl = 0.f;  // wave 3's: a load of a chunk's gates touches 64 cache lines
     const int64_t cstep = (int64_t)C * a.sx_l;
     const uint32_t cspan = chunk_span<T, D>(a.sx_l), gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4);
     uint32_t toff[TT::RPT];
@@ -875,12 +881,15 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
     const int t4base = TriTile<T>::base(tid);
     const uint32_t t4off = (uint32_t)(((tid >> 4) * a.sx_l + 8 * (tid & 15)) * (int64_t)sizeof(T));
     const uint32_t voff = (uint32_t)((n16 * a.sx_l + cl.c0 + 4 * NCT * q4) * (int64_t)sizeof(T));
+    const uint32_t coff = (uint32_t)(cl.col(0) * D + 8 * q4) * 2;  // chunk state pairs
     auto issue = [&](int c) {
         const int64_t nx = c * cstep;
         t1.load_buf(buf_rsrc(Q + nx, cspan), toff, 0);
         t2.load_buf(buf_rsrc(K + nx, cspan), toff, 0);
-        gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
-        bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        if (w == 3) {
+            gl = buf_ld<float>(buf_rsrc(gp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+            bl = buf_ld<float>(buf_rsrc(bp + (int64_t)c * C * a.sg_l, gspan), goff, 0);
+        }
         if constexpr (TPRE) t4.load(buf_rsrc(TW + nx, cspan), t4off, tstep, tid);
         t3.load_buf(buf_rsrc(DO + nx, cspan), toff, 0);
     };
@@ -889,21 +898,18 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
     const unsigned par = pair_parity(a.n_cu);
     for (int c = nch - 1; c >= 0; --c) {
         pair_turn(par);
-        if constexpr (!PREP)  // dS' of chunk c: the gradient of the state leaving it
-            sio.store_t(dS, a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS, cl, q4);
-        const float b2 = wave_scan_dpp(gl * LOG2E);
-        const float b63 = lane_value(b2, 63);
-        const float betal = bl;
         __syncthreads();  // the previous chunk is done with every LDS tile
         t1.store_swz(sQ, LDN, tid, SWX);
         t2.store_swz(sK, LDN, tid, SWX);
         t3.store_swz(sO, LDN, tid, SWX);
         if constexpr (TPRE) t4.store(sT, t4base, tid);
         if (w == 3) {
+            const float b2 = wave_scan_dpp(gl * LOG2E);
+            const float b63 = lane_value(b2, 63);
             sb[lane] = b2;
             sq[lane] = fexp2(b2);
             se[lane] = fexp2(b63 - b2);
-            sbeta[lane] = betal;
+            sbeta[lane] = bl;
         }
         __syncthreads();
 
@@ -937,6 +943,8 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
 
         // dU[t][v] = e^{b_C - b_t} sum_k K[t][k] dS[k][v] + sum_{t' >= t} P^T[t][t'] dO[t'][v]
         // (rows t = prow(tt, r))
+        // dS' of chunk c, the gradient of the state leaving it, is stored on the way
+        const rsrc_t rc = buf_rsrc(PREP ? nullptr : a.wsDc + ((int64_t)bh * (a.L / C) + tok0 / C + c) * SS, D * D * 4);
         f32x4 dU[NCT][4];
 #pragma unroll
         for (int m = 0; m < NCT; ++m)
@@ -946,7 +954,10 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
         for (int ks = 0; ks < D / 32; ++ks) {
             frag_t<T> fh[NCT], fl[NCT];
 #pragma unroll
-            for (int m = 0; m < NCT; ++m) split_acc<T, true>(dS[m][2 * ks], dS[m][2 * ks + 1], fh[m], fl[m]);
+            for (int m = 0; m < NCT; ++m) {
+                split_acc<T, true>(dS[m][2 * ks], dS[m][2 * ks + 1], fh[m], fl[m]);
+                if constexpr (!PREP) put_state_pair<T, D>(rc, coff, m, ks, fh[m], fl[m]);
+            }
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
                 const frag_t<T> kf = *reinterpret_cast<const frag_t<T> *>(
@@ -1057,7 +1068,7 @@ __global__ void __launch_bounds__(256, 2) k_gdn_dwalk(GdnArgs a) {
         if (c > 0) issue(c - 1);
 
         // dS = gamma_C dS + Q^T (gamma o dO) - K^T (beta gamma o G_U)
-        const float gam = fexp2(b63);
+        const float gam = sq[C - 1];
 #pragma unroll
         for (int m = 0; m < NCT; ++m)
 #pragma unroll
@@ -1164,8 +1175,8 @@ __global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
 
 // Parameter gradients of one chunk per item (b, h, chunk), items in a grid-stride
 // loop, one workgroup of D / 16 waves per CU.  S is the state entering the chunk
-// and dS' the gradient of the state leaving it, both stored per chunk and
-// transposed ([v][k] fp32) by the walks.  Three identities keep W, Ubar and a
+// and dS' the gradient of the state leaving it, both stored per chunk by the walks
+// as transposed hi/lo pairs (put_state_pair).  Three identities keep W, Ubar and a
 // second inverse out of the kernel:
 //   U = T diag(beta) (V - diag(gamma) K S),   G_U = T^T dU,
 //   G_W = T^T (-dU S^T) = -G_U S^T,   dA = -(G_W W^T + G_U Ubar^T) = -G_U U^T.
@@ -1174,20 +1185,22 @@ __global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
 //      which go from memory straight into its registers; U^T and G_U^T (rows v)
 //      leave their accumulators as four consecutive channels of a token, into LDS
 //      as hi/lo pairs;
-//   2. the causal 16 x 16 tiles of dA and dP = dO U^T, shared out over the waves,
+//   2. of k: dQ_S^T = S dO^T, G_W^T = -S G_U^T, dK_S^T = dS' U^T on its own rows
+//      of S and dS', handed on through LDS 32 columns at a time (read again from
+//      memory, both missed L2 often enough to cost a third more traffic);
+//   3. the causal 16 x 16 tiles of dA and dP = dO U^T, shared out over the waves,
 //      become E1 = dP o Gamma and E2 = Ah + Ah^T (Ah = dA o beta Gamma) in LDS;
-//   3. of k: dQ_S^T = S dO^T, G_W^T = -S G_U^T, dK_S^T = dS' U^T on its own rows
-//      of S and dS', again straight from memory (the second read finds most of
-//      both in L2);
 //   4. dq = gamma dQ_S + E1 K,  dk = e dK_S + E1^T Q + beta gamma G_W + E2 K, turned
 //      into whole rows through LDS.
-// Five barriers per item.  dbeta and the log-decay gradient come from row and
+// Thirteen barriers per item.  dbeta and the log-decay gradient come from row and
 // column sums in a fixed order (no atomics).  q, k, v, dO enter the products
 // exactly (bf16); the computed fp32 operands (S, dS', T, P, X, U, dU, G_U, E1, E2)
-// as hi/lo bf16 pairs (three products, lo x lo dropped).  The next item's q, k, T
-// wait in registers and its v, dO are copied into LDS during step 4.
+// as hi/lo bf16 pairs (three products, lo x lo dropped).  The next item's q, k, T,
+// S and dS' wait in registers from step 2 on and its v, dO are copied into LDS
+// during step 4.
 // D = 128, 65536 tokens of 40 heads: 7.6 ms with S and dS' staged through LDS in
-// blocks of 32 channels by 16 waves (16 barriers, and T formed again), XX ms so.
+// blocks of 32 channels by 16 waves (T formed again, spills), 3.0 ms so (9.7 GB,
+// 1.9 ms at the rate of a copy).
 template <typename T, int D>
 __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
     constexpr int NW = D / 16, NT = 4 * D, KS = D / 32, BPR = D / 8;
@@ -1196,14 +1209,20 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
     // tiles in DmaTile's layout; G_U's hi half takes v's place (a lane overwrites
     // the values that it alone has read)
     __shared__ __attribute__((aligned(16))) T sQ[XT], sK[XT], sO[XT], sUh[XT], sUl[XT], sGh[XT], sGl[XT];
-    // T then E1 (tri, 12 KB), P^T then part of E2 (full C x C pair)
-    __shared__ __attribute__((aligned(16))) short sR[2 * TRI + 2 * C * C];
+    // T then E1 (tri, 12 KB), P^T then part of E2 (full C x C pair); between the two,
+    // four planes of 32 x D
+    constexpr int RN = 2 * TRI + 2 * C * C > 128 * D ? 2 * TRI + 2 * C * C : 128 * D;
+    __shared__ __attribute__((aligned(16))) short sR[RN];
     __shared__ __attribute__((aligned(16))) float sb[C], sg[C], se[C], sbe[C];
-    __shared__ float sGv[NW][C], sZ[NW][C], sW[NW][C], sY[NW][C];  // per wave: G_U.v, G_W.k, dK_S.k, gamma q.dQ_S
+    __shared__ float sGv[NW][C];                                   // per wave: G_U.v
     __shared__ float sRX[4][C], sXr[2][4][C], sXc[2][4][C];        // per tile column / row: see the sums below
     __shared__ float sWav[NW];
     __shared__ __attribute__((aligned(16))) float sA[TPRE ? 4 : C * (C + 4)];
     T *const sV = sGh;
+    // per wave: G_W.k, dK_S.k, gamma q.dQ_S, once G_U is no longer read
+    typedef float row_t[C];
+    row_t *const sZ = reinterpret_cast<row_t *>(sGl), *const sW = sZ + NW, *const sY = sW + NW;
+    static_assert(3 * NW * C * 4 <= XT * (int)sizeof(T), "the sums fit G_U's lo tile");
     short *const sT = sR;
     T *const sP = reinterpret_cast<T *>(sR + 2 * TRI);
     T *const sE1 = reinterpret_cast<T *>(sR), *const sE2 = reinterpret_cast<T *>(sR + 2 * TRI);
@@ -1212,8 +1231,8 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
     int lane = tid & 63, q4 = lane >> 4, n16 = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t SS = (int64_t)D * D;
-    const int nc = (int)(a.L / C);
-    const int64_t items = (int64_t)a.B * a.H * nc;
+    // (the chunk states of 2^31 items would not fit any memory)
+    const uint32_t nc = (uint32_t)(a.L / C), items = (uint32_t)(a.B * a.H) * nc;
 
     // --- positions (see DmaTile for the swizzle)
     auto xpos = [](int r, int c) { return r * D + (((c >> 3) ^ (r & 7) ^ (((r >> 3) & 1) << 2)) << 3) + (c & 7); };
@@ -1288,19 +1307,16 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
     const int sp = xpos(tid / BPR, 8 * (tid % BPR));
     const uint32_t toff = (uint32_t)((tid >> 4) * (uint64_t)rowb + 16 * (tid & 15));
     blk pq[2], pk[2], pt[2];
-    float gl, bl;
-    f32x4 s1[2 * KS], d1[2 * KS];  // S, dS' of the wave's own v: [own v][32 ks + 8 q4 + 4 h ..]
-    auto xo_of = [&](int64_t it) {
-        const int bh = (int)(it / nc), ch = (int)(it % nc);
-        return (int64_t)(bh / a.H) * a.sx_b + (int64_t)(bh % a.H) * a.sx_h + (int64_t)ch * C * a.sx_l;
-    };
-    auto go_of = [&](int64_t it) {
-        const int bh = (int)(it / nc), ch = (int)(it % nc);
-        return (int64_t)(bh / a.H) * a.sg_b + (int64_t)(bh % a.H) * a.sg_h + (int64_t)ch * C * a.sg_l;
+    float gl = 0.f, bl = 0.f;
+    frag_t<T> s1h[KS], s1l[KS], d1h[KS], d1l[KS];  // S, dS' of the wave's own v: [own v][32 ks + 8 q4 ..]
+    // offsets of an item's tokens and gates
+    auto locate = [&](uint32_t it, int64_t &xo, int64_t &go) {
+        const uint32_t bh = it / nc, ch = it - bh * nc, b = bh / (uint32_t)a.H, h = bh - b * (uint32_t)a.H;
+        xo = b * a.sx_b + h * a.sx_h + (int64_t)(ch * C) * a.sx_l;
+        go = b * a.sg_b + h * a.sg_h + (int64_t)(ch * C) * a.sg_l;
     };
     constexpr uint32_t RS = NT / BPR, RT = NT / 16;  // rows per round of blocks: tiles, T
-    auto load_regs = [&](int64_t it) {
-        const int64_t xo = xo_of(it), go = go_of(it);
+    auto load_regs = [&](int64_t xo, int64_t go) {
         const rsrc_t rq = buf_rsrc((const T *)a.q + xo, span), rk = buf_rsrc((const T *)a.k + xo, span);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -1312,32 +1328,39 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             if ((tid & 7) < 4) pt[0] = buf_ld<blk>(rt, toff, 0);
             pt[1] = buf_ld<blk>(rt, toff, RT * rowb);
         }
-        const uint32_t gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4), goff = (uint32_t)(lane * a.sg_l * 4);
-        gl = buf_ld<float>(buf_rsrc(a.g + go, gspan), goff, 0);
-        bl = buf_ld<float>(buf_rsrc(a.beta + go, gspan), goff, 0);
+        if (w == 0) {  // one cache line per token: a load costs 64 of them, so one wave does it
+            const uint32_t gspan = (uint32_t)(((C - 1) * a.sg_l + 1) * 4), goff = (uint32_t)(lane * a.sg_l * 4);
+            gl = buf_ld<float>(buf_rsrc(a.g + go, gspan), goff, 0);
+            bl = buf_ld<float>(buf_rsrc(a.beta + go, gspan), goff, 0);
+        }
     };
-    auto load_vo = [&](int64_t it) {
-        const int64_t xo = xo_of(it);
+    auto load_vo = [&](int64_t xo) {
         dma.issue(buf_rsrc((const T *)a.v + xo, span), sV, w, rowb);
         dma.issue(buf_rsrc((const T *)a.dO + xo, span), sO, w, rowb);
     };
-    auto load_s1 = [&](int64_t it) {
-        const rsrc_t rs = buf_rsrc(a.wsSc + it * SS, (uint32_t)(SS * 4)), rd = buf_rsrc(a.wsDc + it * SS, (uint32_t)(SS * 4));
-        const uint32_t o = (uint32_t)(((16 * w + n16) * D + 8 * q4) * 4);
+    auto load_s1 = [&](uint32_t it) {
+        const rsrc_t rs = buf_rsrc(a.wsSc + (int64_t)it * SS, (uint32_t)(SS * 4)), rd = buf_rsrc(a.wsDc + (int64_t)it * SS, (uint32_t)(SS * 4));
+        const uint32_t o = (uint32_t)(((16 * w + n16) * D + 8 * q4) * 2);
 #pragma unroll
-        for (int j = 0; j < 2 * KS; ++j) {
-            s1[j] = buf_ld<f32x4>(rs, o, 128 * (j >> 1) + 16 * (j & 1));
-            d1[j] = buf_ld<f32x4>(rd, o, 128 * (j >> 1) + 16 * (j & 1));
+        for (int ks = 0; ks < KS; ++ks) {
+            s1h[ks] = buf_ld<frag_t<T>>(rs, o, 64 * ks);
+            s1l[ks] = buf_ld<frag_t<T>>(rs, o, 64 * ks + D * D * 2);
+            d1h[ks] = buf_ld<frag_t<T>>(rd, o, 64 * ks);
+            d1l[ks] = buf_ld<frag_t<T>>(rd, o, 64 * ks + D * D * 2);
         }
     };
 
-    int64_t it = blockIdx.x;
+    uint32_t it = blockIdx.x;
     if (it >= items) return;
-    load_regs(it);
-    load_vo(it);
+    int64_t xo, go, xn = 0, gn = 0;
+    locate(it, xo, go);
+    load_regs(xo, go);
+    load_vo(xo);
+    vm_wait_all();
     load_s1(it);
-    for (; it < items; it += gridDim.x) {
-        const int64_t nx = it + gridDim.x;
+    for (;; it += gridDim.x, xo = xn, go = gn) {
+        const uint32_t nx = it + gridDim.x;  // (below 2^32: see items)
+        if (nx < items) locate(nx, xn, gn);
         positions();
         // --- stage
 #pragma unroll
@@ -1360,7 +1383,6 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             se[lane] = fexp2(b63 - b2);
             sbe[lane] = bl;
         }
-        vm_wait_all();  // this wave's part of v and dO is in LDS
         __syncthreads();
 
         // --- P^T on the causal tiles (as in the dS walk)
@@ -1402,16 +1424,14 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             gdn_tinv_hl(tid, sA, sT, sT + TRI);
         }
 
-        positions();
         // --- 1. Y = K S, dU = e o (K dS') on the wave's own v (rows t = prow(tt, r))
-        f32x4 x[4], du[4];
+        f32x4 x[4], du[4], sd4 = z4;  // sd4: (S^T dS')[v][v'], its diagonal sums to <dS', S>
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) x[tt] = du[tt] = z4;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            frag_t<T> sh, sl, dh, dl;
-            split_acc<T, true>(s1[2 * ks], s1[2 * ks + 1], sh, sl);
-            split_acc<T, true>(d1[2 * ks], d1[2 * ks + 1], dh, dl);
+            const frag_t<T> sh = s1h[ks], sl = s1l[ks], dh = d1h[ks], dl = d1l[ks];
+            mma3(sd4, sh, sl, dh, dl);
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
                 const frag_t<T> kf = rd(sK, kb[(ks ^ tt) & 1] + roff(tt) * D + 64 * (ks >> 1));
@@ -1422,16 +1442,12 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             }
             sched_fence();
         }
-        // S and dS' again, the wave's own k as rows: s2[kv][j] = S[k'][32 kv + 8 q4 + j]
-        float s2[8 * KS], d2[8 * KS];
         {
-            const rsrc_t rs = buf_rsrc(a.wsSc + it * SS, (uint32_t)(SS * 4)), rdd = buf_rsrc(a.wsDc + it * SS, (uint32_t)(SS * 4));
-            const uint32_t o = (uint32_t)((8 * q4 * D + 16 * w + n16) * 4);
+            float sd = 0.f;
 #pragma unroll
-            for (int j = 0; j < 8 * KS; ++j) {
-                s2[j] = buf_ld<float>(rs, o, (uint32_t)((32 * (j >> 3) + (j & 7)) * D * 4));
-                d2[j] = buf_ld<float>(rdd, o, (uint32_t)((32 * (j >> 3) + (j & 7)) * D * 4));
-            }
+            for (int r = 0; r < 4; ++r) sd += 4 * q4 + r == n16 ? sd4[r] : 0.f;
+            sd = wave_sum(sd);
+            if (lane == 0) sWav[w] = sd;
         }
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) {
@@ -1478,7 +1494,6 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             }
         }
         sched_fence();
-        positions();
         // G_U^T[v][s] = sum_t dU^T[v][t] T[t][s]; v.G_U per token; G_U over v's place
         f32x4 gt[4];
 #pragma unroll
@@ -1500,9 +1515,47 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
         }
         __syncthreads();
         positions();
-        if (nx < items) load_regs(nx);
+        // --- 2. rows k' = own + r, columns t = 16 tt + n16
+        f32x4 aq[4], aw[4], ak[4];  // dQ_S^T, -G_W^T, dK_S^T
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) aq[tt] = aw[tt] = ak[tt] = z4;
+        // 32 v at a time: their two waves put their columns of S and dS' into LDS (four
+        // planes [v][k], hi and lo), every wave reads its own k of them as rows
+        T *const pl = reinterpret_cast<T *>(sR);
+        auto hand_on = [&](int kv) {
+            if ((w >> 1) != kv) return;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                T *const p = pl + rb[ks & 1] + 16 * (w & 1) * D + 64 * (ks >> 1);
+                *reinterpret_cast<frag_t<T> *>(p) = s1h[ks];
+                *reinterpret_cast<frag_t<T> *>(p + 32 * D) = s1l[ks];
+                *reinterpret_cast<frag_t<T> *>(p + 64 * D) = d1h[ks];
+                *reinterpret_cast<frag_t<T> *>(p + 96 * D) = d1l[ks];
+            }
+            if (nx < items) load_s1(nx);  // (the waves' turns spread these loads over the step)
+        };
+        if (nx < items) load_regs(xn, gn);
+        hand_on(0);
+#pragma unroll
+        for (int kv = 0; kv < KS; ++kv) {
+            __syncthreads();
+            auto turned = [&](int plane) { return tr2(pl + plane * 32 * D + tb[0], pl + plane * 32 * D + tb[1]); };
+            const frag_t<T> sh = turned(0), sl = turned(1), dh = turned(2), dl = turned(3);
+            __syncthreads();  // the planes are read (and, after the last, E1 and E2 may take their place)
+            if (kv + 1 < KS) hand_on(kv + 1);
+#pragma unroll
+            for (int tt = 0; tt < 4; ++tt) {
+                const frag_t<T> of = rows(sO, tt, kv);
+                mma(aq[tt], sh, of);
+                mma(aq[tt], sl, of);
+                mma3(aw[tt], sh, sl, rows(sGh, tt, kv), rows(sGl, tt, kv));
+                mma3(ak[tt], dh, dl, rows(sUh, tt, kv), rows(sUl, tt, kv));
+                if (tt & 1) sched_fence();
+            }
+        }
+        positions();
 
-        // --- 2. dA, dP on the causal tiles: rows s = 16 st + 4 q4 + r, column t = 16 tt + n16
+        // --- 3. dA, dP on the causal tiles: rows s = 16 st + 4 q4 + r, column t = 16 tt + n16
         auto tile = [&](int i, bool doA, bool doP) {
             int tt, st;
             tri_tile(i, tt, st);
@@ -1581,35 +1634,8 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             *reinterpret_cast<s4v *>(&sE1[TRI + o]) = s4v{0, 0, 0, 0};
         }
 
-        sched_fence();
-        positions();
-        // --- 3. rows k' = own + r, columns t = 16 tt + n16
-        f32x4 aq[4], aw[4], ak[4];  // dQ_S^T, -G_W^T, dK_S^T
-        float sd = 0.f;             // <dS', S> over this lane's values
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) aq[tt] = aw[tt] = ak[tt] = z4;
-#pragma unroll
-        for (int kv = 0; kv < KS; ++kv) {
-            frag_t<T> sh, sl, dh, dl;
-            split8<T, true>(&s2[8 * kv], sh, sl);
-            split8<T, true>(&d2[8 * kv], dh, dl);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) sd = fmaf(s2[8 * kv + j], d2[8 * kv + j], sd);
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                const frag_t<T> of = rows(sO, tt, kv);
-                mma(aq[tt], sh, of);
-                mma(aq[tt], sl, of);
-                mma3(aw[tt], sh, sl, rows(sGh, tt, kv), rows(sGl, tt, kv));
-                mma3(ak[tt], dh, dl, rows(sUh, tt, kv), rows(sUl, tt, kv));
-                if (tt & 1) sched_fence();
-            }
-        }
         __syncthreads();  // E1, E2 are complete; v's and dO's tiles are free
-        if (nx < items) {
-            load_vo(nx);
-            load_s1(nx);
-        }
+        if (nx < items) load_vo(xn);
 
         sched_fence();
         positions();
@@ -1661,11 +1687,9 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
             st4(sUh + p, aq[tt][0], aq[tt][1], aq[tt][2], aq[tt][3]);
             st4(sUl + p, ak[tt][0], ak[tt][1], ak[tt][2], ak[tt][3]);
         }
-        sd = wave_sum(sd);
-        if (lane == 0) sWav[w] = sd;
+        vm_wait_all();  // this wave's part of the next v and dO is in LDS
         __syncthreads();
         {
-            const int64_t xo = xo_of(it);
             const rsrc_t rq = buf_rsrc((T *)a.dq + xo, span), rk = buf_rsrc((T *)a.dk + xo, span);
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -1674,8 +1698,8 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
                 buf_st(rk, xoff, i * RS * rowb, *reinterpret_cast<const blk *>(sUl + p));
             }
         }
-        if (w == 0) {  // per token, then dg_t = sum_{t' >= t} db_t'
-            const int t = lane;
+        if (w == 0) {  // per token t = 63 - lane, so that dg_t = sum_{t' >= t} db_t' is a prefix sum over lanes
+            const int t = 63 - lane, tt = t >> 4;
             float gwk = 0.f, dk1 = 0.f, qd = 0.f, guv = 0.f, rx = 0.f, row = 0.f, col = 0.f, tot = 0.f;
 #pragma unroll
             for (int u = 0; u < NW; ++u) {
@@ -1686,21 +1710,21 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
                 tot += sWav[u];
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (u <= t >> 4) {
-                    rx += sRX[u][t];
-                    row += sXr[0][u][t] + sXr[1][u][t];
-                }
-                if (u >= t >> 4) col += sXc[0][u][t] + sXc[1][u][t];
+            for (int u = 0; u < 4; ++u) {  // tile columns u <= tt, then tile rows u >= tt (clamped reads, no branches)
+                const int lo = u < tt ? u : tt, hi = u > tt ? u : tt;
+                const float x = sRX[lo][t], y = sXr[0][lo][t] + sXr[1][lo][t], z = sXc[0][hi][t] + sXc[1][hi][t];
+                rx += u <= tt ? x : 0.f;
+                row += u <= tt ? y : 0.f;
+                col += u >= tt ? z : 0.f;
             }
-            const int64_t go = go_of(it);
             a.dbeta[go + (int64_t)t * a.sg_l] = sg[t] * gwk + guv + rx;
             const float rt = se[t] * dk1;
             float db = qd + (row - col) + sbe[t] * sg[t] * gwk - rt;
-            const float rsum = wave_sum(rt);
+            const float rsum = lane_value(wave_scan_dpp(rt), 63);
             if (t == C - 1) db += rsum + sg[C - 1] * tot;
-            a.dg[go + (int64_t)t * a.sg_l] = wave_incl_suffix(db, lane);
+            a.dg[go + (int64_t)t * a.sg_l] = wave_scan_dpp(db);
         }
+        if (nx >= items) break;
     }
 }
 
