@@ -994,7 +994,8 @@ __global__ void __launch_bounds__(128 * D / (16 * NCT)) k_bwd_dkv(SegArgs a) {
 
 // PG with the two roles in workgroups of their own (D/16 waves each), the form
 // used where the one-workgroup walk above does not fit the LDS (fp32 I/O at
-// d = 128: four fp32 tiles and two score tiles need 175 KB).  The v-role
+// d = 128: four fp32 tiles and two score tiles need 175 KB), and at d = 128 for
+// launches that would leave half the CUs idle.  The v-role
 // workgroup keeps G[k][v] and writes dv; the k-role workgroup keeps G^T[v][k]
 // and writes dk and dg.  Each stages three tiles (q and dO, plus k or v) and
 // its one score tile (A^T or dA^T).  The two workgroups of an item lie 8 apart
@@ -1263,13 +1264,24 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
         else
             hipExtLaunchKernelGGL((k_prep<T, D, SF_NCT_PREP, true>), grid, dim3(NTP), 0, s, e0, e1, 0, a);
         break;
-    case SF_K_BWD_DQ: hipExtLaunchKernelGGL((k_walk<T, D, SF_NCT_WALK, true>), grid, dim3(NTW), 0, s, e0, e1, 0, a); break;
+    case SF_K_BWD_DQ:
+        // up to one item per CU there is no second workgroup to cover a wave's
+        // waits: eight waves of one column tile instead of four of two (128 items
+        // of 8 chunks 53.5 -> 49.0 us, 256 of 4 chunks 46.1 -> 43.2)
+        if (sizeof(T) == 2 && D == 128 && (int64_t)grid.x <= (int64_t)a.n_cu)
+            hipExtLaunchKernelGGL((k_walk<T, D, 1, true>), grid, dim3(64 * D / 16), 0, s, e0, e1, 0, a);
+        else
+            hipExtLaunchKernelGGL((k_walk<T, D, SF_NCT_WALK, true>), grid, dim3(NTW), 0, s, e0, e1, 0, a);
+        break;
     case SF_K_BWD_DKV:
-        if constexpr (sizeof(T) == 4 && D == 128) {  // two workgroups per item, 8 apart in dispatch order
+        // a launch that would leave half the CUs idle puts the two roles on CUs of
+        // their own (128 items of 8 chunks: 59.5 -> 43.9 us; with a workgroup per CU
+        // either way the one-workgroup form is the faster, 613 against 816 us)
+        if ((sizeof(T) == 4 && D == 128) || (D == 128 && 2 * (int64_t)grid.x <= (int64_t)a.n_cu)) {
             const int64_t items = (int64_t)a.B * a.H * a.n_super;
             hipExtLaunchKernelGGL((k_bwd_dkv_wg<T, D>), dim3((unsigned)((items + 7) / 8 * 16)), dim3(64 * D / 16), 0, s,
                                   e0, e1, 0, a);
-        } else {
+        } else if constexpr (!(sizeof(T) == 4 && D == 128)) {
             constexpr int NCT = sizeof(T) == 2 && D == 128 ? SF_NCT_DKV : 1;
             hipExtLaunchKernelGGL((k_bwd_dkv<T, D, NCT>), grid, dim3(128 * D / (16 * NCT)), 0, s, e0, e1, 0, a);
         }
