@@ -218,7 +218,8 @@ size_t sf_chain_workspace_bytes(const sf_shape *shape, int32_t n_seg, const int6
 
 /*
  * Bytes of the kept superchunk states of a chain (optional `ckpt` buffer of
- * sf_chain_fwd / sf_chain_bwd): per segment of more than one superchunk, the
+ * sf_chain_fwd / sf_chain_bwd): per segment of more than one superchunk (a chain
+ * that runs as one set of launches counts as one segment), the
  * state entering each superchunk (the ST output of Sec. 2.2, fp32 Dk x Dv per
  * (b, h, superchunk)), each superchunk's log-decay and the state leaving the
  * segment.  The superchunk lengths are those the same shape, segments and
@@ -246,7 +247,9 @@ size_t sf_chain_ckpt_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *
  * concurrently with the next segment's preparation and the previous
  * segment's output kernels (Sec. 3.4, fwd split-and-overlap schedule; with
  * overlap = 2 the preparation runs on aux too, ahead of the scan); both
- * streams must belong to the current device.  On return the work is
+ * streams must belong to the current device.  A chain of at most 32 segments
+ * whose launches would each leave the device idle runs as one set of launches
+ * over all its segments, on main alone.  On return the work is
  * enqueued on main and aux, and main carries a dependency on all of it.
  */
 sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,

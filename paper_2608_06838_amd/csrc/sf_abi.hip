@@ -226,39 +226,44 @@ int device_cus() {
     return cached_cus;
 }
 
+// Superchunks of one head run one after another inside a workgroup.  The cost
+// of a forward and a backward over ns superchunks of at most m chunks for each of
+// bh heads, in chunk steps, fitted to measured steps of five workloads (2 to 128
+// heads, 512- to 65536-token segments):
+//   walks: m chunks per workgroup; up to one workgroup per CU they run in
+//     m steps; beyond that the CUs hold two each, in rounds of 2 * CUs,
+//     a round taking kPair * m (a second workgroup adds 1 / kPair - 1/2 of
+//     a CU's throughput); with superchunks the two prep kernels add kPrep;
+//   + kState per superchunk state of all heads (materialised, scanned and
+//     re-read: about 0.01 steps each at d = 128)
+//   + kScan per superchunk of one head (the scans' sequential steps).
+double chunk_cost(const Shape &r, int64_t m, int64_t ns) {
+    const double cus = (double)device_cus(), kState = 0.01 * (double)r.D * r.D / (128.0 * 128.0);
+    constexpr double kScan = 0.1, kPair = 1.6, kPrep = 1.5;
+    const double wg = (double)((int64_t)r.B * r.H * ns);
+    double cost = wg <= cus ? (double)m : std::ceil(wg / (2.0 * cus)) * (double)m * kPair;
+    if (ns > 1) cost = cost * kPrep + kState * wg + kScan * (double)ns;
+    return cost;
+}
+
 sf_status pick_ts(const Shape &r, int64_t L, const sf_tuning *t, int &ts) {
     if (t && t->ts != 0) {
         if (t->ts < 64 || t->ts % 64) return fail(SF_E_SHAPE, "tuning.ts must be a positive multiple of 64");
         ts = t->ts;
         return SF_OK;
     }
-    // Superchunks of one head run one after another inside a workgroup.  The
-    // superchunk length (a multiple of 64) minimises a cost in chunk steps,
-    // fitted to measured fwd+bwd steps of five workloads (2 to 128 heads,
-    // 512- to 65536-token segments):
-    //   walks: m chunks per workgroup; up to one workgroup per CU they run in
-    //     m steps; beyond that the CUs hold two each, in rounds of 2 * CUs,
-    //     a round taking kPair * m (a second workgroup adds 1 / kPair - 1/2 of
-    //     a CU's throughput); with superchunks the two prep kernels add kPrep;
-    //   + kState per superchunk state of all heads (materialised, scanned and
-    //     re-read: about 0.01 steps each at d = 128)
-    //   + kScan per superchunk of one head (the scans' sequential steps).
-    const int64_t bh = (int64_t)r.B * r.H;
+    // the superchunk length (a multiple of 64) minimises chunk_cost
     const int64_t nc = (L + 63) / 64;
     if (nc <= 1) {
         ts = (int)std::max<int64_t>(64, std::min<int64_t>(L, 1 << 30));
         return SF_OK;
     }
-    const double cus = (double)device_cus(), kState = 0.01 * (double)r.D * r.D / (128.0 * 128.0);
-    constexpr double kScan = 0.1, kPair = 1.6, kPrep = 1.5;
     double best = 1e300;
     int64_t best_m = nc;
     for (int64_t m = 1; m <= nc; ++m) {  // chunks per superchunk
         const int64_t ns = (nc + m - 1) / m;
         if (m > 1 && (nc + m - 2) / (m - 1) == ns) continue;  // same split as a shorter m
-        const double wg = (double)(bh * ns);
-        double cost = wg <= cus ? (double)m : std::ceil(wg / (2.0 * cus)) * (double)m * kPair;
-        if (ns > 1) cost = cost * kPrep + kState * wg + kScan * (double)ns;
+        const double cost = chunk_cost(r, m, ns);
         if (cost < best - 1e-9) {
             best = cost;
             best_m = m;
@@ -274,9 +279,8 @@ int n_super_of(int64_t L, int ts) { return L > 0 ? (int)((L + ts - 1) / ts) : 0;
 struct WsLayout {
     size_t S = 0, E = 0, Lg = 0, Dot = 0, total = 0;
 };
-WsLayout ws_layout(const Shape &r, int64_t L, int ts, bool bwd) {
+WsLayout ws_layout_n(const Shape &r, int n, bool bwd) {
     WsLayout w;
-    const int n = n_super_of(L, ts);
     const size_t bh = (size_t)r.B * r.H, SS = (size_t)r.D * r.D;
     size_t off = 0;
     if (n > 1) {
@@ -295,6 +299,80 @@ WsLayout ws_layout(const Shape &r, int64_t L, int ts, bool bwd) {
     }
     w.total = off;
     return w;
+}
+
+WsLayout ws_layout(const Shape &r, int64_t L, int ts, bool bwd) { return ws_layout_n(r, n_super_of(L, ts), bwd); }
+
+// Kept superchunk states of one segment with more than one superchunk: the
+// kernels' wsS (S_J after the forward scan), wsLg and wsSn regions.
+struct CkptLayout {
+    size_t S = 0, Lg = 0, Sn = 0, total = 0;
+};
+CkptLayout ckpt_layout_n(const Shape &r, int n) {
+    CkptLayout c;
+    if (n <= 1) return c;
+    const size_t bh = (size_t)r.B * r.H, SS = (size_t)r.D * r.D;
+    c.Lg = al(bh * n * SS * 4);
+    c.Sn = c.Lg + al(bh * n * (r.gate == SF_GATE_VECTOR ? r.D : 1) * 4);
+    c.total = c.Sn + al(bh * SS * 4);
+    return c;
+}
+CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) { return ckpt_layout_n(r, n_super_of(L, ts)); }
+
+// A chain may run as one segment: its segments are consecutive, so with the
+// superchunks cut at their ends one set of launches covers all of them, and the
+// scan hands out the boundary states.  Chosen when chunk_cost says so, a set of
+// launches and their empty first and last moments counting kSeg steps (35 us of
+// launches and prologues at 13 us a step), and no segment has more than one
+// workgroup per CU (B 4 H 32, 32 segments of 512 tokens: 4.30 ms a step segment by
+// segment, 3.65 ms in one; H 16, 8 of 4096, kept states: 1.28, 1.09; vector gate, B
+// 2 H 16, 16 of 4096: 7.23, 6.69; but the 256K layer, 480 or more a segment: 14.29,
+// 14.65).  The choice depends on the shape and the tuning alone, never on the kept
+// states, so a backward that replays and one that reads them take the same
+// superchunks; with a given ts, whose kept states are sized segment by segment, the
+// chain's have to fit that size.  Superchunks get no longer than the segments' own:
+// the gate gradient sums its token terms over a superchunk, and its rounding grows
+// with that run (H 16 at 2048 tokens instead of 256 takes 0.74 ms, but twice the
+// error).  n = 0: segment by segment.
+struct Merged {
+    int n = 0, ts = 0;
+};
+sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, const sf_tuning *t, Merged &p) {
+    p = Merged{};
+    if (n_seg < 2 || n_seg > sf::MAX_MERGED || r.L / 64 > (1 << 30)) return SF_OK;
+    constexpr double kSeg = 2.5;
+    double each = 0.0;
+    int64_t longest = 0;  // chunks of the longest superchunk the segments would take
+    size_t kept = 0;
+    for (int i = 0; i < n_seg; ++i) {
+        int ts;
+        const sf_status rc = pick_ts(r, seg_len[i], t, ts);
+        if (rc != SF_OK) return rc;
+        const int n = n_super_of(seg_len[i], ts);
+        if (seg_len[i] <= 0 || (int64_t)r.B * r.H * n > device_cus()) return SF_OK;
+        kept += ckpt_layout(r, seg_len[i], ts).total;
+        const int64_t m = std::min<int64_t>(seg_len[i], ts) / 64;
+        each += chunk_cost(r, m, n) + kSeg;
+        longest = std::max(longest, m);
+    }
+    double best = each - kSeg;
+    auto consider = [&](int64_t m) {
+        int64_t n = 0;
+        for (int i = 0; i < n_seg; ++i) n += (seg_len[i] / 64 + m - 1) / m;
+        const double cost = chunk_cost(r, m, n);
+        if (n <= (1 << 24) && cost < best - 1e-9) {
+            best = cost;
+            p.n = (int)n;
+            p.ts = (int)(m * 64);
+        }
+    };
+    if (t && t->ts != 0) {
+        consider(longest);
+        if (p.n > 0 && ckpt_layout_n(r, p.n).total > kept) p = Merged{};
+    } else {
+        for (int64_t m = 1; m <= longest; ++m) consider(m);
+    }
+    return SF_OK;
 }
 
 // ------------------------------------------------------------- kernel timing
@@ -410,7 +488,7 @@ struct Seg {
     sf_timing *tm;
 };
 
-Seg make_seg(const Shape &r, int64_t L, int ts, char *ws, bool bwd, sf_timing *tm) {
+Seg make_seg_n(const Shape &r, int64_t L, int ts, int n, char *ws, bool bwd, sf_timing *tm) {
     Seg s{};
     s.tm = tm;
     sf::SegArgs &a = s.a;
@@ -426,15 +504,33 @@ Seg make_seg(const Shape &r, int64_t L, int ts, char *ws, bool bwd, sf_timing *t
     a.n_cu = device_cus();
     a.L = L;
     a.ts = ts;
-    a.n_super = n_super_of(L, ts);
-    s.n = a.n_super;
-    WsLayout w = ws_layout(r, L, ts, bwd);
+    a.n_super = n;
+    s.n = n;
+    WsLayout w = ws_layout_n(r, n, bwd);
     if (s.n > 1) {
         a.wsS = (float *)(ws + w.S);
         a.wsE = bwd ? (float *)(ws + w.E) : nullptr;
         a.wsLg = (float *)(ws + w.Lg);
     }
     if (bwd && s.n >= 1) a.wsDot = (float *)(ws + w.Dot);
+    return s;
+}
+
+Seg make_seg(const Shape &r, int64_t L, int ts, char *ws, bool bwd, sf_timing *tm) {
+    return make_seg_n(r, L, ts, n_super_of(L, ts), ws, bwd, tm);
+}
+// the whole chain as one segment (chain_plan); the caller sets the tensors
+Seg merged_seg(const Shape &r, int32_t n_seg, const int64_t *seg_len, const Merged &mg, const float *S_bnd, char *ws,
+               bool bwd, sf_timing *tm) {
+    Seg s = make_seg_n(r, r.L, mg.ts, mg.n, ws, bwd, tm);
+    sf::SegArgs &a = s.a;
+    a.n_seg = n_seg;
+    a.S_bnd = const_cast<float *>(S_bnd);  // (the backward only reads it)
+    a.S_in = S_bnd;
+    for (int i = 0; i < n_seg; ++i) {
+        a.seg_sc[i + 1] = a.seg_sc[i] + n_super_of(seg_len[i], mg.ts);
+        a.seg_ck[i + 1] = a.seg_ck[i] + (int32_t)(seg_len[i] / 64);
+    }
     return s;
 }
 
@@ -541,21 +637,6 @@ sf_status check_segments(const Shape &r, int32_t n_seg, const int64_t *seg_len) 
     return SF_OK;
 }
 
-// Kept superchunk states of one segment with more than one superchunk: the
-// kernels' wsS (S_J after the forward scan), wsLg and wsSn regions.
-struct CkptLayout {
-    size_t S = 0, Lg = 0, Sn = 0, total = 0;
-};
-CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) {
-    CkptLayout c;
-    const int n = n_super_of(L, ts);
-    if (n <= 1) return c;
-    const size_t bh = (size_t)r.B * r.H, SS = (size_t)r.D * r.D;
-    c.Lg = al(bh * n * SS * 4);
-    c.Sn = c.Lg + al(bh * n * (r.gate == SF_GATE_VECTOR ? r.D : 1) * 4);
-    c.total = c.Sn + al(bh * SS * 4);
-    return c;
-}
 sf_status chain_ckpt(const Shape &r, int32_t n_seg, const int64_t *seg_len, const sf_tuning *t, size_t &bytes) {
     bytes = 0;
     for (int i = 0; i < n_seg; ++i) {
@@ -563,11 +644,14 @@ sf_status chain_ckpt(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
         TRY(pick_ts(r, seg_len[i], t, ts));
         bytes += ckpt_layout(r, seg_len[i], ts).total;
     }
+    Merged mg;
+    TRY(chain_plan(r, n_seg, seg_len, t, mg));
+    if (mg.n > 0) bytes = std::max(bytes, ckpt_layout_n(r, mg.n).total);
     return SF_OK;
 }
 // point a segment's superchunk-state regions into the kept-state buffer
 void use_ckpt(const Shape &r, Seg &s, char *base, bool bwd) {
-    const CkptLayout c = ckpt_layout(r, s.a.L, s.a.ts);
+    const CkptLayout c = ckpt_layout_n(r, s.n);
     if (c.total == 0) return;
     s.a.wsS = (float *)(base + c.S);
     s.a.wsLg = (float *)(base + c.Lg);
@@ -583,6 +667,9 @@ size_t chain_ws(const Shape &r, int32_t n_seg, const int64_t *seg_len, const sf_
         slot = std::max(slot, std::max(ws_layout(r, seg_len[i], ts, true).total,
                                        ws_layout(r, seg_len[i], ts, false).total));
     }
+    Merged mg;
+    if (chain_plan(r, n_seg, seg_len, t, mg) != SF_OK) return 0;
+    if (mg.n > 0) slot = std::max(slot, (ws_layout_n(r, mg.n, true).total + 1) / 2);  // both slots together
     const size_t gbnd = al((size_t)r.B * r.H * r.D * r.D * 4);
     return 2 * al(slot) + 2 * gbnd;
 }
@@ -907,6 +994,21 @@ sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
                      span(ckpt, (int64_t)kneed, "ckpt"), wsrange(ws, need)}));
     const size_t slot = (need - 2 * al((size_t)r.B * r.H * r.D * r.D * 4)) / 2;
     const int64_t SSB = (int64_t)r.B * r.H * r.D * r.D;
+    Merged mg;
+    TRY(chain_plan(r, n_seg, seg_len, tuning, mg));
+    if (mg.n > 0) {
+        Seg s = merged_seg(r, n_seg, seg_len, mg, S_bnd, (char *)ws, false, timing_of(tuning));
+        if (ckpt) use_ckpt(r, s, (char *)ckpt, false);
+        s.a.q = q;
+        s.a.k = k;
+        s.a.v = v;
+        s.a.g = g;
+        s.a.o = o;
+        s.a.S_out = S_bnd + n_seg * SSB;
+        TRY(fwd_prep(r, s, (hipStream_t)main_s));
+        TRY(fwd_scan(r, s, (hipStream_t)main_s));
+        return fwd_out(r, s, (hipStream_t)main_s);
+    }
     hipStream_t mn = (hipStream_t)main_s;
     hipStream_t ax = (aux_s && (!tuning || tuning->overlap != 0)) ? (hipStream_t)aux_s : mn;
     const bool prep_aux = ax != mn && tuning && tuning->overlap == 2;
@@ -1002,6 +1104,26 @@ sf_status sf_chain_bwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
     const size_t slot = (need - 2 * gb) / 2;
     float *gbnd[2] = {(float *)((char *)ws + 2 * slot), (float *)((char *)ws + 2 * slot + gb)};
     const int64_t SSB = (int64_t)r.B * r.H * r.D * r.D;
+    Merged mg;
+    TRY(chain_plan(r, n_seg, seg_len, tuning, mg));
+    if (mg.n > 0) {
+        Seg s = merged_seg(r, n_seg, seg_len, mg, S_bnd, (char *)ws, true, timing_of(tuning));
+        if (ckpt) use_ckpt(r, s, (char *)ckpt, true);
+        s.a.q = q;
+        s.a.k = k;
+        s.a.v = v;
+        s.a.g = g;
+        s.a.dO = dO;
+        s.a.dq = dq;
+        s.a.dk = dk;
+        s.a.dv = dv;
+        s.a.dg = dg;
+        s.a.dS_out = dS_final;
+        s.a.dS_in = dS_init;
+        TRY(bwd_prep(r, s, (hipStream_t)main_s));
+        TRY(bwd_scan(r, s, (hipStream_t)main_s));
+        return bwd_grad(r, s, (hipStream_t)main_s);
+    }
     hipStream_t mn = (hipStream_t)main_s;
     hipStream_t ax = (aux_s && (!tuning || tuning->overlap != 0)) ? (hipStream_t)aux_s : mn;
     const bool prep_aux = ax != mn && tuning && tuning->overlap == 2;

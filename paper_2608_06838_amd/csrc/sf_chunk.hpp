@@ -41,6 +41,14 @@ __device__ __forceinline__ Decode decode(const SegArgs &a, int item) {
     d.bh = item / a.n_super;
     d.b = d.bh / a.H;
     d.h = d.bh % a.H;
+    if (a.n_seg > 1) {  // a chain in one launch: superchunks are cut at the segments' ends
+        int i = 0;
+        while (i + 1 < a.n_seg && d.J >= a.seg_sc[i + 1]) ++i;
+        const int ck = a.seg_ck[i] + (d.J - a.seg_sc[i]) * (a.ts / C), end = a.seg_ck[i + 1];
+        d.tok0 = (int64_t)ck * C;
+        d.nch = end - ck < a.ts / C ? end - ck : a.ts / C;
+        return d;
+    }
     d.tok0 = (int64_t)d.J * a.ts;
     int64_t rem = a.L - d.tok0;
     d.nch = (int)((rem < a.ts ? rem : a.ts) / C);

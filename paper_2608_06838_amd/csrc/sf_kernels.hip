@@ -188,6 +188,9 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
     // batches of SB, double-buffered: the loads of the next batch are in flight
     // while the current one is applied (slot indices stay compile-time).
     constexpr int SB = 8;
+    const int64_t SSB = (int64_t)a.B * a.H * SS;
+    float *const bnd = a.n_seg > 1 ? a.S_bnd + bh * SS + e : nullptr;  // + i SSB: entering segment i
+    int si = 1;                                                       // the next segment to start, in order of J
     f32x4 S = a.S_in ? *reinterpret_cast<const f32x4 *>(a.S_in + bh * SS + e) : f32x4{0.f, 0.f, 0.f, 0.f};
     if (BWD && a.ckpt) {
         S = *reinterpret_cast<const f32x4 *>(a.wsSn + bh * SS + e);
@@ -200,6 +203,10 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
                 if (J0 + u < n) {
                     dd[slot][u] = *reinterpret_cast<const f32x4 *>(Sb + (int64_t)(J0 + u) * SS);
                     f[slot][u] = fexp2(lg[(J0 + u) * LS]);
+                    if (BWD && bnd && si < a.n_seg && J0 + u + 1 == a.seg_sc[si]) {
+                        dd[slot][u] = *reinterpret_cast<const f32x4 *>(bnd + si++ * SSB);  // the given state
+                        f[slot][u] = 0.f;
+                    }
                 }
         };
         // slot J of wsS: D_J in, S_J out (this thread reads each element before it writes it)
@@ -208,6 +215,8 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
             for (int u = 0; u < SB; ++u)
                 if (J0 + u < n) {
                     *reinterpret_cast<f32x4 *>(Sb + (int64_t)(J0 + u) * SS) = S;
+                    if (!BWD && bnd && si < a.n_seg && J0 + u == a.seg_sc[si])
+                        *reinterpret_cast<f32x4 *>(bnd + si++ * SSB) = S;
                     S = f[slot][u] * S + dd[slot][u];
                 }
         };

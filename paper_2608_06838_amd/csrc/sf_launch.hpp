@@ -8,6 +8,8 @@
 
 namespace sf {
 
+constexpr int MAX_MERGED = 32;  // segments of a chain that one set of launches can cover
+
 // One segment (or one superchunk-parallel launch over a segment).  Token
 // tensors point at the segment's first token; strides are in elements.
 struct SegArgs {
@@ -36,6 +38,13 @@ struct SegArgs {
                    // beside the superchunk states when the forward keeps them
     int32_t ckpt;  // backward: 1 when wsS, wsLg and wsSn already hold the
                    // forward's superchunk states, decays and final state
+    // a chain run as one segment: n_seg > 1 segments, segment i holding the
+    // superchunks seg_sc[i] .. seg_sc[i + 1] - 1 from chunk seg_ck[i] on (the last
+    // superchunk of each may be short); the forward scan writes the state entering
+    // segment i >= 1 to S_bnd + i B H D D, the backward's replay starts from it
+    int32_t n_seg;
+    int32_t seg_sc[MAX_MERGED + 1], seg_ck[MAX_MERGED + 1];
+    float *S_bnd;
 };
 
 // kind is an sf_kernel_id; io an sf_dtype.  The scan runs its backward form

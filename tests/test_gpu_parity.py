@@ -174,6 +174,53 @@ def test_chain_nonuniform_small(ts):
     check_chain("bf16", inp, a, seg_lens)
 
 
+@pytest.mark.parametrize("name,D,io,head_major", [("mid_bf16", 128, "bf16", False), ("mid_bf16", 64, "bf16", True),
+                                                  ("tiny_fp32", 64, "f32", False), ("vector_gate", 128, "bf16", True)])
+def test_chain_launched_as_one_segment(name, D, io, head_major):
+    """32 short segments go out as one set of launches, 33 segment by segment:
+    both against a segment call per segment, handing over S_out and dS_in, with
+    the superchunks that ts = 64 gives all three.  Only how the scans round between
+    segments differs, so the oracle's bars hold; and the 33 agree bitwise in every
+    overlap mode (their scans and preparations do run on the aux stream)."""
+    w = synth.workload(name, B=2, H=3, D=D, io=io)
+    for n in (32, 33):
+        seg_lens = [64, 192, 128] * 10 + [64] * (n - 30)
+        inp = synth.make_inputs(w, device="cpu", seed=71 + n, dS_out_std=0.1, L=sum(seg_lens))
+        g = on_gpu(inp)
+        if head_major:
+            for key in ("q", "k", "v", "g", "dO"):
+                p = (0, 2, 1, 3)[:g[key].dim()]
+                g[key] = g[key].permute(*p).contiguous().permute(*p)
+        say(f"[chain] {n} segments {name} D={D} {io} against segment calls")
+        a = run_chain(g, seg_lens, ts=64, overlap=False)
+        for mode in (True, 2) if n > 32 else ():
+            b = run_chain(g, seg_lens, ts=64, overlap=mode)
+            for key in a:
+                assert torch.equal(a[key], b[key]), (key, mode)
+        pos = np.cumsum([0] + seg_lens).tolist()
+        S = a["S_bnd"][0]
+        bnd, outs, grads = [S], [], [None] * n
+        for i in range(n):
+            part = [g[key][:, pos[i]:pos[i + 1]] for key in ("q", "k", "v", "g")]
+            o, S = sf.segment_fwd(*part, S, ts=64)
+            outs.append(o)
+            bnd.append(S)
+        dS = g["dS_out"]
+        for i in reversed(range(n)):
+            part = [g[key][:, pos[i]:pos[i + 1]] for key in ("q", "k", "v", "g")]
+            *grads[i], dS = sf.segment_bwd(*part, bnd[i], g["dO"][:, pos[i]:pos[i + 1]], dS, ts=64)
+        torch.cuda.synchronize()
+        want = dict(o=torch.cat(outs, 1), S_bnd=torch.stack(bnd), dS_in=dS)
+        for j, key in enumerate(("dq", "dk", "dv", "dg")):
+            want[key] = torch.cat([x[j] for x in grads], 1)
+        for key in want:
+            X, R = to64(a[key]), to64(want[key])
+            if a[key].dtype == torch.bfloat16:  # both rounded: a step apart (2^-7) where they fall either side
+                assert np.all(np.abs(X - R) <= 2.0 ** -7 * np.abs(R) + 2e-3 * np.sqrt(np.mean(R * R))), key
+            else:
+                assert_close(key, X, R, io)
+
+
 KEPT_CASES = [("mid_bf16", 128, "bf16", 0), ("mid_bf16", 128, "bf16", 64), ("mid_bf16", 64, "bf16", 128),
               ("tiny_fp32", 64, "f32", 128), ("vector_gate", 128, "bf16", 128), ("vector_gate", 64, "f32", 64)]
 
