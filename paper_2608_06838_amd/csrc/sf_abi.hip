@@ -295,7 +295,7 @@ WsLayout ws_layout_n(const Shape &r, int n, bool bwd) {
     }
     if (bwd && n >= 1) {
         w.Dot = off;
-        off += al(bh * n * (r.gate == SF_GATE_VECTOR ? (size_t)r.D : SS / 256) * 4);
+        off += al(bh * n * (size_t)r.D * 4);
     }
     w.total = off;
     return w;

@@ -159,26 +159,38 @@ __global__ void __launch_bounds__(64 * D / (16 * NCT), sizeof(T) == 2 ? 2 : 1) k
 }
 
 // ---------------------------------------------------------------------------
-// ST (and STB): fp32 scan over superchunk summaries, 4 state elements per
-// thread; grid = B*H*(D*D/1024).  Forward: slot J of wsS is replaced by S_J
+// The sum over each LR consecutive lanes (16, 32 or 64), in the last of them.
+template <int LR>
+__device__ __forceinline__ float row_total(float x) {
+    x += dpp_or0<0x111>(x);  // row_shr:1, 2, 4, 8
+    x += dpp_or0<0x112>(x);
+    x += dpp_or0<0x114>(x);
+    x += dpp_or0<0x118>(x);
+    if (LR >= 32) x += dpp_or0<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    if (LR >= 64) x += dpp_or0<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// ST (and STB): fp32 scan over superchunk summaries, NE state elements per
+// thread, a state row on D/NE lanes; grid = B*H*(D*D/(256*NE)).  Forward: slot J of wsS is replaced by S_J
 // (state entering superchunk J).  Backward additionally walks J downwards:
 // slot J of wsE is replaced by G_{J+1} (gradient of the state leaving J) and
-// <G_{J+1}, S_{J+1}> goes to wsDot: scalar gate as wave partials at
-// [(bh, J)][part*4 + wave], vector gate (VG) per key row at [(bh, J)][row].
-// VG: the superchunk decay is per key row (wsLg[(bh, J)][row]); a thread's 4
-// elements lie in one row.
+// <G_{J+1}, S_{J+1}> goes to wsDot per key row, [(bh, J)][row].
+// VG: the superchunk decay is per key row (wsLg[(bh, J)][row]).
 // Kept states: the forward also writes the final state to wsSn; a backward
 // with a.ckpt set finds S_J already in wsS and the final state in wsSn, and
 // runs the backward half only.
-template <bool BWD, bool VG>
-__global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
+template <int D, int NE, bool BWD, bool VG>
+__global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
+    constexpr int LR = D / NE;  // lanes per row
+    typedef float vecE __attribute__((ext_vector_type(NE)));
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int parts = D * D / 1024;
+    constexpr int parts = D * D / (SCAN_NT * NE);
     const int part = blockIdx.x % parts;
     const int64_t bh = blockIdx.x / parts;
     const int64_t SS = (int64_t)D * D;
-    const int64_t e = (int64_t)(part * SCAN_NT + tid) * 4;
-    const int row = (int)(e / D);
+    const int64_t e = (int64_t)(part * SCAN_NT + tid) * NE;
+    const int row = (part * 4 + __builtin_amdgcn_readfirstlane(w)) * (64 / LR) + (LR < 64 ? lane / LR : 0);
     const int n = a.n_super;
     float *Sb = a.wsS + bh * n * SS + e;
     const int LS = VG ? D : 1;  // wsLg entries per superchunk
@@ -187,24 +199,24 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
     // The chain over J is sequential; its loads are not.  Superchunks go in
     // batches of SB, double-buffered: the loads of the next batch are in flight
     // while the current one is applied (slot indices stay compile-time).
-    constexpr int SB = 8;
+    constexpr int SB = NE < 4 ? 16 : 8;
     const int64_t SSB = (int64_t)a.B * a.H * SS;
     float *const bnd = a.n_seg > 1 ? a.S_bnd + bh * SS + e : nullptr;  // + i SSB: entering segment i
     int si = 1;                                                       // the next segment to start, in order of J
-    f32x4 S = a.S_in ? *reinterpret_cast<const f32x4 *>(a.S_in + bh * SS + e) : f32x4{0.f, 0.f, 0.f, 0.f};
+    vecE S = a.S_in ? *reinterpret_cast<const vecE *>(a.S_in + bh * SS + e) : vecE(0.f);
     if (BWD && a.ckpt) {
-        S = *reinterpret_cast<const f32x4 *>(a.wsSn + bh * SS + e);
+        S = *reinterpret_cast<const vecE *>(a.wsSn + bh * SS + e);
     } else {
-        f32x4 dd[2][SB];
+        vecE dd[2][SB];
         float f[2][SB];
         auto fetch = [&](int slot, int J0) {
 #pragma unroll
             for (int u = 0; u < SB; ++u)
                 if (J0 + u < n) {
-                    dd[slot][u] = *reinterpret_cast<const f32x4 *>(Sb + (int64_t)(J0 + u) * SS);
+                    dd[slot][u] = *reinterpret_cast<const vecE *>(Sb + (int64_t)(J0 + u) * SS);
                     f[slot][u] = fexp2(lg[(J0 + u) * LS]);
                     if (BWD && bnd && si < a.n_seg && J0 + u + 1 == a.seg_sc[si]) {
-                        dd[slot][u] = *reinterpret_cast<const f32x4 *>(bnd + si++ * SSB);  // the given state
+                        dd[slot][u] = *reinterpret_cast<const vecE *>(bnd + si++ * SSB);  // the given state
                         f[slot][u] = 0.f;
                     }
                 }
@@ -214,9 +226,9 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
 #pragma unroll
             for (int u = 0; u < SB; ++u)
                 if (J0 + u < n) {
-                    *reinterpret_cast<f32x4 *>(Sb + (int64_t)(J0 + u) * SS) = S;
+                    *reinterpret_cast<vecE *>(Sb + (int64_t)(J0 + u) * SS) = S;
                     if (!BWD && bnd && si < a.n_seg && J0 + u == a.seg_sc[si])
-                        *reinterpret_cast<f32x4 *>(bnd + si++ * SSB) = S;
+                        *reinterpret_cast<vecE *>(bnd + si++ * SSB) = S;
                     S = f[slot][u] * S + dd[slot][u];
                 }
         };
@@ -229,23 +241,22 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
         }
     }
     if constexpr (!BWD) {
-        if (a.S_out) *reinterpret_cast<f32x4 *>(a.S_out + bh * SS + e) = S;
-        if (a.wsSn) *reinterpret_cast<f32x4 *>(a.wsSn + bh * SS + e) = S;
+        if (a.S_out) *reinterpret_cast<vecE *>(a.S_out + bh * SS + e) = S;
+        if (a.wsSn) *reinterpret_cast<vecE *>(a.wsSn + bh * SS + e) = S;
     } else {
-        const int ndot = VG ? D : D * D / 256;
         float *Eb = a.wsE + bh * n * SS + e;
-        f32x4 G = a.dS_out ? *reinterpret_cast<const f32x4 *>(a.dS_out + bh * SS + e)
-                           : f32x4{0.f, 0.f, 0.f, 0.f};
-        f32x4 Sn = S;  // S_{J+1} for J = n-1 is S_out
-        f32x4 E[2][SB], Sj[2][SB];
+        vecE G = a.dS_out ? *reinterpret_cast<const vecE *>(a.dS_out + bh * SS + e)
+                           : vecE(0.f);
+        vecE Sn = S;  // S_{J+1} for J = n-1 is S_out
+        vecE E[2][SB], Sj[2][SB];
         float f[2][SB];
         // batch starting at J0 going down: superchunks J0, J0-1, ..., J0-SB+1
         auto fetch = [&](int slot, int J0) {
 #pragma unroll
             for (int u = 0; u < SB; ++u)
                 if (J0 - u >= 0) {
-                    E[slot][u] = *reinterpret_cast<const f32x4 *>(Eb + (int64_t)(J0 - u) * SS);
-                    Sj[slot][u] = *reinterpret_cast<const f32x4 *>(Sb + (int64_t)(J0 - u) * SS);
+                    E[slot][u] = *reinterpret_cast<const vecE *>(Eb + (int64_t)(J0 - u) * SS);
+                    Sj[slot][u] = *reinterpret_cast<const vecE *>(Sb + (int64_t)(J0 - u) * SS);
                     f[slot][u] = fexp2(lg[(J0 - u) * LS]);
                 }
         };
@@ -254,16 +265,12 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
             for (int u = 0; u < SB; ++u)
                 if (J0 - u >= 0) {
                     const int J = J0 - u;
-                    float p = G[0] * Sn[0] + G[1] * Sn[1] + G[2] * Sn[2] + G[3] * Sn[3];
-                    if constexpr (!VG) {
-                        p = lane_value(wave_scan_dpp(p), 63);
-                        if (lane == 0) a.wsDot[(bh * n + J) * ndot + part * 4 + w] = p;
-                    } else {
-                        // the D/4 threads of one row are consecutive lanes
-                        for (int o = D / 8; o >= 1; o >>= 1) p += __shfl_xor(p, o, 64);
-                        if ((lane & (D / 4 - 1)) == 0) a.wsDot[(bh * n + J) * ndot + row] = p;
-                    }
-                    *reinterpret_cast<f32x4 *>(Eb + (int64_t)J * SS) = G;
+                    float p = 0.f;
+#pragma unroll
+                    for (int x = 0; x < NE; ++x) p += G[x] * Sn[x];
+                    p = row_total<LR>(p);
+                    if ((lane & (LR - 1)) == LR - 1) a.wsDot[(bh * n + J) * D + row] = p;
+                    *reinterpret_cast<vecE *>(Eb + (int64_t)J * SS) = G;
                     G = f[slot][u] * G + E[slot][u];
                     Sn = Sj[slot][u];
                 }
@@ -275,7 +282,7 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a, int D) {
             if (J0 - 2 * SB >= 0) fetch(0, J0 - 2 * SB);
             if (J0 - SB >= 0) apply(1, J0 - SB);
         }
-        if (a.dS_in) *reinterpret_cast<f32x4 *>(a.dS_in + bh * SS + e) = G;
+        if (a.dS_in) *reinterpret_cast<vecE *>(a.dS_in + bh * SS + e) = G;
     }
 }
 
@@ -651,10 +658,12 @@ __global__ void __launch_bounds__(64 * D / (16 * NCT * CS), sizeof(T) == 2 ? 2 :
                     }
             }
             p = wave_sum(p);
-            const int ndot = D * D / 256;
+            const int ndot = D;
             float *dot = a.wsDot + (int64_t)d.bh * ndot;
             if (lane == 0) dot[w] = p;
-            if (w == 0 && lane >= NW && lane < ndot) dot[lane] = 0.f;
+            if (w == 0)
+                for (int x = lane; x < ndot; x += 64)
+                    if (x >= NW) dot[x] = 0.f;
         }
     }
 }
@@ -731,7 +740,7 @@ __global__ void __launch_bounds__(128 * D / (16 * NCT)) k_bwd_dkv(SegArgs a) {
     const float *gp = a.g + go;
     float *dgp = a.dg + go;
     const int64_t SS = (int64_t)D * D;
-    const int ndot = D * D / 256;
+    const int ndot = D;
     // role operands: the B side of the decayed-state product, the own-column
     // transposed tile of the intra-chunk product and of the G update, the score
     // tile, and the shared operand of the G update
@@ -762,7 +771,7 @@ __global__ void __launch_bounds__(128 * D / (16 * NCT)) k_bwd_dkv(SegArgs a) {
     float carry = 0.f;  // wave DGW: decay gradient carried in from later tokens
     if (w == DGW) {
         const float *dot = a.wsDot + ((int64_t)d.bh * a.n_super + d.J) * ndot;
-        carry = wave_sum(lane < ndot ? dot[lane] : 0.f);
+        carry = wave_sum(dot[lane] + (ndot > 64 ? dot[lane + 64] : 0.f));
     }
     // score tiles read by the dv/dk products but above the diagonal stay zero
     for (int e = tid; e < 512; e += NT) {
@@ -1049,7 +1058,7 @@ __global__ void __launch_bounds__(64 * D / 16) k_bwd_dkv_wg(SegArgs a) {
     const float *gp = a.g + go;
     float *dgp = a.dg + go;
     const int64_t SS = (int64_t)D * D;
-    const int ndot = D * D / 256;
+    const int ndot = D;
     // role operands: the own-column transposed tile of the intra-chunk product
     // and of the G update, the shared operand of the G update, and the t side
     // of the score product (A = Q K^T, dA = dO V^T); sX is the other side of
@@ -1075,7 +1084,7 @@ __global__ void __launch_bounds__(64 * D / 16) k_bwd_dkv_wg(SegArgs a) {
     float carry = 0.f;  // k role, wave 0: decay gradient carried in from later tokens
     if (kside && w == 0) {
         const float *dot = a.wsDot + ((int64_t)d.bh * a.n_super + d.J) * ndot;
-        carry = wave_sum(lane < ndot ? dot[lane] : 0.f);
+        carry = wave_sum(dot[lane] + (ndot > 64 ? dot[lane + 64] : 0.f));
     }
     // score tile entries read by the products but above the diagonal stay zero
     for (int e = tid; e < 512; e += NT) {
@@ -1254,8 +1263,21 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
     const dim3 grid((unsigned)((int64_t)a.B * a.H * a.n_super));
     constexpr int NTP = 64 * D / (16 * SF_NCT_PREP);
     constexpr int NTW = 64 * D / (16 * SF_NCT_WALK);
+    constexpr int NT1 = 64 * D / 16;
+    // up to one item per CU there is no second workgroup to cover a wave's waits:
+    // twice the waves, one column tile each, instead of two (bf16, d = 128: prep,
+    // 220 items of 6 chunks 30.1 -> 18.0 us, but 1000 of 66 165 -> 179; dq walk, 128
+    // of 8 53.5 -> 49.0, 256 of 4 46.1 -> 43.2; the output walk is the same either
+    // way, 43; fp32, d = 64, 32 of 1: prep 9.9 -> 8.4, output walk 16.0 -> 12.8, dq
+    // walk 16.7 -> 13.8; fp32 at d = 128 keeps its one column split)
+    const bool alone = (sizeof(T) == 2 || D == 64) && (int64_t)grid.x <= (int64_t)a.n_cu;
     switch (kind) {
-    case SF_K_FWD_PREP: hipExtLaunchKernelGGL((k_prep<T, D, SF_NCT_PREP, false>), grid, dim3(NTP), 0, s, e0, e1, 0, a); break;
+    case SF_K_FWD_PREP:
+        if (alone)
+            hipExtLaunchKernelGGL((k_prep<T, D, 1, false>), grid, dim3(NT1), 0, s, e0, e1, 0, a);
+        else
+            hipExtLaunchKernelGGL((k_prep<T, D, SF_NCT_PREP, false>), grid, dim3(NTP), 0, s, e0, e1, 0, a);
+        break;
     case SF_K_FWD_OUT:
         // a launch that would leave half the CUs idle splits the state's columns
         // over two workgroups per item (scan-bound workload: 5.15 -> 4.98 ms per
@@ -1263,22 +1285,25 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
         if (sizeof(T) == 2 && D == 128 && 2 * (int64_t)grid.x <= (int64_t)a.n_cu) {
             hipExtLaunchKernelGGL((k_walk<T, D, 1, false, 2>), dim3((grid.x + 7) / 8 * 16), dim3(64 * D / 32), 0, s, e0,
                                   e1, 0, a);
+        } else if (D == 64 && alone) {
+            hipExtLaunchKernelGGL((k_walk<T, D, 1, false>), grid, dim3(NT1), 0, s, e0, e1, 0, a);
         } else {
             hipExtLaunchKernelGGL((k_walk<T, D, SF_NCT_WALK, false>), grid, dim3(NTW), 0, s, e0, e1, 0, a);
         }
         break;
     case SF_K_BWD_PREP:  // the replay of D_J (the forward's prep), skipped for kept states, then E_J
-        if (!a.ckpt)
+        if (!a.ckpt && alone && 2 * (int64_t)grid.x <= (int64_t)a.n_cu)
+            hipExtLaunchKernelGGL((k_prep_bwd<T, D, 1>), dim3(2 * grid.x), dim3(NT1), 0, s, e0, e1, 0, a);
+        else if (!a.ckpt)
             hipExtLaunchKernelGGL((k_prep_bwd<T, D, SF_NCT_PREP>), dim3(2 * grid.x), dim3(NTP), 0, s, e0, e1, 0, a);
+        else if (alone)
+            hipExtLaunchKernelGGL((k_prep<T, D, 1, true>), grid, dim3(NT1), 0, s, e0, e1, 0, a);
         else
             hipExtLaunchKernelGGL((k_prep<T, D, SF_NCT_PREP, true>), grid, dim3(NTP), 0, s, e0, e1, 0, a);
         break;
     case SF_K_BWD_DQ:
-        // up to one item per CU there is no second workgroup to cover a wave's
-        // waits: eight waves of one column tile instead of four of two (128 items
-        // of 8 chunks 53.5 -> 49.0 us, 256 of 4 chunks 46.1 -> 43.2)
-        if (sizeof(T) == 2 && D == 128 && (int64_t)grid.x <= (int64_t)a.n_cu)
-            hipExtLaunchKernelGGL((k_walk<T, D, 1, true>), grid, dim3(64 * D / 16), 0, s, e0, e1, 0, a);
+        if (alone)
+            hipExtLaunchKernelGGL((k_walk<T, D, 1, true>), grid, dim3(NT1), 0, s, e0, e1, 0, a);
         else
             hipExtLaunchKernelGGL((k_walk<T, D, SF_NCT_WALK, true>), grid, dim3(NTW), 0, s, e0, e1, 0, a);
         break;
@@ -1300,16 +1325,29 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
     return hipGetLastError();
 }
 
+// Four elements a thread, whole 16-byte accesses, where that gives a workgroup
+// per CU; a row per wave (fewer elements each, twice the superchunks in flight)
+// where it would not: a scan's time is then its loads' latency alone.
+// (256 CUs, forward and backward scan: 24 workgroups 82.9 us, 96 of a row per wave
+// 66.2; 8 and 32: 18.8, 13.2; but 256 and 512: 201.4, 207.7; 512 and 1024: 478, 626.)
+template <int D, bool BWD, bool VG>
+static void launch_scan(const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int64_t wg4 = (int64_t)a.B * a.H * (D * D / 1024);
+    if (wg4 >= a.n_cu)
+        hipExtLaunchKernelGGL((k_scan<D, 4, BWD, VG>), dim3((unsigned)wg4), dim3(SCAN_NT), 0, s, e0, e1, 0, a);
+    else
+        hipExtLaunchKernelGGL((k_scan<D, D / 64, BWD, VG>), dim3((unsigned)(wg4 * 256 / D)), dim3(SCAN_NT), 0, s, e0,
+                              e1, 0, a);
+}
+template <int D>
+static void launch_scan(const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (a.vec) a.wsE ? launch_scan<D, true, true>(a, s, e0, e1) : launch_scan<D, false, true>(a, s, e0, e1);
+    else a.wsE ? launch_scan<D, true, false>(a, s, e0, e1) : launch_scan<D, false, false>(a, s, e0, e1);
+}
+
 hipError_t launch_kernel(int kind, int io, int D, const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (kind == SF_K_SCAN) {
-        const dim3 grid((unsigned)((int64_t)a.B * a.H * (D * D / 1024)));
-        if (a.vec) {
-            if (a.wsE) hipExtLaunchKernelGGL((k_scan<true, true>), grid, dim3(SCAN_NT), 0, s, e0, e1, 0, a, D);
-            else hipExtLaunchKernelGGL((k_scan<false, true>), grid, dim3(SCAN_NT), 0, s, e0, e1, 0, a, D);
-        } else {
-            if (a.wsE) hipExtLaunchKernelGGL((k_scan<true, false>), grid, dim3(SCAN_NT), 0, s, e0, e1, 0, a, D);
-            else hipExtLaunchKernelGGL((k_scan<false, false>), grid, dim3(SCAN_NT), 0, s, e0, e1, 0, a, D);
-        }
+        D == 64 ? launch_scan<64>(a, s, e0, e1) : launch_scan<128>(a, s, e0, e1);
         return hipGetLastError();
     }
     if (a.vec) return launch_kernel_vg(kind, io, D, a, s, e0, e1);

@@ -32,8 +32,8 @@ struct SegArgs {
     float *wsS;    // [B][H][n_super][D][D]: D_J, replaced by S_J by the scan
     float *wsE;    // [B][H][n_super][D][D]: E_J, replaced by G_{J+1} (backward only)
     float *wsLg;   // [B][H][n_super] (vector gate: [..][D]): log2 of the superchunk decay
-    float *wsDot;  // [B][H][n_super][D*D/256]: partials of <G_{J+1}, S_{J+1}>;
-                   // vector gate: [B][H][n_super][D], the per-key-row sums
+    float *wsDot;  // [B][H][n_super][D]: <G_{J+1}, S_{J+1}> per key row (scalar
+                   // gate, one superchunk: D partials of it)
     float *wsSn;   // [B][H][D][D] or NULL: the state leaving the segment, kept
                    // beside the superchunk states when the forward keeps them
     int32_t ckpt;  // backward: 1 when wsS, wsLg and wsSn already hold the

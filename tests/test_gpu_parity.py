@@ -75,6 +75,19 @@ def test_bf16_segment_paths(D, ts):
     check_all("bf16", got, oracle_run(inp), inp)
 
 
+@pytest.mark.parametrize("name,D,io", [("mid_bf16", 64, "bf16"), ("tiny_fp32", 64, "f32"), ("vector_gate", 64, "bf16"),
+                                       ("vector_gate", 64, "f32"), ("mid_bf16", 128, "bf16")])
+@pytest.mark.parametrize("ts", [64, 128])
+def test_more_items_than_cus(name, D, io, ts):
+    """B=1, H=88, L=192: 264 or 176 items and, at d = 64, 352 scan workgroups on 256
+    CUs.  Launches of more items than CUs, and of a scan workgroup per CU, take other
+    kernel forms than the small cases do; the scans' rows are then shared out
+    otherwise too."""
+    w = synth.workload(name, B=1, H=88, D=D, io=io)
+    inp, got = seg_case(w, 192, ts, seed=83 + D + ts, s_in_std=0.1)
+    check_all(io, got, oracle_run(inp), inp)
+
+
 @pytest.mark.parametrize("ts", [1024, 128, 192])
 def test_fp32_d128_segment(ts):
     """fp32 I/O at d = 128 (scalar gate; its dk/dv walk runs as two workgroups
