@@ -246,6 +246,14 @@ double chunk_cost(const Shape &r, int64_t m, int64_t ns) {
     return cost;
 }
 
+// the shortest superchunk longer than m that splits nc chunks into fewer parts
+// (past nc after the whole): every distinct split in 2 sqrt(nc) steps, where trying
+// each length took 20 us of host time for 64K tokens, twice or more a call
+int64_t next_split(int64_t nc, int64_t m) {
+    const int64_t ns = (nc + m - 1) / m;
+    return ns <= 1 ? nc + 1 : (nc + ns - 2) / (ns - 1);
+}
+
 sf_status pick_ts(const Shape &r, int64_t L, const sf_tuning *t, int &ts) {
     if (t && t->ts != 0) {
         if (t->ts < 64 || t->ts % 64) return fail(SF_E_SHAPE, "tuning.ts must be a positive multiple of 64");
@@ -260,9 +268,8 @@ sf_status pick_ts(const Shape &r, int64_t L, const sf_tuning *t, int &ts) {
     }
     double best = 1e300;
     int64_t best_m = nc;
-    for (int64_t m = 1; m <= nc; ++m) {  // chunks per superchunk
+    for (int64_t m = 1; m <= nc; m = next_split(nc, m)) {  // chunks per superchunk
         const int64_t ns = (nc + m - 1) / m;
-        if (m > 1 && (nc + m - 2) / (m - 1) == ns) continue;  // same split as a shorter m
         const double cost = chunk_cost(r, m, ns);
         if (cost < best - 1e-9) {
             best = cost;
@@ -1316,9 +1323,8 @@ sf_status gdn_pick_ts(const Shape &r, const sf_tuning *t, int &ts) {
     const double kScan = 0.2 * std::max(1.0, (double)bh * (r.D / 16) / (0.55 * cu));
     double best = 1e300;
     int64_t best_m = nc;
-    for (int64_t m = 1; m <= nc; ++m) {
+    for (int64_t m = 1; m <= nc; m = next_split(nc, m)) {
         const int64_t ns = (nc + m - 1) / m;
-        if (m > 1 && (nc + m - 2) / (m - 1) == ns) continue;
         const double step = (double)m * gdn_step_factor((double)(bh * ns), cu);
         const double cost = ns > 1 ? step + kScan * (double)(ns - 1) + kLaunch : 0.6 * step;
         if (cost < best - 1e-9) {
