@@ -1238,7 +1238,10 @@ sf_status sf_conv_fwd(const sf_conv_shape *shape, const void *x, const float *w,
     a.nTB = (int32_t)conv_nblocks(r, false);
     a.sx_b = r.sx_b;
     a.sx_l = r.sx_l;
-    if (a.nTB > 65535) return fail(SF_E_UNSUPPORTED, "L too large for one call (%lld tokens)", (long long)r.L);
+    // whole runs put their blocks on grid.y, which ends at 65535; shortened runs lie on
+    // a flat grid, so their larger number of blocks is not held to it
+    if (r.L > 65535 * (int64_t)256)
+        return fail(SF_E_UNSUPPORTED, "L too large for one call (%lld tokens)", (long long)r.L);
     return conv_run(SF_K_CONV_FWD, false, a, (hipStream_t)stream, timing_of(tuning));
 }
 

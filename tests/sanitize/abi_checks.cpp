@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 
+#include "launch_stubs.hpp"
 #include "stateflow.h"
 
 static int failures = 0;
@@ -102,6 +103,24 @@ int main() {
     c.C = 64;
     EXPECT(sf_conv_bwd(&c, P(1), F(2), F(3), P(4), F(5), P(6), F(7), F(8), P(9), 16, nullptr, nullptr) ==
            SF_E_WORKSPACE);
+    // few channels and many tokens: shortened runs may come in more than 65535 blocks,
+    // whole ones (and so the call) may not
+    for (int ch : {8, 16, 24}) {
+        sf::LaunchRecord rec;
+        sf::launch_record = &rec;
+        c.B = 1, c.C = ch;
+        for (int64_t L : {int64_t(524280), int64_t(524296), int64_t(1 << 20), int64_t(65535) * 256}) {
+            c.L = L;
+            EXPECT(sf_conv_fwd(&c, P(1), F(2), F(3), P(4), F(5), nullptr, nullptr) == SF_OK);
+            const sf::ConvArgs &a = rec.conv.back();
+            EXPECT(a.nTB * a.T >= L && (a.nTB - 1) * a.T < L);
+            EXPECT(a.T == 256 ? a.nTB <= 65535 : a.T >= 8 && a.T < 256);
+        }
+        EXPECT(rec.conv.size() == 4);
+        c.L = int64_t(65535) * 256 + 1;
+        EXPECT(sf_conv_fwd(&c, P(1), F(2), F(3), P(4), F(5), nullptr, nullptr) == SF_E_UNSUPPORTED);
+        sf::launch_record = nullptr;
+    }
     // gated delta rule
     EXPECT(sf_gdn_fwd(&s, P(1), P(2), P(3), F(4), F(5), nullptr, P(1), F(7), nullptr, P(8), 1ull << 40, nullptr,
                       nullptr) == SF_E_ALIAS);

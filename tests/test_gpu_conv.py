@@ -186,3 +186,14 @@ def test_conv_run_splits(io, C, L):
 
     ref = run_oracle({k: pick(v).cpu() for k, v in inp.items()}, "silu")
     compare({k: pick(v) for k, v in got.items()}, ref, io, W)
+
+
+@pytest.mark.parametrize("io,C", [("f32", 8), ("bf16", 16)])
+def test_conv_few_channels_many_tokens(io, C):
+    """524297 tokens of one or two channel groups: the forward's runs of 8 tokens
+    come in more than 65535 blocks."""
+    L, W = 524297, 4
+    say(f"[conv] few channels io={io} C={C} L={L}")
+    inp = synth.make_conv_inputs(1, L, C, W, io=io, seed=3700 + C, device=DEV)
+    cpu = {k: (v.cpu() if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    compare(run_gpu(inp, "silu"), run_oracle(cpu, "silu"), io, W)
