@@ -180,7 +180,10 @@ __device__ __forceinline__ float row_total(float x) {
 // Kept states: the forward also writes the final state to wsSn; a backward
 // with a.ckpt set finds S_J already in wsS and the final state in wsSn, and
 // runs the backward half only.
-template <int D, int NE, bool BWD, bool VG>
+// MG: a chain in one launch; its forward writes the states entering the segments
+// and its backward's replay starts each segment from the given one.  (A form of its
+// own: tests of the segment ends in every scan cost 1.2 of 69 us at 32 items.)
+template <int D, int NE, bool BWD, bool VG, bool MG>
 __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
     constexpr int LR = D / NE;  // lanes per row
     typedef float vecE __attribute__((ext_vector_type(NE)));
@@ -201,8 +204,8 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
     // while the current one is applied (slot indices stay compile-time).
     constexpr int SB = NE < 4 ? 16 : 8;
     const int64_t SSB = (int64_t)a.B * a.H * SS;
-    float *const bnd = a.n_seg > 1 ? a.S_bnd + bh * SS + e : nullptr;  // + i SSB: entering segment i
-    int si = 1;                                                       // the next segment to start, in order of J
+    float *const bnd = MG ? a.S_bnd + bh * SS + e : nullptr;  // + i SSB: entering segment i
+    int si = 1;                                              // the next segment to start, in order of J
     vecE S = a.S_in ? *reinterpret_cast<const vecE *>(a.S_in + bh * SS + e) : vecE(0.f);
     if (BWD && a.ckpt) {
         S = *reinterpret_cast<const vecE *>(a.wsSn + bh * SS + e);
@@ -215,9 +218,9 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
                 if (J0 + u < n) {
                     dd[slot][u] = *reinterpret_cast<const vecE *>(Sb + (int64_t)(J0 + u) * SS);
                     f[slot][u] = fexp2(lg[(J0 + u) * LS]);
-                    if (BWD && bnd && si < a.n_seg && J0 + u + 1 == a.seg_sc[si]) {
+                    if (BWD && MG && si < a.n_seg && J0 + u + 1 == a.seg_sc[si]) {
                         dd[slot][u] = *reinterpret_cast<const vecE *>(bnd + si++ * SSB);  // the given state
-                        f[slot][u] = 0.f;
+                        f[slot][u] = -1.f;                                                // (no decay: it replaces S)
                     }
                 }
         };
@@ -227,9 +230,10 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
             for (int u = 0; u < SB; ++u)
                 if (J0 + u < n) {
                     *reinterpret_cast<vecE *>(Sb + (int64_t)(J0 + u) * SS) = S;
-                    if (!BWD && bnd && si < a.n_seg && J0 + u == a.seg_sc[si])
+                    if (!BWD && MG && si < a.n_seg && J0 + u == a.seg_sc[si])
                         *reinterpret_cast<vecE *>(bnd + si++ * SSB) = S;
-                    S = f[slot][u] * S + dd[slot][u];
+                    // a given state is taken, not added to 0 S, which is NaN where S is not finite
+                    S = BWD && MG && f[slot][u] < 0.f ? dd[slot][u] : f[slot][u] * S + dd[slot][u];
                 }
         };
         fetch(0, 0);
@@ -1330,19 +1334,23 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
 // where it would not: a scan's time is then its loads' latency alone.
 // (256 CUs, forward and backward scan: 24 workgroups 82.9 us, 96 of a row per wave
 // 66.2; 8 and 32: 18.8, 13.2; but 256 and 512: 201.4, 207.7; 512 and 1024: 478, 626.)
-template <int D, bool BWD, bool VG>
+template <int D, bool BWD, bool VG, bool MG>
 static void launch_scan(const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int64_t wg4 = (int64_t)a.B * a.H * (D * D / 1024);
     if (wg4 >= a.n_cu)
-        hipExtLaunchKernelGGL((k_scan<D, 4, BWD, VG>), dim3((unsigned)wg4), dim3(SCAN_NT), 0, s, e0, e1, 0, a);
+        hipExtLaunchKernelGGL((k_scan<D, 4, BWD, VG, MG>), dim3((unsigned)wg4), dim3(SCAN_NT), 0, s, e0, e1, 0, a);
     else
-        hipExtLaunchKernelGGL((k_scan<D, D / 64, BWD, VG>), dim3((unsigned)(wg4 * 256 / D)), dim3(SCAN_NT), 0, s, e0,
+        hipExtLaunchKernelGGL((k_scan<D, D / 64, BWD, VG, MG>), dim3((unsigned)(wg4 * 256 / D)), dim3(SCAN_NT), 0, s, e0,
                               e1, 0, a);
+}
+template <int D, bool VG, bool MG>
+static void launch_scan(const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    a.wsE ? launch_scan<D, true, VG, MG>(a, s, e0, e1) : launch_scan<D, false, VG, MG>(a, s, e0, e1);
 }
 template <int D>
 static void launch_scan(const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (a.vec) a.wsE ? launch_scan<D, true, true>(a, s, e0, e1) : launch_scan<D, false, true>(a, s, e0, e1);
-    else a.wsE ? launch_scan<D, true, false>(a, s, e0, e1) : launch_scan<D, false, false>(a, s, e0, e1);
+    if (a.n_seg > 1) a.vec ? launch_scan<D, true, true>(a, s, e0, e1) : launch_scan<D, false, true>(a, s, e0, e1);
+    else a.vec ? launch_scan<D, true, false>(a, s, e0, e1) : launch_scan<D, false, false>(a, s, e0, e1);
 }
 
 hipError_t launch_kernel(int kind, int io, int D, const SegArgs &a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

@@ -234,6 +234,45 @@ def test_chain_launched_as_one_segment(name, D, io, head_major):
                 assert_close(key, X, R, io)
 
 
+def launches(fn, *kernels):
+    """(fn(timing), launches per kernel kind of that call)"""
+    t = sf.KernelTimer(kernels, capacity=512)
+    try:
+        out = fn(t)
+        return out, {k: n for k, (_, n) in t.read().items()}
+    finally:
+        t.close()
+
+
+@pytest.mark.parametrize("name,D,io", [("mid_bf16", 128, "bf16"), ("tiny_fp32", 64, "f32"), ("vector_gate", 128, "bf16")])
+def test_chain_replay_starts_from_the_given_states(name, D, io):
+    """A backward over several segments in one set of launches replays each segment
+    from the S_bnd it is given: infinities in the first segment's v leave every
+    gradient of the later segments, and the gradient of the initial state (which
+    depends on no v), bitwise as they were."""
+    w = synth.workload(name, B=1, H=3, D=D, io=io)
+    seg_lens = [128, 64, 192, 128]
+    inp = synth.make_inputs(w, device="cpu", seed=91 + D, dS_out_std=0.1, L=sum(seg_lens))
+    g = on_gpu(inp)
+    say(f"[chain] replay from the given states {name} D={D} {io}")
+    _, S_bnd = sf.chain_fwd(g["q"], g["k"], g["v"], g["g"], seg_lens, g["S_in"], ts=64, overlap=False)
+
+    def bwd(v):
+        out, n = launches(lambda t: sf.chain_bwd(g["q"], g["k"], v, g["g"], seg_lens, S_bnd, g["dO"], g["dS_out"],
+                                                 ts=64, overlap=False, timing=t), "scan")
+        assert n == {"scan": 1}  # one set of launches
+        return out
+
+    bad = g["v"].clone()
+    bad[:, 5, :, 3] = float("inf")
+    a, b = bwd(g["v"]), bwd(bad)
+    assert not torch.isfinite(b[0][:, :seg_lens[0]]).all()
+    for x, y in zip(a[:4], b[:4]):
+        assert torch.isfinite(x).all()
+        assert torch.equal(x[:, seg_lens[0]:], y[:, seg_lens[0]:])
+    assert torch.equal(a[4], b[4])
+
+
 KEPT_CASES = [("mid_bf16", 128, "bf16", 0), ("mid_bf16", 128, "bf16", 64), ("mid_bf16", 64, "bf16", 128),
               ("tiny_fp32", 64, "f32", 128), ("vector_gate", 128, "bf16", 128), ("vector_gate", 64, "f32", 64)]
 
