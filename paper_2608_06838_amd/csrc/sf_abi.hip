@@ -337,19 +337,23 @@ CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) { return ckpt_layout_n
 // 14.65).  The choice depends on the shape and the tuning alone, never on the kept
 // states, so a backward that replays and one that reads them take the same
 // superchunks; with a given ts, whose kept states are sized segment by segment, the
-// chain's have to fit that size.  Superchunks get no longer than the segments' own:
-// the gate gradient sums its token terms over a superchunk, and its rounding grows
-// with that run (H 16 at 2048 tokens instead of 256: 0.74 ms, but over 1.5 times the
-// error).  n = 0: segment by segment.
+// chain's have to fit that size.  No segment gets longer superchunks than it would
+// take alone: the gate gradient sums its token terms over a superchunk, and its
+// rounding grows with that run (H 16 at 2048 tokens instead of 256: 0.74 ms, but
+// over 1.5 times the error; H 6, 1984 + 1088 + 4160 with one length for all: the
+// vector gate 215 us instead of 220, the scalar gate's dg 5.8e-6 off instead of
+// 5.4e-6; H 5, 10432 + 896: 201 us instead of 255, segment by segment 287).
+// n = 0: segment by segment.
 struct Merged {
-    int n = 0, ts = 0;
+    int n = 0, ts = 0;            // superchunks of a head, tokens of the longest
+    int32_t m[sf::MAX_MERGED]{};  // chunks per superchunk of each segment
 };
 sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, const sf_tuning *t, Merged &p) {
     p = Merged{};
     if (n_seg < 2 || n_seg > sf::MAX_MERGED || r.L / 64 > (1 << 30)) return SF_OK;
     constexpr double kSeg = 2.5;
     double each = 0.0;
-    int64_t longest = 0;  // chunks of the longest superchunk the segments would take
+    int64_t longest = 0, own[sf::MAX_MERGED];  // chunks per superchunk that each segment would take
     size_t kept = 0;
     for (int i = 0; i < n_seg; ++i) {
         int ts;
@@ -358,14 +362,17 @@ sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
         const int n = n_super_of(seg_len[i], ts);
         if (seg_len[i] <= 0 || (int64_t)r.B * r.H * n > device_cus()) return SF_OK;
         kept += ckpt_layout(r, seg_len[i], ts).total;
-        const int64_t m = std::min<int64_t>(seg_len[i], ts) / 64;
-        each += chunk_cost(r, m, n) + kSeg;
-        longest = std::max(longest, m);
+        own[i] = std::min<int64_t>(seg_len[i], ts) / 64;
+        each += chunk_cost(r, own[i], n) + kSeg;
+        longest = std::max(longest, own[i]);
     }
     double best = each - kSeg;
     auto consider = [&](int64_t m) {
         int64_t n = 0;
-        for (int i = 0; i < n_seg; ++i) n += (seg_len[i] / 64 + m - 1) / m;
+        for (int i = 0; i < n_seg; ++i) {
+            const int64_t mi = std::min(m, own[i]);
+            n += (seg_len[i] / 64 + mi - 1) / mi;
+        }
         const double cost = chunk_cost(r, m, n);
         if (n <= (1 << 24) && cost < best - 1e-9) {
             best = cost;
@@ -379,6 +386,7 @@ sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
     } else {
         for (int64_t m = 1; m <= longest; ++m) consider(m);
     }
+    for (int i = 0; i < n_seg; ++i) p.m[i] = (int32_t)std::min<int64_t>(p.ts / 64, own[i]);
     return SF_OK;
 }
 
@@ -535,8 +543,10 @@ Seg merged_seg(const Shape &r, int32_t n_seg, const int64_t *seg_len, const Merg
     a.S_bnd = const_cast<float *>(S_bnd);  // (the backward only reads it)
     a.S_in = S_bnd;
     for (int i = 0; i < n_seg; ++i) {
-        a.seg_sc[i + 1] = a.seg_sc[i] + n_super_of(seg_len[i], mg.ts);
-        a.seg_ck[i + 1] = a.seg_ck[i] + (int32_t)(seg_len[i] / 64);
+        const int32_t nc = (int32_t)(seg_len[i] / 64);
+        a.seg_m[i] = mg.m[i];
+        a.seg_sc[i + 1] = a.seg_sc[i] + (nc + mg.m[i] - 1) / mg.m[i];
+        a.seg_ck[i + 1] = a.seg_ck[i] + nc;
     }
     return s;
 }

@@ -44,9 +44,9 @@ __device__ __forceinline__ Decode decode(const SegArgs &a, int item) {
     if (a.n_seg > 1) {  // a chain in one launch: superchunks are cut at the segments' ends
         int i = 0;
         while (i + 1 < a.n_seg && d.J >= a.seg_sc[i + 1]) ++i;
-        const int ck = a.seg_ck[i] + (d.J - a.seg_sc[i]) * (a.ts / C), end = a.seg_ck[i + 1];
+        const int m = a.seg_m[i], ck = a.seg_ck[i] + (d.J - a.seg_sc[i]) * m, end = a.seg_ck[i + 1];
         d.tok0 = (int64_t)ck * C;
-        d.nch = end - ck < a.ts / C ? end - ck : a.ts / C;
+        d.nch = end - ck < m ? end - ck : m;
         return d;
     }
     d.tok0 = (int64_t)d.J * a.ts;

@@ -39,11 +39,11 @@ struct SegArgs {
     int32_t ckpt;  // backward: 1 when wsS, wsLg and wsSn already hold the
                    // forward's superchunk states, decays and final state
     // a chain run as one segment: n_seg > 1 segments, segment i holding the
-    // superchunks seg_sc[i] .. seg_sc[i + 1] - 1 from chunk seg_ck[i] on (the last
-    // superchunk of each may be short); the forward scan writes the state entering
-    // segment i >= 1 to S_bnd + i B H D D, the backward's replay starts from it
+    // superchunks seg_sc[i] .. seg_sc[i + 1] - 1 of seg_m[i] chunks from chunk seg_ck[i]
+    // on (the last superchunk of each may be short); the forward scan writes the state
+    // entering segment i >= 1 to S_bnd + i B H D D, the backward's replay starts from it
     int32_t n_seg;
-    int32_t seg_sc[MAX_MERGED + 1], seg_ck[MAX_MERGED + 1];
+    int32_t seg_sc[MAX_MERGED + 1], seg_ck[MAX_MERGED + 1], seg_m[MAX_MERGED];
     float *S_bnd;
 };
 

@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <vector>
 
 #include "launch_stubs.hpp"
 #include "stateflow.h"
@@ -28,7 +29,53 @@ static sf_shape shape(int64_t L = 1024) {
     return s;
 }
 
+// A chain of small segments goes out as one set of launches whose superchunks cover
+// every segment's chunks in order, cross no segment's end and are no longer than
+// those the segment would take in a call of its own.
+static void check_merged(int B, int H, int D, int gate, const std::vector<int64_t> &len, int ts) {
+    int64_t L = 0;
+    for (int64_t x : len) L += x;
+    sf_shape s = shape(L);
+    s.B = B, s.H = H, s.Dk = s.Dv = D, s.gate = gate;
+    sf_tuning t;
+    std::memset(&t, 0, sizeof t);
+    t.ts = ts;
+    const int n = (int)len.size();
+    sf::LaunchRecord rec, one;
+    sf::launch_record = &rec;
+    EXPECT(sf_chain_fwd(&s, n, len.data(), P(1), P(2), P(3), F(4), P(5), F(6), nullptr, 0, P(7), 1 << 30, &t, nullptr,
+                        nullptr) == SF_OK);
+    EXPECT(rec.seg.size() == 3);
+    EXPECT(sf_chain_bwd(&s, n, len.data(), P(1), P(2), P(3), F(4), F(5), nullptr, 0, P(6), nullptr, P(8), P(9), P(10),
+                        F(11), F(12), P(13), 1 << 30, &t, nullptr, nullptr) == SF_OK);
+    EXPECT(rec.seg.size() == 7);
+    sf::launch_record = &one;
+    for (const auto &launch : rec.seg) {
+        const sf::SegArgs &a = launch.second;
+        EXPECT(a.n_seg == n && a.seg_sc[0] == 0 && a.seg_ck[0] == 0 && a.seg_sc[n] == a.n_super);
+        for (int i = 0; i < n; ++i) {
+            const int64_t nc = len[i] / 64, ns = a.seg_sc[i + 1] - a.seg_sc[i];
+            EXPECT(a.seg_ck[i + 1] - a.seg_ck[i] == nc && a.seg_m[i] > 0);
+            EXPECT(ns * a.seg_m[i] >= nc && (ns - 1) * a.seg_m[i] < nc);
+            sf_shape si = s;
+            si.L = len[i];
+            EXPECT(sf_segment_fwd(&si, P(1), P(2), P(3), F(4), nullptr, P(5), F(6), P(7), 1 << 30, &t, nullptr) == SF_OK);
+            const sf::SegArgs &b = one.seg.back().second;
+            EXPECT(a.seg_m[i] * 64 <= (b.ts < len[i] ? b.ts : len[i]));
+        }
+    }
+    sf::launch_record = nullptr;
+}
+
 int main() {
+    for (int gate : {SF_GATE_SCALAR, SF_GATE_VECTOR})
+        for (int H : {1, 2, 6, 16}) {
+            check_merged(1, H, 128, gate, {1984, 1088, 4160}, 0);
+            check_merged(1, H, 64, gate, {1984, 1088, 4160}, 0);
+            check_merged(1, H, 128, gate, {64, 8192, 192, 64, 2048}, 0);
+            check_merged(2, H, 128, gate, std::vector<int64_t>(32, 512), 0);
+            check_merged(1, H, 128, gate, {192, 64, 320, 128}, 64);
+        }
     sf_tuning t;
     std::memset(&t, 0, sizeof t);
     t.ts = 128;
