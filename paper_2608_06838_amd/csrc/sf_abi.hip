@@ -342,7 +342,7 @@ CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) { return ckpt_layout_n
 // rounding grows with that run (H 16 at 2048 tokens instead of 256: 0.74 ms, but
 // over 1.5 times the error; H 6, 1984 + 1088 + 4160 with one length for all: the
 // vector gate 215 us instead of 220, the scalar gate's dg 5.8e-6 off instead of
-// 5.4e-6; H 5, 10432 + 896: 201 us instead of 255, segment by segment 287).
+// 5.0e-6; H 5, 10432 + 896: 201 us instead of 255, segment by segment 287).
 // n = 0: segment by segment.
 struct Merged {
     int n = 0, ts = 0;            // superchunks of a head, tokens of the longest

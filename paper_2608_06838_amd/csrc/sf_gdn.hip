@@ -1195,7 +1195,9 @@ __global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
 // Thirteen barriers per item.  dbeta and the log-decay gradient come from row and
 // column sums in a fixed order (no atomics).  q, k, v, dO enter the products
 // exactly (bf16); the computed fp32 operands (S, dS', T, P, X, U, dU, G_U, E1, E2)
-// as hi/lo bf16 pairs (three products, lo x lo dropped).  The next item's q, k, T,
+// as hi/lo bf16 pairs (three products, lo x lo dropped; kept in <dS', S>, which all
+// of dg is at weak decay: without it dg was 7.5e-6 off at g = -e^-8, with it 7.0e-6).
+// The next item's q, k, T,
 // S and dS' wait in registers from step 2 on and its v, dO are copied into LDS
 // during step 4.
 // D = 128, 65536 tokens of 40 heads: 7.6 ms with S and dS' staged through LDS in
@@ -1425,13 +1427,14 @@ __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
         }
 
         // --- 1. Y = K S, dU = e o (K dS') on the wave's own v (rows t = prow(tt, r))
-        f32x4 x[4], du[4], sd4 = z4;  // sd4: (S^T dS')[v][v'], its diagonal sums to <dS', S>
+        f32x4 x[4], du[4], sd4 = z4;  // sd4: (S^T dS')[v][v'], its diagonal sums to <dS', S>, lo x lo included
 #pragma unroll
         for (int tt = 0; tt < 4; ++tt) x[tt] = du[tt] = z4;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const frag_t<T> sh = s1h[ks], sl = s1l[ks], dh = d1h[ks], dl = d1l[ks];
             mma3(sd4, sh, sl, dh, dl);
+            mma(sd4, sl, dl);
 #pragma unroll
             for (int tt = 0; tt < 4; ++tt) {
                 const frag_t<T> kf = rd(sK, kb[(ks ^ tt) & 1] + roff(tt) * D + 64 * (ks >> 1));

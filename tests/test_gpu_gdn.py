@@ -328,3 +328,23 @@ def test_gdn_chain_entry_points(D, ts):
                             threads=cores())
         assert_close(f"S_bnd{i + 1}", S_bnd[i + 1], Si, "bf16")
     check_bwd(res[True][3:], ref_bwd(inp, dO, dS_final))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("ts", [128, 512])
+def test_gdn_gate_gradient_of_the_states(D, ts):
+    """q = k = dO = 0 and g = 0: the state and its gradient pass every chunk
+    unchanged and dg_t = <dS_out, S_in> for every token.  With every element of both
+    1 + 250 / 2^16, whose parts in 8 bits are 1 and 250 / 2^16, a sum without the
+    products of the low parts is 1.5e-5 short; fp32 sums of 2^14 equal terms keep
+    within 2^-18."""
+    B, L, H = 1, 512, 2
+    say(f"[gdn bwd] gate gradient of the states D={D} ts={ts}")
+    z = torch.zeros((B, L, H, D), dtype=torch.bfloat16, device=DEV)
+    g = torch.zeros((B, L, H), device=DEV)
+    S = torch.full((B, H, D, D), 1 + 250 / 2 ** 16, device=DEV)
+    out = sf.gdn_bwd(z, z.clone(), z.clone(), g, torch.full_like(g, 0.5), S, z.clone(), S.clone(), ts=ts)
+    torch.cuda.synchronize()
+    want = D * D * (1 + 250 / 2 ** 16) ** 2
+    assert np.abs(to64(out[3]) / want - 1).max() <= 2.0 ** -18
+    assert torch.equal(out[5], S)
