@@ -474,7 +474,7 @@ sf_status conv_resolve(const sf_conv_shape *sh, ConvShape &r) {
 // chip); the backward's is what one dw partial covers and grows with L so that
 // at most 256 partials per batch go through the workspace
 int64_t conv_block(const ConvShape &r, bool bwd) {
-    if (!bwd) return sf::conv_fwd_run(r.B, r.C, r.L);
+    if (!bwd) return sf::conv_fwd_run(r.B, r.C, r.L, device_cus());
     const int64_t per = (r.L + 255) / 256;
     return std::max<int64_t>(256, (per + 63) / 64 * 64);
 }
@@ -1246,6 +1246,7 @@ sf_status sf_conv_fwd(const sf_conv_shape *shape, const void *x, const float *w,
     a.L = r.L;
     a.T = conv_block(r, false);
     a.nTB = (int32_t)conv_nblocks(r, false);
+    a.n_cu = device_cus();
     a.sx_b = r.sx_b;
     a.sx_l = r.sx_l;
     // whole runs put their blocks on grid.y, which ends at 65535; shortened runs lie on
@@ -1294,6 +1295,7 @@ sf_status sf_conv_bwd(const sf_conv_shape *shape, const void *x, const float *w,
     a.L = r.L;
     a.T = conv_block(r, true);
     a.nTB = (int32_t)conv_nblocks(r, true);
+    a.n_cu = device_cus();
     a.sx_b = r.sx_b;
     a.sx_l = r.sx_l;
     return conv_run(SF_K_CONV_BWD, true, a, (hipStream_t)stream, timing_of(tuning));

@@ -15,7 +15,7 @@
 // A run's length is a balance: 256 tokens make the halo 1% of the reads, but a
 // small call then has too few waves to hide the latency of its serial run
 // (B 2, L 1037, C 1536: 10 workgroups).  The launcher therefore shortens the
-// runs until the launch has CONV_FILL threads (six waves per CU), down to one
+// runs until the launch has CONV_FILL threads (six waves) per CU, down to one
 // load group; the halos of short runs come from the cache.
 //
 // Backward: du_t = dy_t * act'(u_t); dxh_s = sum_j w[j] du_{s+W-1-j} plus
@@ -385,10 +385,7 @@ hipError_t conv_td(bool bwd, const ConvArgs &a, hipStream_t s, hipEvent_t e0, hi
         const dim3 flat((unsigned)((ncg * a.nTB + CONV_NT - 1) / CONV_NT), 1, (unsigned)a.B);
         hipExtLaunchKernelGGL((k_conv_fwd<T, W, SILU, true>), flat, dim3(CONV_NT), 0, s, e0, e1, 0, a);
     } else {
-        // runs per block: doubled until the launch fills the chip, at most one per load group
-        const int64_t threads = ncg * a.nTB * a.B;
-        int sub = 1;
-        while (sub < 32 && threads * sub < (sizeof(T) == 2 ? CONV_FILL_BWD16 : CONV_FILL_BWD32)) sub *= 2;
+        const int sub = conv_bwd_runs(ncg * a.nTB * a.B, sizeof(T) == 2, a.n_cu);
         auto split = [&](auto tsub) {
             constexpr int TS = decltype(tsub)::value, CGW = CONV_NT / TS;
             const dim3 grid((unsigned)((ncg + CGW - 1) / CGW), (unsigned)a.nTB, (unsigned)a.B);

@@ -71,22 +71,29 @@ struct ConvArgs {
     float *dtail_in;
     float *ws;
     int32_t B, C, W, act, io;
-    int32_t nTB;
+    int32_t nTB, n_cu;  // token blocks; compute units of the device
     int64_t L, T, sx_b, sx_l;
 };
 int conv_channels_per_thread();
-constexpr int CONV_E = 8, CONV_G = 8;          // channels per thread, tokens per load group
-// Threads that fill the chip, below which runs are shortened.  Forward: six waves
-// per CU (bf16, 101248 threads: whole runs 214 us, halves 226).  Backward: the
-// split runs cost halos, so the line lies where they stop paying (whole blocks /
-// runs, us): bf16 122880 threads 350/384, 101248 340/343, 50624 253/199; fp32
+constexpr int CONV_E = 8, CONV_G = 8;  // channels per thread, tokens per load group
+// Threads per CU that fill the chip, below which runs are shortened.  Forward: six
+// waves (256 CUs, bf16, 101248 threads: whole runs 214 us, halves 226).  Backward: the
+// split runs cost halos, so the line lies where they stop paying (256 CUs, whole
+// blocks / runs, us): bf16 122880 threads 350/384, 101248 340/343, 50624 253/199; fp32
 // 61440 threads 318/352, 50624 309/346, 25312 253/200.
-constexpr int64_t CONV_FILL = 256 * 384, CONV_FILL_BWD16 = 256 * 384, CONV_FILL_BWD32 = 256 * 160;
+constexpr int64_t CONV_FILL = 384, CONV_FILL_BWD16 = 384, CONV_FILL_BWD32 = 160;
 // tokens per thread of the forward: 256, halved until the launch fills the chip
-inline int64_t conv_fwd_run(int64_t B, int64_t C, int64_t L) {
+inline int64_t conv_fwd_run(int64_t B, int64_t C, int64_t L, int n_cu) {
     int64_t T = 256;
-    while (T > CONV_G && B * (C / CONV_E) * ((L + T - 1) / T) < CONV_FILL) T /= 2;
+    while (T > CONV_G && B * (C / CONV_E) * ((L + T - 1) / T) < CONV_FILL * n_cu) T /= 2;
     return T;
+}
+// runs per block of the backward: doubled until the launch fills the chip, at most
+// one per load group of the shortest block
+inline int conv_bwd_runs(int64_t threads, bool b16, int n_cu) {
+    int sub = 1;
+    while (sub < 32 && threads * sub < (b16 ? CONV_FILL_BWD16 : CONV_FILL_BWD32) * n_cu) sub *= 2;
+    return sub;
 }
 
 // Gated delta rule (sf_gdn.hip).  n_super superchunks of ts tokens per

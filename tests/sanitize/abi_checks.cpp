@@ -168,6 +168,20 @@ int main() {
         EXPECT(sf_conv_fwd(&c, P(1), F(2), F(3), P(4), F(5), nullptr, nullptr) == SF_E_UNSUPPORTED);
         sf::launch_record = nullptr;
     }
+    // runs are shortened until the device at hand is full, and no further: an eighth
+    // of the CUs need an eighth of the threads
+    for (int cus : {32, 64, 256})
+        for (int64_t L : {64, 1037, 4096, 65536}) {
+            const int64_t groups = 1920 / 8;
+            const int64_t T = sf::conv_fwd_run(1, 1920, L, cus), threads = groups * ((L + T - 1) / T);
+            EXPECT(T == 256 || groups * ((L + 2 * T - 1) / (2 * T)) < 384 * cus);
+            EXPECT(T == 8 || threads >= 384 * cus);
+            for (bool b16 : {false, true}) {
+                const int64_t whole = groups * ((L + 255) / 256), fill = (b16 ? 384 : 160) * cus;
+                const int n = sf::conv_bwd_runs(whole, b16, cus);
+                EXPECT((n == 1 || whole * n / 2 < fill) && (n == 32 || whole * n >= fill));
+            }
+        }
     // gated delta rule
     EXPECT(sf_gdn_fwd(&s, P(1), P(2), P(3), F(4), F(5), nullptr, P(1), F(7), nullptr, P(8), 1ull << 40, nullptr,
                       nullptr) == SF_E_ALIAS);
