@@ -208,6 +208,19 @@ def test_gdn_bwd_long_segment_sampled():
     check_bwd(sub, want)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_gdn_bwd_more_chunks_than_cus(D):
+    """B=2, H=12, 1088 tokens: 408 chunks over 256 CUs, so the per-chunk gradient
+    kernel's workgroups take a second item, loaded during the first (d = 64 forms T of
+    each in the kernel)."""
+    B, L, H = 2, 1088, 12
+    say(f"[gdn bwd] more chunks than CUs D={D}")
+    assert B * H * L // 64 > torch.cuda.get_device_properties(DEV).multi_processor_count
+    inp = synth.make_gdn_inputs(B, L, H, D, seed=4950 + D)
+    dO, dS = grads_inputs(inp, 4960 + D)
+    check_bwd(run_bwd(inp, dO, dS), ref_bwd(inp, dO, dS))
+
+
 def test_gdn_bwd_chained_segments():
     """Forward chained through S, backward chained through dS in reverse: the
     gradients of the concatenated segments equal the oracle's over the whole
