@@ -98,17 +98,19 @@ def test_fp32_d128_segment(ts):
     check_all("f32", got, oracle_run(inp), inp)
 
 
-@pytest.mark.parametrize("ts", [0, 64])
+@pytest.mark.parametrize("ts", [0, 64, 128])
 def test_fp32_d128_chain(ts):
-    """fp32 I/O at d = 128 over four nonuniform segments: overlap on and off and
-    kept superchunk states give bitwise the same outputs; fp32 bar."""
+    """fp32 I/O at d = 128 over four nonuniform segments, in one set of launches (ts =
+    0, 64) and segment by segment (128): overlap on and off and kept superchunk states
+    give bitwise the same outputs; fp32 bar."""
     w = synth.workload("tiny_fp32", B=1, H=3, D=128)
     seg_lens = [192, 64, 320, 128]
     inp = synth.make_inputs(w, device="cpu", seed=1210 + ts, dS_out_std=0.1, L=sum(seg_lens))
     g = on_gpu(inp)
     say(f"[chain] fp32 d=128 ts={ts}")
+    assert in_one(g, seg_lens, ts) == (ts != 128)
     a = run_chain(g, seg_lens, ts=ts, overlap=True)
-    for kw in (dict(overlap=False), dict(overlap=True, keep=True)):
+    for kw in (dict(overlap=False), dict(overlap=2), dict(overlap=True, keep=True), dict(overlap=2, keep=True)):
         b = run_chain(g, seg_lens, ts=ts, **kw)
         for key in a:
             assert torch.equal(a[key], b[key]), (key, kw)
@@ -146,6 +148,24 @@ def test_empty_segment():
     assert torch.equal(dS_in, inp["dS_out"])
 
 
+def launches(fn, *kernels):
+    """(fn(timing), launches per kernel kind of that call)"""
+    t = sf.KernelTimer(kernels, capacity=512)
+    try:
+        out = fn(t)
+        return out, {k: n for k, (_, n) in t.read().items()}
+    finally:
+        t.close()
+
+
+def in_one(g, seg_lens, ts):
+    """Whether the chain goes out as one set of launches over all its segments."""
+    _, n = launches(lambda t: sf.chain_fwd(g["q"], g["k"], g["v"], g["g"], seg_lens, g["S_in"], ts=ts, overlap=False,
+                                           timing=t), "fwd_out")
+    assert n["fwd_out"] in (1, len(seg_lens))
+    return n["fwd_out"] == 1
+
+
 def run_chain(g, seg_lens, ts=0, overlap=True, keep=False):
     """keep: the backward reads the superchunk states the forward kept."""
     ck = None
@@ -172,13 +192,15 @@ def check_chain(io, inp, got, seg_lens, pairs=None):
 
 @pytest.mark.parametrize("ts", [0, 64, 128])
 def test_chain_nonuniform_small(ts):
-    """Four nonuniform segments, chained; every overlap mode (serial, scans on
-    the aux stream, preparation and scans there) agrees bitwise."""
+    """Four nonuniform segments, chained, in one set of launches (ts = 0, 64) and
+    segment by segment (128); every overlap mode (serial, scans on the aux stream,
+    preparation and scans there) agrees bitwise."""
     w = synth.workload("mid_bf16", B=1, H=4, D=128)
     seg_lens = [192, 64, 320, 128]
     inp = synth.make_inputs(w, device="cpu", seed=11, dS_out_std=0.1, L=sum(seg_lens))
     g = on_gpu(inp)
     say(f"[chain] small nonuniform ts={ts}")
+    assert in_one(g, seg_lens, ts) == (ts != 128)
     a = run_chain(g, seg_lens, ts=ts, overlap=True)
     for mode in (False, 2):
         b = run_chain(g, seg_lens, ts=ts, overlap=mode)
@@ -205,6 +227,7 @@ def test_chain_launched_as_one_segment(name, D, io, head_major):
                 p = (0, 2, 1, 3)[:g[key].dim()]
                 g[key] = g[key].permute(*p).contiguous().permute(*p)
         say(f"[chain] {n} segments {name} D={D} {io} against segment calls")
+        assert in_one(g, seg_lens, 64) == (n == 32)
         a = run_chain(g, seg_lens, ts=64, overlap=False)
         for mode in (True, 2) if n > 32 else ():
             b = run_chain(g, seg_lens, ts=64, overlap=mode)
@@ -232,16 +255,6 @@ def test_chain_launched_as_one_segment(name, D, io, head_major):
                 assert np.all(np.abs(X - R) <= 2.0 ** -7 * np.abs(R) + 2e-3 * np.sqrt(np.mean(R * R))), key
             else:
                 assert_close(key, X, R, io)
-
-
-def launches(fn, *kernels):
-    """(fn(timing), launches per kernel kind of that call)"""
-    t = sf.KernelTimer(kernels, capacity=512)
-    try:
-        out = fn(t)
-        return out, {k: n for k, (_, n) in t.read().items()}
-    finally:
-        t.close()
 
 
 @pytest.mark.parametrize("name,D,io", [("mid_bf16", 128, "bf16"), ("tiny_fp32", 64, "f32"), ("vector_gate", 128, "bf16")])
@@ -274,19 +287,23 @@ def test_chain_replay_starts_from_the_given_states(name, D, io):
 
 
 KEPT_CASES = [("mid_bf16", 128, "bf16", 0), ("mid_bf16", 128, "bf16", 64), ("mid_bf16", 64, "bf16", 128),
-              ("tiny_fp32", 64, "f32", 128), ("vector_gate", 128, "bf16", 128), ("vector_gate", 64, "f32", 64)]
+              ("tiny_fp32", 64, "f32", 128), ("vector_gate", 128, "bf16", 128), ("vector_gate", 64, "f32", 64),
+              ("mid_bf16", 128, "bf16", 128), ("tiny_fp32", 128, "f32", 128), ("vector_gate", 64, "f32", 128),
+              ("vector_gate", 128, "bf16", 64)]
 
 
 @pytest.mark.parametrize("name,D,io,ts", KEPT_CASES)
 def test_kept_states(name, D, io, ts):
     """Backward from the superchunk states the forward kept: bitwise the
     outputs of the backward that replays them (segments of one and of several
-    superchunks, overlap on and off), and within the bar of the oracle."""
+    superchunks; in one set of launches, or, for ts = 128, segment by segment in
+    every overlap mode), and within the bar of the oracle."""
     w = synth.workload(name, B=1, H=3, D=D, io=io)
     seg_lens = [192, 64, 320, 128]
     inp = synth.make_inputs(w, device="cpu", seed=53 + D + ts, dS_out_std=0.1, L=sum(seg_lens))
     g = on_gpu(inp)
     say(f"[chain] kept states {name} D={D} {io} ts={ts}")
+    assert in_one(g, seg_lens, ts) == (ts != 128)
     for overlap in (False, True, 2):
         a = run_chain(g, seg_lens, ts=ts, overlap=overlap)
         b = run_chain(g, seg_lens, ts=ts, overlap=overlap, keep=True)
@@ -356,13 +373,15 @@ def test_vector_gate_decay_regimes(g_mu):
     check_all("bf16", got, oracle_run(inp), inp, dg_apriori_ts=128 if g_mu < -10 else None)
 
 
-@pytest.mark.parametrize("ts", [0, 64])
+@pytest.mark.parametrize("ts", [0, 64, 128])
 def test_vector_gate_chain_nonuniform(ts):
+    """As test_chain_nonuniform_small, with the per-key-channel gate."""
     w = synth.workload("vector_gate", B=1, H=3, D=128)
     seg_lens = [192, 64, 320, 128]
     inp = synth.make_inputs(w, device="cpu", seed=43, dS_out_std=0.1, L=sum(seg_lens))
     g = on_gpu(inp)
     say(f"[chain] vector gate nonuniform ts={ts}")
+    assert in_one(g, seg_lens, ts) == (ts != 128)
     a = run_chain(g, seg_lens, ts=ts, overlap=True)
     for mode in (False, 2):
         b = run_chain(g, seg_lens, ts=ts, overlap=mode)
