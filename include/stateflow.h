@@ -124,7 +124,7 @@ typedef enum {
     SF_K_BWD_DKV = 5,    /* dk, dv, dg by a reverse state-gradient walk (PG) */
     SF_K_CONV_FWD = 6,   /* short convolution, forward */
     SF_K_CONV_BWD = 7,   /* short convolution, backward (dx, dtail_in, dw partials and their sum) */
-    SF_K_GDN_PREP = 8,   /* gated delta rule: superchunk maps (M_J, N_J) */
+    SF_K_GDN_PREP = 8,   /* gated delta rule: superchunk maps (M_J, N_J); T of every chunk (Dk = 128) */
     SF_K_GDN_SCAN = 9,   /* gated delta rule: fp32 affine state scan */
     SF_K_GDN_OUT = 10,   /* gated delta rule: output walk */
     SF_K_GDN_STORE = 11, /* gated delta rule backward: walk storing the state entering every chunk */
@@ -212,7 +212,12 @@ sf_status sf_segment_bwd(const sf_shape *shape, const void *q, const void *k, co
                          float *dS_in, void *ws, size_t ws_bytes, const sf_tuning *tuning,
                          sf_stream stream);
 
-/* Workspace bytes for the chain calls (covers both directions). */
+/* Workspace bytes for the chain calls (covers both directions).  Segment by
+ * segment, the largest segment's needs twice over; a chain that runs as one set
+ * of launches (see sf_chain_fwd) holds the superchunk states and state gradients
+ * of all its segments at once: 8 Dk Dv bytes per (b, h, superchunk), at most
+ * 32 segments of one workgroup per CU each (1.1 GB at Dk = 128 on 256 CUs; B 4,
+ * H 32, 32 segments of 512 tokens: 556 MB, where 33 segments take 17 MB). */
 size_t sf_chain_workspace_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
                                 const sf_tuning *tuning);
 
@@ -223,8 +228,11 @@ size_t sf_chain_workspace_bytes(const sf_shape *shape, int32_t n_seg, const int6
  * state entering each superchunk (the ST output of Sec. 2.2, fp32 Dk x Dv per
  * (b, h, superchunk)), each superchunk's log-decay and the state leaving the
  * segment.  The superchunk lengths are those the same shape, segments and
- * tuning select.  0 when no segment has more than one superchunk, and on
- * invalid arguments (then sf_last_error() is set).
+ * tuning select.  0 when no segment has more than one superchunk and the chain
+ * runs segment by segment, and on invalid arguments (then sf_last_error() is
+ * set).  With tuning->ts = 0 a chain in one set of launches keeps the states of
+ * all its superchunks, also where every segment is one (277 MB for the example
+ * above, where 33 segments keep nothing).
  */
 size_t sf_chain_ckpt_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
                            const sf_tuning *tuning);
@@ -247,9 +255,11 @@ size_t sf_chain_ckpt_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *
  * concurrently with the next segment's preparation and the previous
  * segment's output kernels (Sec. 3.4, fwd split-and-overlap schedule; with
  * overlap = 2 the preparation runs on aux too, ahead of the scan); both
- * streams must belong to the current device.  A chain of at most 32 segments
- * whose launches would each leave the device idle runs as one set of launches
- * over all its segments, on main alone.  On return the work is
+ * streams must belong to the current device.  A chain of 2 to 32 segments of at
+ * most one workgroup per CU each, whose launches one by one would leave the
+ * device idle, runs as one set of launches over all its segments, on main alone,
+ * whatever the overlap (with a given tuning->ts only where its kept states fit
+ * the bytes they take segment by segment).  On return the work is
  * enqueued on main and aux, and main carries a dependency on all of it.
  */
 sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
@@ -262,7 +272,7 @@ sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
  * segments processed last to first.  S_bnd is the forward's boundary array
  * (slot i = S_in of segment i; slot n_seg is not read).  dS_final is the
  * gradient of the final state (NULL = zero); dS_init receives the gradient
- * of S_init.  Overlap as in sf_chain_fwd (Sec. 3.4, bwd schedule).
+ * of S_init.  Without ckpt every segment is replayed from its slot of S_bnd.  Overlap as in sf_chain_fwd (Sec. 3.4, bwd schedule).
  * ckpt: NULL (every superchunk state is recomputed: the preparation replays
  * D_J and the scan runs forward again), or the buffer that sf_chain_fwd
  * filled for the same shape, segments and tuning (read only; at least
@@ -361,6 +371,10 @@ sf_status sf_partition_hybrid(int64_t T, int32_t N, double alpha, double w_tok, 
  *   ws  device scratch of at least sf_gdn_fwd_workspace_bytes() (0 when the
  *       segment is one superchunk); contents on entry ignored, on return
  *       unspecified.
+ *   o   is scratch during the call (Dk = 128: its rows hold intermediate values
+ *       until they are written): undefined until the call's work is done, and
+ *       after work that failed.  The same holds for dq in the backward calls and
+ *       for both in the chain calls.
  * Same ownership, validation, aliasing and error rules as the other entry
  * points.
  */
@@ -380,9 +394,9 @@ sf_status sf_gdn_fwd(const sf_shape *shape, const void *q, const void *k, const 
  * over the chunks (dS_start = M_J^T dS_end + E_J per superchunk, the
  * transpose of the forward's chunk map) and is stored for every chunk; the
  * parameter gradients of all chunks are then computed in parallel.
- *   ws  device scratch of at least sf_gdn_bwd_workspace_bytes(): two fp32
- *       D x D states per 64-token chunk plus the superchunk maps; contents
- *       on entry ignored.
+ *   ws  device scratch of at least sf_gdn_bwd_workspace_bytes(): two D x D
+ *       states per 64-token chunk, each as a bf16 hi/lo pair (4 bytes an
+ *       element), plus the superchunk maps; contents on entry ignored.
  * Same shape rules as sf_gdn_fwd; same ownership, validation, aliasing and
  * error rules as the other entry points.
  */

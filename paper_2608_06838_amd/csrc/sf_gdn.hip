@@ -804,7 +804,7 @@ __global__ void __launch_bounds__(4 * D) k_gdn_scan(GdnArgs a) {
 //   k_gdn_dscan:        dS_end(J) for every J (M_{J+1}^T, fp32, in reverse);
 //   k_gdn_dwalk<false>: from dS_end(J), writes dS' of every chunk and dS_in;
 //   k_gdn_dchunk:       the parameter gradients of every chunk, all chunks in
-//                       parallel, from the stored S and dS' (fp32 arithmetic).
+//                       parallel, from the stored S and dS' (bf16 hi/lo pairs, fp32 sums).
 
 // The backward's state-gradient walk, its waves, columns and tiles as the forward
 // walks'.  Per chunk, each wave on its own columns:
@@ -1197,12 +1197,11 @@ __global__ void __launch_bounds__(4 * D) k_gdn_dscan(GdnArgs a) {
 // exactly (bf16); the computed fp32 operands (S, dS', T, P, X, U, dU, G_U, E1, E2)
 // as hi/lo bf16 pairs (three products, lo x lo dropped; kept in <dS', S>, which all
 // of dg is at weak decay: without it dg was 7.5e-6 off at g = -e^-8, with it 7.0e-6).
-// The next item's q, k, T,
-// S and dS' wait in registers from step 2 on and its v, dO are copied into LDS
-// during step 4.
+// The next item's q, k, T, S and dS' wait in registers from step 2 on and its v, dO
+// are copied into LDS during step 4.
 // D = 128, 65536 tokens of 40 heads: 7.6 ms with S and dS' staged through LDS in
-// blocks of 32 channels by 16 waves (T formed again, spills), 3.0 ms so (9.7 GB,
-// 1.9 ms at the rate of a copy).
+// blocks of 32 channels by 16 waves (T formed again, spills), 3.0 ms so (10.9 GB
+// moved, 9.9 of them needed; 2.1 ms at the rate of a copy).
 template <typename T, int D>
 __global__ void __launch_bounds__(4 * D, 1) k_gdn_dchunk(GdnArgs a) {
     constexpr int NW = D / 16, NT = 4 * D, KS = D / 32, BPR = D / 8;

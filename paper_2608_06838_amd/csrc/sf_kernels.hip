@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(SCAN_NT) k_scan(SegArgs a) {
                     dd[slot][u] = *reinterpret_cast<const vecE *>(Sb + (int64_t)(J0 + u) * SS);
                     f[slot][u] = fexp2(lg[(J0 + u) * LS]);
                     if (BWD && MG && si < a.n_seg && J0 + u + 1 == a.seg_sc[si]) {
-                        dd[slot][u] = *reinterpret_cast<const vecE *>(bnd + si++ * SSB);  // the given state
+                        dd[slot][u] = *reinterpret_cast<const vecE *>(bnd + si++ * SSB);  // the given state, not D_J
                         f[slot][u] = -1.f;                                                // (no decay: it replaces S)
                     }
                 }

@@ -8,7 +8,9 @@
 
 namespace sf {
 
-constexpr int MAX_MERGED = 32;  // segments of a chain that one set of launches can cover
+// segments of a chain that one set of launches can cover: their table travels in the
+// kernel arguments; longer chains run segment by segment
+constexpr int MAX_MERGED = 32;
 
 // One segment (or one superchunk-parallel launch over a segment).  Token
 // tensors point at the segment's first token; strides are in elements.
@@ -99,7 +101,7 @@ inline int conv_bwd_runs(int64_t threads, bool b16, int n_cu) {
 // Gated delta rule (sf_gdn.hip).  n_super superchunks of ts tokens per
 // (batch, head); with n_super > 1 the workspace holds the boundary states
 // wsS [B*H][n_super][D][D] and the superchunk maps wsM, wsN
-// [B*H][n_prep][D][D] (all fp32; n_prep = n_super - 1 for the forward,
+// [B*H][n_prep][D][D] (these fp32; n_prep = n_super - 1 for the forward,
 // n_super for the backward, which also needs M of the last superchunk).
 struct GdnArgs {
     const void *q, *k, *v;
@@ -107,22 +109,23 @@ struct GdnArgs {
     void *o, *v_new;
     float *S_out;
     float *wsS, *wsM, *wsN;  // boundary states; superchunk maps (n_prep per head)
-    float *wsSc;             // backward: the state entering every chunk [B*H][L/64][D][D]
+    float *wsSc;             // backward: the state entering every chunk [B*H][L/64], as two D x D planes of
+                             // bf16 (hi, lo), transposed: the bytes of an fp32 state
     // backward
     const void *dO;
     const float *dS_out;
     void *dq, *dk, *dv;
     float *dg, *dbeta, *dS_in;
     float *wsE, *wsDe;  // superchunk dS offsets E_J [B*H][n_super-1], dS_end(J) [B*H][n_super]
-    float *wsDc;        // dS' of every chunk [B*H][L/64][D][D]
+    float *wsDc;        // dS' of every chunk, as wsSc
     int32_t B, H, n_super, ts, n_prep, n_x;  // n_x: workgroups of the per-chunk gradient kernel
     int32_t scan_out;  // forward chains: maps of every superchunk, the scan writes S_out
     int32_t n_cu;      // compute units of the device
     void *tw;          // D = 128: the output (o or dq) whose rows hold T until it is written
     int64_t L, sx_b, sx_l, sx_h, sg_b, sg_l, sg_h;
 };
-// One kernel of the delta-rule pipeline: T of every chunk (D = 128); forward prep ([M|N] maps of the
-// superchunks), scan (S_J), output walk; backward state-storing walk, dS prep
+// One kernel of the delta-rule pipeline: T of every chunk (D = 128); forward prep
+// (the superchunks' maps M and N), scan (S_J), output walk; backward state-storing walk, dS prep
 // (E_J), dS scan (dS_end(J)), dS walk, per-chunk gradients.
 enum GdnPhase { GDN_PREP, GDN_SCAN, GDN_OUT, GDN_STORE, GDN_DPREP, GDN_DSCAN, GDN_DWALK, GDN_DCHUNK, GDN_TPREP };
 hipError_t launch_gdn_phase(int phase, const GdnArgs &a, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
