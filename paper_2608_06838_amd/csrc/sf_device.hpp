@@ -432,6 +432,11 @@ __device__ __forceinline__ int swz_col(int row, int col, int swx) { return col ^
 // fragment address is one of them plus a compile-time constant.
 struct LaneOff {
     int lo, hi;
+    // lo or hi by a bit that may depend on the wave.  Not `bit ? hi : lo`: the compiler
+    // turns that into one load at a chosen address, keeps the pair in memory for it,
+    // and puts it into LDS, indexed with the workgroup's size, which it reads from the
+    // dispatch packet, in host memory: 9 us on 256 workgroups, and 8 bytes a thread.
+    __device__ __forceinline__ int at(int bit) const { return lo + (bit ? hi - lo : 0); }
 };
 // for ldfragTR: rows k0 + 8q + (a / 4) (+4), channels c0 + 4 (a % 4) (bf16) or
 // rows k0 + 8q + j, channel c0 + a (fp32), with a = lane % 16
@@ -461,7 +466,7 @@ __device__ __forceinline__ LaneOff swz_off(int lane) {
 // (k0 a multiple of 32, c0 of 16; o = tr_off(lane)).
 template <typename T, int LD, int SWX>
 __device__ __forceinline__ frag_t<T> ldfragTR(const T *M, const LaneOff &o, int k0, int c0) {
-    const int e = ((c0 & SWX) ? o.hi : o.lo) + k0 * LD + c0;
+    const int e = o.at(c0 & SWX) + k0 * LD + c0;
     if constexpr (sizeof(T) == 2) {
         typedef short s4 __attribute__((ext_vector_type(4)));
         typedef short s8 __attribute__((ext_vector_type(8)));
@@ -480,7 +485,7 @@ __device__ __forceinline__ frag_t<T> ldfragTR(const T *M, const LaneOff &o, int 
 // row0 a multiple of 16, k0 of 32; o = swz_off(lane)).
 template <typename T, int LD, int SWX>
 __device__ __forceinline__ frag_t<T> ldfrag_swz(const T *M, const LaneOff &o, int row0, int k0) {
-    return *reinterpret_cast<const frag_t<T> *>(M + ((k0 & SWX) ? o.hi : o.lo) + row0 * LD + k0);
+    return *reinterpret_cast<const frag_t<T> *>(M + o.at(k0 & SWX) + row0 * LD + k0);
 }
 // Fragment in plain channel order (channels k0 + 8q .. +7) from a tile stored
 // in nat_pos order: the 8 channels sit in two 4-channel runs 8 apart.

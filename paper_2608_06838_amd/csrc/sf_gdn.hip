@@ -321,7 +321,7 @@ struct TriTile {
 template <typename T, int D, int NW>
 struct DmaTile {
     static constexpr int BPR = D / 8, RPI = 64 / BPR, NI = C / RPI / NW;  // blocks per row, rows per instruction
-    uint32_t v0, v1;  // source offsets; v1 for the instructions whose rows flip f's bit 2
+    uint32_t v0, v1;  // source offsets; v1 for the instructions whose rows flip f's bit 2 (chosen as in LaneOff::at)
     __device__ __forceinline__ DmaTile(int lane, int64_t ld) {
         const int r = lane / BPR, b = (lane % BPR) ^ r;  // r < RPI <= 8: f(r) = r
         v0 = (uint32_t)((r * ld + 8 * b) * (int64_t)sizeof(T));
@@ -333,7 +333,7 @@ struct DmaTile {
             const int k = NI * w + i;
             const bool flip = (D == 128 ? k ^ (k >> 1) : k) & 1;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + 512 * k), 16,
-                                                     flip ? v1 : v0, (int)(RPI * k * row_bytes), 0, 0);
+                                                     v0 + (flip ? v1 - v0 : 0), (int)(RPI * k * row_bytes), 0, 0);
         }
     }
     // fragment rows 16 tt + n16, columns 32 ks + 8 q4: base[ks & 1] + row0 D + 64 (ks >> 1)

@@ -6,7 +6,13 @@ address as data.  One loop shape of the delta-rule state scan once produced
 exactly that store; the likeliest cause is a stored value the compiler saw as
 undefined (read before written), which frees it to reuse any register.  The
 build therefore also compiles every source with clang's uninitialized-value
-warnings and fails on any.  CPU only; skipped without hipcc.
+warnings and fails on any.
+
+No kernel keeps a variable in scratch memory or reads the dispatch packet.  A
+value chosen by address (`bit ? x.hi : x.lo` with a runtime bit) stays in
+memory; where the compiler then moves it into LDS, every workgroup reads its
+own size from the dispatch packet in host memory, 9 us over 256 workgroups.
+CPU only; skipped without hipcc.
 """
 import concurrent.futures
 import os
@@ -49,6 +55,18 @@ def overlapping_stores(asm_text):
     return n, bad
 
 
+def in_memory(asm_text):
+    """Kernels with a scratch segment or a pointer to the dispatch packet, and how many kernels there are."""
+    bad, n, fn = [], 0, None
+    for line in asm_text.splitlines():
+        m = re.match(r"\s+\.amdhsa_(kernel|private_segment_fixed_size|user_sgpr_dispatch_ptr)\s+(\S+)", line)
+        if m and m.group(1) == "kernel":
+            fn, n = m.group(2), n + 1
+        elif m and m.group(2) != "0":
+            bad.append((fn, line.strip()))
+    return n, bad
+
+
 def test_overlap_detector():
     n, bad = overlapping_stores("\tglobal_store_dwordx4 v[4:5], v[2:5], off\n\tglobal_store_dwordx4 v[6:7], v[2:5], off\n"
                                 "\tbuffer_store_dwordx4 v[2:5], v3, s[0:3], 0 offen\n\tds_write_b128 v1, v[2:5]\n")
@@ -68,14 +86,16 @@ def test_no_store_overlaps_its_address():
                              check=True, capture_output=True, text=True)
         warn = [ln for ln in res.stderr.splitlines() if "uninitialized" in ln]
         with open(out) as f:
-            return src, overlapping_stores(f.read()), warn
+            asm = f.read()
+        return src, overlapping_stores(asm), in_memory(asm), warn
 
     try:
         with concurrent.futures.ThreadPoolExecutor(max_workers=4) as ex:
             results = list(ex.map(build, SOURCES))
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
-    for src, (n, bad), warn in results:
+    for src, (n, bad), (kernels, kept), warn in results:
+        assert kernels > 10 and not kept, f"{src}: {kept[:3]} of {kernels}"
         assert n > 100, f"{src}: too few stores parsed ({n})"
         assert not bad, f"{src}: {bad[:3]}"
         # a value read before it is written is undefined: the compiler may then
