@@ -216,8 +216,8 @@ sf_status sf_segment_bwd(const sf_shape *shape, const void *q, const void *k, co
  * segment, the largest segment's needs twice over; a chain that runs as one set
  * of launches (see sf_chain_fwd) holds the superchunk states and state gradients
  * of all its segments at once: 8 Dk Dv bytes per (b, h, superchunk), at most
- * 32 segments of one workgroup per CU each (1.1 GB at Dk = 128 on 256 CUs; B 4,
- * H 32, 32 segments of 512 tokens: 556 MB, where 33 segments take 17 MB). */
+ * 32 segments of one workgroup per CU each (1.1 GB at Dk = 128 on 256 CUs; H 16,
+ * 32 segments of 512 tokens: 541 MB, where 33 segments take 36 MB). */
 size_t sf_chain_workspace_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
                                 const sf_tuning *tuning);
 
@@ -231,8 +231,8 @@ size_t sf_chain_workspace_bytes(const sf_shape *shape, int32_t n_seg, const int6
  * tuning select.  0 when no segment has more than one superchunk and the chain
  * runs segment by segment, and on invalid arguments (then sf_last_error() is
  * set).  With tuning->ts = 0 a chain in one set of launches keeps the states of
- * all its superchunks, also where every segment is one (277 MB for the example
- * above, where 33 segments keep nothing).
+ * all its superchunks, also where every segment is one (H 100, 32 segments of 512
+ * tokens: 216 MB, where 33 segments keep nothing).
  */
 size_t sf_chain_ckpt_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
                            const sf_tuning *tuning);
@@ -256,10 +256,12 @@ size_t sf_chain_ckpt_bytes(const sf_shape *shape, int32_t n_seg, const int64_t *
  * segment's output kernels (Sec. 3.4, fwd split-and-overlap schedule; with
  * overlap = 2 the preparation runs on aux too, ahead of the scan); both
  * streams must belong to the current device.  A chain of 2 to 32 segments of at
- * most one workgroup per CU each, whose launches one by one would leave the
- * device idle, runs as one set of launches over all its segments, on main alone,
- * whatever the overlap (with a given tuning->ts only where its kept states fit
- * the bytes they take segment by segment).  On return the work is
+ * most one workgroup per CU each (where every segment is one superchunk: about half
+ * a workgroup per CU at Dk = 128, 5/8 to 13/16 at Dk = 64), whose launches one by one
+ * would leave the device idle, runs as one set of launches over all its segments, on
+ * main alone, whatever the overlap (with a given tuning->ts only where its kept
+ * states fit the bytes they take segment by segment; of two segments of 64 tokens
+ * only the backward).  On return the work is
  * enqueued on main and aux, and main carries a dependency on all of it.
  */
 sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_len,
@@ -272,7 +274,8 @@ sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
  * segments processed last to first.  S_bnd is the forward's boundary array
  * (slot i = S_in of segment i; slot n_seg is not read).  dS_final is the
  * gradient of the final state (NULL = zero); dS_init receives the gradient
- * of S_init.  Without ckpt every segment is replayed from its slot of S_bnd.  Overlap as in sf_chain_fwd (Sec. 3.4, bwd schedule).
+ * of S_init.  Without ckpt every segment is replayed from its slot of S_bnd.
+ * Overlap as in sf_chain_fwd (Sec. 3.4, bwd schedule).
  * ckpt: NULL (every superchunk state is recomputed: the preparation replays
  * D_J and the scan runs forward again), or the buffer that sf_chain_fwd
  * filled for the same shape, segments and tuning (read only; at least

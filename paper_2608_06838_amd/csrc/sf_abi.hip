@@ -331,23 +331,45 @@ CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) { return ckpt_layout_n
 // scan hands out the boundary states.  Chosen when chunk_cost says so, a set of
 // launches and their empty first and last moments counting kSeg steps (35 us of
 // launches and prologues at 13 us a step), and no segment has more than one
-// workgroup per CU (B 4 H 32, 32 segments of 512 tokens: 4.30 ms a step segment by
-// segment, 3.65 ms in one; H 16, 8 of 4096, kept states: 1.28, 1.09; vector gate, B
-// 2 H 16, 16 of 4096: 7.23, 6.69; but the 256K layer, 480 or more a segment: 14.29,
-// 14.65).  The choice depends on the shape and the tuning alone, never on the kept
-// states, so a backward that replays and one that reads them take the same
-// superchunks; with a given ts, whose kept states are sized segment by segment, the
-// chain's have to fit that size.  No segment gets longer superchunks than it would
-// take alone: the gate gradient sums its token terms over a superchunk, and its
-// rounding grows with that run (H 16 at 2048 tokens instead of 256: 0.74 ms, but
-// over 1.5 times the error; H 6, 1984 + 1088 + 4160 with one length for all: the
-// vector gate 215 us instead of 220, the scalar gate's dg 5.8e-6 off instead of
-// 5.0e-6; H 5, 10432 + 896: 201 us instead of 255, segment by segment 287).
-// n = 0: segment by segment.
+// workgroup per CU (H 16, 8 of 4096, kept states: 1.28 ms a step segment by segment,
+// 1.09 in one; vector gate, B 2 H 16, 16 of 4096: 7.23, 6.69; but the 256K layer, 480
+// or more a segment: 14.29, 14.65).  The choice depends on the shape and the tuning
+// alone, never on the kept states, so a backward that replays and one that reads
+// them take the same superchunks; with a given ts, whose kept states are sized
+// segment by segment, the chain's have to fit that size.  No segment gets longer
+// superchunks than it would take alone: the gate gradient sums its token terms over
+// a superchunk, and its rounding grows with that run (H 16 at 2048 tokens instead of
+// 256: 0.74 ms, but over 1.5 times the error; H 6, 1984 + 1088 + 4160 with one length
+// for all: the vector gate 215 us instead of 220, the scalar gate's dg 5.8e-6 off
+// instead of 5.0e-6; H 5, 10432 + 896: 201 us instead of 255, segment by segment 287).
+//
+// Segments of one superchunk each need no preparation, no scan and no states of
+// their own segment by segment, so such a chain runs in one only while a segment
+// leaves the CUs well below full (ones_limit, in sixteenths of the CUs; forward and
+// backward in us, segment by segment / in one, 256 CUs, 16 segments):
+//   D 128, scalar, 7 (launches of up to half the CUs split an item over two CUs):
+//     B H 100, 8 chunks 1863 / 1441; 112, 4 chunks 1132 / 988; 120, 1 chunk 555 / 584;
+//     128, 8 chunks 1859 / 1951; 200, 4 chunks 1415 / 1780
+//   D 128, vector, 8: 128, 8 chunks 4365 / 3528; 144, 1 chunk 908 / 998
+//   D 64, 13 (scalar, fp32, 1 chunk: 200 652 / 595, 250 696 / 718; bf16, 4 chunks: 200
+//     828 / 753, 250 851 / 928; vector, bf16, 200 1639 / 1347), but fp32 vector 8 (128
+//     2107 / 1788, 200, 1 chunk 827 / 866), and 10 below 8 segments (4 of 4 chunks, fp32:
+//     160 414 / 391, 200 418 / 468)
+// and two such segments only up to a workgroup per CU (fp32, D 64, 1 chunk: B H 128
+// 80 / 78, 144 82 / 94).  Two of one chunk run the forward segment by segment all the
+// same (2 launches instead of 3: 31 / 34 us; backward 41 / 38, vector 72 / 47): then
+// S_bnd holds all there is to keep.
+// n = 0: segment by segment; fwd = false: the backward alone in one.
 struct Merged {
     int n = 0, ts = 0;            // superchunks of a head, tokens of the longest
+    bool fwd = true;
     int32_t m[sf::MAX_MERGED]{};  // chunks per superchunk of each segment
 };
+int ones_limit(const Shape &r, int32_t n_seg) {
+    const bool vec = r.gate == SF_GATE_VECTOR;
+    if (r.D == 128) return vec ? 8 : 7;
+    return vec && r.io == SF_F32 ? 8 : n_seg >= 8 ? 13 : 10;
+}
 sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, const sf_tuning *t, Merged &p) {
     p = Merged{};
     if (n_seg < 2 || n_seg > sf::MAX_MERGED || r.L / 64 > (1 << 30)) return SF_OK;
@@ -355,6 +377,7 @@ sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
     double each = 0.0;
     int64_t longest = 0, own[sf::MAX_MERGED];  // chunks per superchunk that each segment would take
     size_t kept = 0;
+    bool ones = true;  // every segment one superchunk
     for (int i = 0; i < n_seg; ++i) {
         int ts;
         const sf_status rc = pick_ts(r, seg_len[i], t, ts);
@@ -365,6 +388,12 @@ sf_status chain_plan(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
         own[i] = std::min<int64_t>(seg_len[i], ts) / 64;
         each += chunk_cost(r, own[i], n) + kSeg;
         longest = std::max(longest, own[i]);
+        ones = ones && n == 1;
+    }
+    if (ones) {
+        const int64_t wg = (int64_t)r.B * r.H, cus = device_cus();
+        if (16 * wg > ones_limit(r, n_seg) * cus || (n_seg == 2 && 2 * wg > cus)) return SF_OK;
+        p.fwd = n_seg > 2 || longest > 1;
     }
     double best = each - kSeg;
     auto consider = [&](int64_t m) {
@@ -663,7 +692,7 @@ sf_status chain_ckpt(const Shape &r, int32_t n_seg, const int64_t *seg_len, cons
     }
     Merged mg;
     TRY(chain_plan(r, n_seg, seg_len, t, mg));
-    if (mg.n > 0) bytes = std::max(bytes, ckpt_layout_n(r, mg.n).total);
+    if (mg.n > 0 && mg.fwd) bytes = std::max(bytes, ckpt_layout_n(r, mg.n).total);
     return SF_OK;
 }
 // point a segment's superchunk-state regions into the kept-state buffer
@@ -1013,7 +1042,7 @@ sf_status sf_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
     const int64_t SSB = (int64_t)r.B * r.H * r.D * r.D;
     Merged mg;
     TRY(chain_plan(r, n_seg, seg_len, tuning, mg));
-    if (mg.n > 0) {
+    if (mg.n > 0 && mg.fwd) {
         Seg s = merged_seg(r, n_seg, seg_len, mg, S_bnd, (char *)ws, false, timing_of(tuning));
         if (ckpt) use_ckpt(r, s, (char *)ckpt, false);
         s.a.q = q;
@@ -1125,7 +1154,7 @@ sf_status sf_chain_bwd(const sf_shape *shape, int32_t n_seg, const int64_t *seg_
     TRY(chain_plan(r, n_seg, seg_len, tuning, mg));
     if (mg.n > 0) {
         Seg s = merged_seg(r, n_seg, seg_len, mg, S_bnd, (char *)ws, true, timing_of(tuning));
-        if (ckpt) use_ckpt(r, s, (char *)ckpt, true);
+        if (ckpt && mg.fwd) use_ckpt(r, s, (char *)ckpt, true);
         s.a.q = q;
         s.a.k = k;
         s.a.v = v;

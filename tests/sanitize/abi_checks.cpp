@@ -67,6 +67,27 @@ static void check_merged(int B, int H, int D, int gate, const std::vector<int64_
     sf::launch_record = nullptr;
 }
 
+// Launches of a chain's two directions, and the bytes it keeps.
+static void check_form(int H, int D, int io, int gate, int n, int chunks, bool fwd_one, bool bwd_one) {
+    const std::vector<int64_t> len(n, 64 * chunks);
+    sf_shape s = shape((int64_t)n * 64 * chunks);
+    s.B = 1, s.H = H, s.Dk = s.Dv = D, s.io_dtype = io, s.gate = gate;
+    sf::LaunchRecord rec;
+    sf::launch_record = &rec;
+    EXPECT(sf_chain_fwd(&s, n, len.data(), P(1), P(2), P(3), F(4), P(5), F(6), nullptr, 0, P(7), 1ull << 40, nullptr, nullptr,
+                        nullptr) == SF_OK);
+    EXPECT(rec.seg.size() == (fwd_one ? 3 : (size_t)n));
+    rec.seg.clear();
+    EXPECT(sf_chain_bwd(&s, n, len.data(), P(1), P(2), P(3), F(4), F(5), nullptr, 0, P(6), nullptr, P(8), P(9), P(10),
+                        F(11), F(12), P(13), 1ull << 40, nullptr, nullptr, nullptr) == SF_OK);
+    EXPECT(rec.seg.size() == (bwd_one ? 4 : 2 * (size_t)n));
+    sf::launch_record = nullptr;
+    // segments of one superchunk, segment by segment: nothing to keep, and no states in the workspace
+    const size_t state = (size_t)H * D * D * 4;
+    EXPECT((sf_chain_ckpt_bytes(&s, n, len.data(), nullptr) == 0) == !fwd_one);
+    EXPECT((sf_chain_workspace_bytes(&s, n, len.data(), nullptr) < 3 * state) == !bwd_one);
+}
+
 int main() {
     for (int gate : {SF_GATE_SCALAR, SF_GATE_VECTOR})
         for (int H : {1, 2, 6, 16}) {
@@ -76,6 +97,22 @@ int main() {
             check_merged(2, H, 128, gate, std::vector<int64_t>(32, 512), 0);
             check_merged(1, H, 128, gate, {192, 64, 320, 128}, 64);
         }
+    // segments of one superchunk each, on 256 CUs, either side of each line: in one (3
+    // and 4 launches) or segment by segment (1 and 2 a segment)
+    struct { int H, D, io, gate, n, chunks; bool one; } forms[] = {
+        {112, 128, SF_BF16, SF_GATE_SCALAR, 16, 1, true},  {113, 128, SF_BF16, SF_GATE_SCALAR, 16, 1, false},
+        {128, 128, SF_BF16, SF_GATE_SCALAR, 32, 8, false}, {128, 128, SF_BF16, SF_GATE_VECTOR, 16, 8, true},
+        {129, 128, SF_BF16, SF_GATE_VECTOR, 16, 1, false}, {208, 64, SF_F32, SF_GATE_SCALAR, 8, 1, true},
+        {209, 64, SF_F32, SF_GATE_SCALAR, 16, 1, false},   {160, 64, SF_F32, SF_GATE_SCALAR, 4, 1, true},
+        {161, 64, SF_F32, SF_GATE_SCALAR, 4, 1, false},    {208, 64, SF_BF16, SF_GATE_VECTOR, 16, 1, true},
+        {128, 64, SF_F32, SF_GATE_VECTOR, 16, 1, true},    {129, 64, SF_F32, SF_GATE_VECTOR, 16, 1, false},
+        {129, 64, SF_F32, SF_GATE_SCALAR, 2, 1, false},    {100, 128, SF_BF16, SF_GATE_SCALAR, 2, 4, true},
+        {33, 128, SF_BF16, SF_GATE_SCALAR, 33, 1, false}};
+    for (const auto &f : forms)
+        check_form(f.H, f.D, f.io, f.gate, f.n, f.chunks, f.one, f.one);
+    // two of one chunk: forward segment by segment, backward in one
+    for (int gate : {SF_GATE_SCALAR, SF_GATE_VECTOR}) check_form(5, 64, SF_F32, gate, 2, 1, false, true);
+
     sf_tuning t;
     std::memset(&t, 0, sizeof t);
     t.ts = 128;

@@ -286,6 +286,27 @@ def test_chain_replay_starts_from_the_given_states(name, D, io):
     assert torch.equal(a[4], b[4])
 
 
+@pytest.mark.parametrize("name,D,io", [("mid_bf16", 128, "bf16"), ("tiny_fp32", 64, "f32"), ("vector_gate", 128, "bf16")])
+def test_two_segments_of_one_chunk(name, D, io):
+    """Two segments of one chunk each: the forward runs segment by segment and keeps
+    nothing, the backward as one set of launches from S_bnd, with the kept states' buffer
+    or without it."""
+    w = synth.workload(name, B=1, H=3, D=D, io=io)
+    seg_lens = [64, 64]
+    inp = synth.make_inputs(w, device="cpu", seed=97 + D, dS_out_std=0.1, L=128)
+    g = on_gpu(inp)
+    say(f"[chain] two segments of one chunk {name} D={D} {io}")
+    assert not in_one(g, seg_lens, 0) and sf.chain_ckpt_bytes(g["q"], g["g"], seg_lens, ts=0) == 0
+    a = run_chain(g, seg_lens, ts=0, overlap=False)
+    _, n = launches(lambda t: sf.chain_bwd(g["q"], g["k"], g["v"], g["g"], seg_lens, a["S_bnd"], g["dO"], g["dS_out"], ts=0,
+                                           overlap=False, timing=t), "bwd_dq")
+    assert n == {"bwd_dq": 1}
+    b = run_chain(g, seg_lens, ts=0, overlap=False, keep=True)
+    for key in a:
+        assert torch.equal(a[key], b[key]), key
+    check_chain(io, inp, a, seg_lens)
+
+
 KEPT_CASES = [("mid_bf16", 128, "bf16", 0), ("mid_bf16", 128, "bf16", 64), ("mid_bf16", 64, "bf16", 128),
               ("tiny_fp32", 64, "f32", 128), ("vector_gate", 128, "bf16", 128), ("vector_gate", 64, "f32", 64),
               ("mid_bf16", 128, "bf16", 128), ("tiny_fp32", 128, "f32", 128), ("vector_gate", 64, "f32", 128),
