@@ -1518,9 +1518,16 @@ sf_status gdn_launch(int phase, const sf::GdnArgs &a, int D, hipStream_t s, sf_t
 }
 
 
+// Whether a forward's output walk forms T itself: for a call of one chunk a launch for
+// T ahead of the walk costs more than it takes off it (256 CUs, us, T in a launch of its
+// own / in the walk: B H 4 24.6 / 21.9, 200 23.4 / 21.1, 256 24.4 / 22.5).  Beyond a
+// workgroup per CU the walk's second workgroup, which LDS has no room for then, is
+// worth the launch, and so is T of two segments at once (B H 128 35.2 / 38.7).
+bool gdn_own_t(const Shape &r) { return r.L == 64 && (int64_t)r.B * r.H <= device_cus(); }
+
 // the phases of one delta-rule segment call, in order, on one stream
 sf_status gdn_run_fwd(const sf::GdnArgs &a, int D, hipStream_t s, sf_timing *tm) {
-    TRY(gdn_launch(sf::GDN_TPREP, a, D, s, tm));
+    if (a.tw) TRY(gdn_launch(sf::GDN_TPREP, a, D, s, tm));
     if (a.n_super > 1) {
         TRY(gdn_launch(sf::GDN_PREP, a, D, s, tm));
         TRY(gdn_launch(sf::GDN_SCAN, a, D, s, tm));
@@ -1582,7 +1589,7 @@ sf_status sf_gdn_fwd(const sf_shape *shape, const void *q, const void *k, const 
     a.beta = beta;
     a.S_in = S_in;
     a.o = o;
-    a.tw = o;
+    a.tw = gdn_own_t(r) ? nullptr : o;
     a.n_cu = device_cus();
     a.v_new = v_new;
     a.S_out = S_out;
@@ -1732,13 +1739,15 @@ sf_status sf_gdn_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *
                      span(ckpt, (int64_t)kneed, "ckpt"), wsrange(ws, W.total)}));
     const int64_t SSB = (int64_t)r.B * r.H * r.D * r.D;
     const GdnFwdWs F = gdn_fwd_ws_n(r, p.n_max, p.n_max);
+    const bool own_t = gdn_own_t(r);
     std::vector<sf::GdnArgs> seg(n_seg);
     int64_t tok = 0;
     size_t kofs = 0;
     for (int i = 0; i < n_seg; ++i) {
         sf::GdnArgs &a = seg[i];
         a = gdn_seg_args(r, tok, seg_len[i], p.ts[i], q, k, v, g, beta);
-        a.o = a.tw = (void *)offset_x(r, o, tok);
+        a.o = (void *)offset_x(r, o, tok);
+        a.tw = own_t ? nullptr : a.o;
         a.v_new = v_new ? (void *)offset_x(r, v_new, tok) : nullptr;
         a.S_in = S_bnd + i * SSB;
         a.S_out = S_bnd + (i + 1) * SSB;
@@ -1768,7 +1777,7 @@ sf_status sf_gdn_chain_fwd(const sf_shape *shape, int32_t n_seg, const int64_t *
     // waits on main for ST(i-1), queued before Pre(i+1) overwrites workspace set
     // (i+1) % 2 = (i-1) % 2.
     // T of every segment's chunks first, in one launch.
-    {
+    if (!own_t) {
         sf::GdnArgs t = gdn_seg_args(r, 0, r.L, 64, q, k, v, g, beta);
         t.tw = o;
         TRY(gdn_launch(sf::GDN_TPREP, t, r.D, mn, timing_of(tuning)));

@@ -367,11 +367,11 @@ struct DmaTri {
 // pairs, and neither W nor Ubar is formed).  V joins X's accumulators through an
 // MFMA with the identity, which is exact and needs no 2-byte LDS reads.  Nothing
 // but P and the staged tiles is shared between waves, so a chunk has two barriers
-// (three with P).
-template <typename T, int D, int MODE>
+// (three with P).  TPRE: T comes from k_gdn_tprep; else the walk forms it (D = 64, and
+// D = 128 for forward calls of one chunk, which are two launches otherwise).
+template <typename T, int D, int MODE, bool TPRE = D == 128>
 __global__ void __launch_bounds__(256, 2) k_gdn_walk(GdnArgs a) {
     constexpr bool PREP = MODE == W_PREP, OUTP = MODE == W_OUT;  // STORE: states only
-    constexpr bool TPRE = D == 128;                              // T comes from k_gdn_tprep
     constexpr int NT = 256, NK = D / 16, NCT = GdnCols<D>::NCT;
     constexpr int LDN = D + pad<T>(), SWX = swx<T, D>(), LDA = C + 4;
     __shared__ __attribute__((aligned(16))) T sQ[OUTP ? C * D : 8];    // DmaTile
@@ -1745,6 +1745,10 @@ hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0
         break;
     case GDN_SCAN: hipExtLaunchKernelGGL((k_gdn_scan<D>), scan_grid<D>(bh), dim3(4 * D), 0, s, e0, e1, 0, a); break;
     case GDN_OUT:
+        if (D == 128 && !a.tw) {
+            hipExtLaunchKernelGGL((k_gdn_walk<__bf16, D, W_OUT, false>), dim3(bh * a.n_super), wblk, 0, s, e0, e1, 0, a);
+            break;
+        }
         hipExtLaunchKernelGGL((k_gdn_walk<__bf16, D, W_OUT>), dim3(bh * a.n_super), wblk, 0, s, e0, e1, 0, a);
         break;
     case GDN_STORE:
@@ -1776,7 +1780,8 @@ hipError_t gdn_phase_d(int phase, const GdnArgs &a, hipStream_t s, hipEvent_t e0
 hipError_t launch_gdn_phase(int phase, const GdnArgs &a, int D, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (a.n_super < 1) return hipErrorInvalidValue;
     const bool multi = a.n_super > 1;
-    if (D == 128 && phase != GDN_SCAN && phase != GDN_DSCAN && phase != GDN_DCHUNK && a.L >= C && !a.tw)
+    if (D == 128 && phase != GDN_SCAN && phase != GDN_DSCAN && phase != GDN_DCHUNK && a.L >= C && !a.tw &&
+        !(phase == GDN_OUT && a.L == C))  // (of one chunk: the walk forms T)
         return hipErrorInvalidValue;
     switch (phase) {
     case GDN_TPREP:

@@ -121,7 +121,8 @@ struct GdnArgs {
     int32_t B, H, n_super, ts, n_prep, n_x;  // n_x: workgroups of the per-chunk gradient kernel
     int32_t scan_out;  // forward chains: maps of every superchunk, the scan writes S_out
     int32_t n_cu;      // compute units of the device
-    void *tw;          // D = 128: the output (o or dq) whose rows hold T until it is written
+    void *tw;          // D = 128: the output (o or dq) whose rows hold T until it is written;
+                       // NULL: the output walk forms T (calls of one chunk)
     int64_t L, sx_b, sx_l, sx_h, sg_b, sg_l, sg_h;
 };
 // One kernel of the delta-rule pipeline: T of every chunk (D = 128); forward prep

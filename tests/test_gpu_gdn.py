@@ -56,6 +56,33 @@ def test_gdn_parity(D):
     assert_close("v_new", vn, ru, "bf16")
 
 
+@pytest.mark.parametrize("H", [3, 257])
+def test_gdn_one_chunk(H):
+    """A forward of one chunk is one launch up to a head per CU (its walk forms T), two
+    beyond; either way, and as a chain, bitwise the first chunk of a longer call (T from
+    a launch of its own), V^new included, and within the oracle's bar."""
+    say(f"[gdn] one chunk H={H}")
+    inp = synth.make_gdn_inputs(1, 128, H, 128, seed=4150 + H)
+    g = {k: (v.to(DEV) if isinstance(v, torch.Tensor) else v) for k, v in inp.items()}
+    x = [g[k] for k in ("q", "k", "v", "g", "beta")]
+    first = [t[:, :64] for t in x]
+    o2, _, vn2 = sf.gdn_fwd(*x, g["S_in"], ts=128, with_v_new=True)
+    timer = sf.KernelTimer(("gdn_prep", "gdn_out"), capacity=16)
+    o, S, vn = sf.gdn_fwd(*first, g["S_in"], with_v_new=True, timing=timer)
+    kernels = {k: n for k, (_, n) in timer.read().items()}
+    timer.close()
+    cus = torch.cuda.get_device_properties(DEV).multi_processor_count
+    assert kernels == ({"gdn_out": 1} if H <= cus else {"gdn_prep": 1, "gdn_out": 1})
+    assert torch.equal(o, o2[:, :64]) and torch.equal(vn, vn2[:, :64])
+    oc, Sc = sf.gdn_chain_fwd(*first, (64,), g["S_in"])[:2]
+    assert torch.equal(o, oc) and torch.equal(S, Sc[1])
+    heads = [0, H // 2, H - 1]
+    sub = {k: (v[:, :64] if k != "S_in" else v) for k, v in inp.items() if isinstance(v, torch.Tensor)}
+    ro, rS = ref(sub, heads)
+    assert_close("o", o[:, :, heads], ro, "bf16")
+    assert_close("S_out", S[:, heads], rS, "bf16")
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("ts", [64, 192, 256, 448])
 def test_gdn_superchunks(D, ts):
