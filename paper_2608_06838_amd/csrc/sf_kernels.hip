@@ -1269,11 +1269,12 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
     constexpr int NTW = 64 * D / (16 * SF_NCT_WALK);
     constexpr int NT1 = 64 * D / 16;
     // up to one item per CU there is no second workgroup to cover a wave's waits:
-    // twice the waves, one column tile each, instead of two (bf16, d = 128: prep,
-    // 220 items of 6 chunks 30.1 -> 18.0 us, but 1000 of 66 165 -> 179; dq walk, 128
-    // of 8 53.5 -> 49.0, 256 of 4 46.1 -> 43.2; the output walk is the same either
-    // way, 43; fp32, d = 64, 32 of 1: prep 9.9 -> 8.4, output walk 16.0 -> 12.8, dq
-    // walk 16.7 -> 13.8; fp32 at d = 128 keeps its one column split)
+    // twice the waves, one column tile each, instead of two (256 CUs, us; bf16, d = 128:
+    // prep, 256 items of 2 chunks 12.0 -> 9.4, of 64 143 -> 133; dq walk, 128 of 16 80
+    // -> 70, 256 of 2 21.5 -> 19.3, of 64 349 -> 329; the output walk is the same either
+    // way; bf16, d = 64, 256 of 2: output walk 12.7 -> 10.8, of 64 219 -> 159, dq walk
+    // 242 -> 191; fp32, d = 64, 256 of 32: output walk 324 -> 210, dq walk 345 -> 230;
+    // fp32 at d = 128 keeps its one column split)
     const bool alone = (sizeof(T) == 2 || D == 64) && (int64_t)grid.x <= (int64_t)a.n_cu;
     switch (kind) {
     case SF_K_FWD_PREP:
@@ -1313,8 +1314,9 @@ static hipError_t launch_td(int kind, const SegArgs &a, hipStream_t s, hipEvent_
         break;
     case SF_K_BWD_DKV:
         // a launch that would leave half the CUs idle puts the two roles on CUs of
-        // their own (128 items of 8 chunks: 59.5 -> 43.9 us; with a workgroup per CU
-        // either way the one-workgroup form is the faster, 613 against 816 us)
+        // their own (128 items of 16 chunks 100 -> 84 us, of 64 372 -> 314; with a
+        // workgroup per CU either way the one-workgroup form is the faster, 613 against
+        // 816 us)
         if ((sizeof(T) == 4 && D == 128) || (D == 128 && 2 * (int64_t)grid.x <= (int64_t)a.n_cu)) {
             const int64_t items = (int64_t)a.B * a.H * a.n_super;
             hipExtLaunchKernelGGL((k_bwd_dkv_wg<T, D>), dim3((unsigned)((items + 7) / 8 * 16)), dim3(64 * D / 16), 0, s,
