@@ -331,9 +331,9 @@ CkptLayout ckpt_layout(const Shape &r, int64_t L, int ts) { return ckpt_layout_n
 // scan hands out the boundary states.  Chosen when chunk_cost says so, a set of
 // launches and their empty first and last moments counting kSeg steps (35 us of
 // launches and prologues at 13 us a step), and no segment has more than one
-// workgroup per CU (H 16, 8 of 4096, kept states: 1.28 ms a step segment by segment,
-// 1.09 in one; vector gate, B 2 H 16, 16 of 4096: 7.23, 6.69; but the 256K layer, 480
-// or more a segment: 14.29, 14.65).  The choice depends on the shape and the tuning
+// workgroup per CU (H 16, 8 of 4096, kept states: 1.08 ms a step segment by segment,
+// 1.07 in one; vector gate, B 2 H 16, 16 of 4096: 6.79, 6.60; H 5, 16 of 512: 787 us,
+// 250; but the 256K layer, 480 or more a segment: 14.29, 14.65).  The choice depends on the shape and the tuning
 // alone, never on the kept states, so a backward that replays and one that reads
 // them take the same superchunks; with a given ts, whose kept states are sized
 // segment by segment, the chain's have to fit that size.  No segment gets longer
