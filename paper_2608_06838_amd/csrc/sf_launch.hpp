@@ -9,7 +9,8 @@
 namespace sf {
 
 // segments of a chain that one set of launches can cover: their table travels in the
-// kernel arguments; longer chains run segment by segment
+// kernel arguments; longer chains run segment by segment (H 16, 512 tokens each: 41.8 us
+// a segment, forward and backward, for 32 of them, 60.9 for 33)
 constexpr int MAX_MERGED = 32;
 
 // One segment (or one superchunk-parallel launch over a segment).  Token
